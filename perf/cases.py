@@ -1,0 +1,619 @@
+"""Workloads of the EOFA library for performance measurements.
+
+    listed()             the fixed cases
+    draw(rng)            one more case from the ranges the listed ones stand for
+    prepare(case, seed)  context, gauge field and inputs on the GPU, made from the seed
+    run(state)           one pass through the public entry points; returns what it computes
+    work(case)           bytes and floating-point operations a pass cannot do without
+    exact(case, seed)    the same outputs from plain torch operations in 64 bits (None where that takes long)
+
+The lattices are those of the workloads in paper_1710_09621_amd/inputs.py (4^4 with Ns = 8, 16^3 x 32, 24^3 x 48
+and 32^3 x 64 with Ns = 16), the 8^4 equilibrium lattice of the HMC and ragged ones in between.
+"""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+from paper_1710_09621_amd import eofa as E
+from paper_1710_09621_amd import inputs as IN
+from paper_1710_09621_amd import mpseq
+
+M0 = 1.3
+DEV = "cuda:0"
+TOL = 1e-11  # true residual of the solves: outputs of two solves then agree far below 1e-9
+
+
+def _case(name, kind, dims, Ns, **kw):
+    c = dict(kind=kind, lx=dims[0], ly=dims[1], lz=dims[2], lt=dims[3], Ns=Ns, eps=0.5)
+    if name:
+        c["name"] = name
+    c.update(kw)
+    return c
+
+
+def listed():
+    return [
+        # the smallest call: one operator application in a test or an analysis script (launch latency)
+        _case("apply_dt_4x4x4x4", "apply", (4, 4, 4, 4), 8, op="DT", prec=0, mp=0.05, mm=1.0, eps=0.3),
+        # FP32 storage on a ragged lattice (Lx / 2 odd, no extent a power of two except Ns)
+        _case("apply_ht_fp32_10x6x12x14", "apply", (10, 6, 12, 14), 16, op="HT", prec=1, mp=0.1, mm=1.0),
+        # the operator on the largest lattice of the workloads: residual checks, eigenvalue and analysis codes
+        _case("apply_dt_32x32x32x64", "apply", (32, 32, 32, 64), 16, op="DT", prec=0, mp=0.01, mm=0.1, eps=0.7),
+        # H^-1 phi on the smallest workload (two FP64 solves of about 100 iterations): latency of the CG loop
+        _case("hinv_fp64_4x4x4x4", "hinv", (4, 4, 4, 4), 8, prec=0, m1=0.05, m2=1.0, graph=0, eps=0.3),
+        # a mixed-precision 5D solve at the largest Ns on a ragged lattice
+        _case("solve_fp32_12x6x10x8_ns32", "solve", (12, 6, 10, 8), 32, prec=1, m1=0.1, m2=1.0, graph=1),
+        # the tuned time to solution: the three new-MP actions of one source in one FP16-column batch with graphs
+        _case("newmp_fp16_16x16x16x32", "batch", (16, 16, 16, 32), 16, prec=2, m1=0.01, m2=0.1, graph=1),
+        # an FP64 action and its fermion force on the lattice of Sec. III under a stored t-walk schedule
+        _case("force_fp64_24x24x24x48", "force", (24, 24, 24, 48), 16, prec=0, m1=0.2, m2=1.0, graph=0, tuned=1, eps=0.6),
+        # a heat-bath pseudofermion: the poles of the rational approximation as one batch
+        _case("heatbath_fp16_8x8x8x16", "heatbath", (8, 8, 8, 16), 16, prec=2, m1=0.05, m2=1.0, graph=0),
+        # one molecular-dynamics trajectory of the new-MP splitting on the time scales of Sec. III
+        _case("trajectory_8x8x8x8", "trajectory", (8, 8, 8, 8), 8, prec=2, m1=0.05, m2=0.3, k0=480, k1=12, k2=6),
+        # the gauge force alone, evaluated at every innermost step of a trajectory
+        _case("gauge_force_24x24x24x48", "gauge", (24, 24, 24, 48), 16, beta=6.2),
+        # the learned preconditioner: one application (once per FGCR iteration) and one training step
+        _case("cnn_apply_16x16x16x32", "cnn_apply", (16, 16, 16, 32), 16),
+        _case("cnn_train_16x16x16x32", "cnn_train", (16, 16, 16, 32), 16, lr=2e-4),
+    ]
+
+
+# volume x Ns drawn per kind (log-uniform) and the Ns it takes
+RANGES = {
+    "apply": (2048, 12_000_000, (4, 8, 16, 32)),
+    "hinv": (2048, 200_000, (4, 8, 16)),
+    "solve": (8192, 1_000_000, (8, 16, 32)),
+    "batch": (32768, 2_100_000, (8, 16, 32)),
+    "force": (8192, 1_500_000, (8, 16, 32)),
+    "heatbath": (4096, 260_000, (8, 16)),
+    "trajectory": (2048, 20_000, (8,)),
+    "gauge": (256 * 8, 600_000 * 8, (8,)),
+    "cnn_apply": (8192, 2_100_000, (8, 16, 32)),
+    "cnn_train": (8192, 2_100_000, (8, 16, 32)),
+}
+
+
+def _dims(rng, target):
+    """Even extents, round ones in half of the draws, with a volume within 30% of the target (or near it)."""
+    best, off = None, math.inf
+    plain = rng.random() < 0.5
+    for _ in range(400):
+        if plain:
+            d = [rng.choice((4, 8, 12, 16, 24)) for _ in range(3)] + [rng.choice((4, 8, 12, 16, 24, 32, 48))]
+        else:
+            d = [2 * rng.randint(2, 14) for _ in range(3)] + [2 * rng.randint(2, 24)]
+        e = abs(math.log(d[0] * d[1] * d[2] * d[3] / target))
+        if e < off:
+            best, off = tuple(d), e
+        if e < 0.26:
+            break
+    return best
+
+
+def draw(rng):
+    kind = rng.choice(list(RANGES))
+    lo, hi, nss = RANGES[kind]
+    Ns = rng.choice(nss)
+    n5 = math.exp(rng.uniform(math.log(lo), math.log(hi)))
+    dims = _dims(rng, max(256.0, n5 / Ns))
+    light, heavy = round(rng.uniform(0.06, 0.25), 3), rng.choice((0.5, 1.0))
+    kw = dict(eps=rng.choice((0.3, 0.5, 0.6)))
+    if kind == "apply":
+        kw.update(op=rng.choice(("DT", "DT_DAG", "HT", "DW", "HOP", "AT_INV", "SCHUR", "SCHUR_DAG", "SCHUR_NORMAL", "DODWF",
+                                 "DODWF_DAG")), prec=rng.choice((0, 0, 1)), mp=light, mm=heavy)
+    elif kind == "hinv":
+        kw.update(prec=0, m1=light, m2=heavy, graph=rng.choice((0, 1)))
+    elif kind == "solve":
+        kw.update(prec=rng.choice((0, 1, 2)), m1=light, m2=heavy, graph=rng.choice((0, 1)))
+    elif kind == "batch":
+        kw.update(prec=rng.choice((0, 1, 2)), m1=round(light / 3, 3), m2=light, graph=rng.choice((0, 1)))
+    elif kind == "force":
+        kw.update(prec=rng.choice((0, 2)), m1=light, m2=heavy, graph=0, tuned=0)
+    elif kind == "heatbath":
+        kw.update(prec=rng.choice((0, 2)), m1=light, m2=heavy, graph=0)
+    elif kind == "trajectory":
+        k2 = rng.choice((2, 4))
+        kw.update(prec=rng.choice((0, 2)), m1=light, m2=0.5, k0=40 * k2, k1=2 * k2, k2=k2)
+    elif kind == "gauge":
+        kw.update(beta=6.2)
+    elif kind == "cnn_train":
+        kw.update(lr=2e-4)
+    return _case(None, kind, dims, Ns, **kw)
+
+
+# ------------------------------------------------------------------ inputs (plain torch, seeded)
+def _gen(seed, k):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1_000_003 * int(seed) + k)
+    return g
+
+
+def _mm3(a, b):
+    """Products of stacks of 3 x 3 matrices."""
+    return torch.stack([torch.stack([a[..., i, 0] * b[..., 0, j] + a[..., i, 1] * b[..., 1, j] + a[..., i, 2] * b[..., 2, j]
+                                     for j in range(3)], -1) for i in range(3)], -2)
+
+
+def _links(case, seed):
+    """U = exp(i eps theta_a t^a), theta ~ N(0, 1): the near-unit SU(3) links of the workloads."""
+    shape = (case["lt"], case["lz"], case["ly"], case["lx"], 4)
+    th = case["eps"] * 0.5 * torch.randn(shape + (8,), dtype=torch.float64, device=DEV, generator=_gen(seed, 1))
+    t = [th[..., a] for a in range(8)]
+    r3 = 1 / math.sqrt(3)
+    z = torch.zeros_like(t[0])
+    X = torch.stack([torch.complex(z, t[2] + r3 * t[7]), torch.complex(t[1], t[0]), torch.complex(t[4], t[3]),
+                     torch.complex(-t[1], t[0]), torch.complex(z, r3 * t[7] - t[2]), torch.complex(t[6], t[5]),
+                     torch.complex(-t[4], t[3]), torch.complex(-t[6], t[5]), torch.complex(z, -2 * r3 * t[7])], -1)
+    X = X.reshape(shape + (3, 3)) / 16
+    eye = torch.eye(3, dtype=torch.complex128, device=DEV)
+    U = eye.expand_as(X)
+    for n in range(12, 0, -1):  # Taylor polynomial of exp(X / 16), then four squarings
+        U = eye + _mm3(X, U) / n
+    for _ in range(4):
+        U = _mm3(U, U)
+    return U.contiguous()
+
+
+def _gauss(shape, seed, k):
+    return torch.complex(*(math.sqrt(0.5) * torch.randn(shape, dtype=torch.float64, device=DEV, generator=_gen(seed, k + i))
+                           for i in range(2)))
+
+
+def _shape4(case):
+    return (case["lt"], case["lz"], case["ly"], case["lx"], 4, 3)
+
+
+def _shape5(case):
+    return (case["Ns"],) + _shape4(case)
+
+
+def _cnn_weights(seed):
+    """Near-identity network with 5% noise on the live channels, as the training starts from."""
+    P = torch.zeros((4, 81 * 1024 + 32), dtype=torch.float64, device=DEV)
+    noise = torch.randn((4, 81, 32, 32), dtype=torch.float64, device=DEV, generator=_gen(seed, 9))
+    for l, (cin, cout) in enumerate(((24, 32), (32, 32), (32, 32), (32, 24))):
+        W = torch.zeros((81, 32, 32), dtype=torch.float64, device=DEV)
+        W[:, :cout, :cin] = noise[l, :, :cout, :cin] * (0.05 / math.sqrt(81 * cin))
+        W[40, torch.arange(24), torch.arange(24)] += 1.0
+        P[l, :81 * 1024] = W.reshape(-1)
+    return P.float().reshape(-1)
+
+
+def _actions(case):
+    """The three chiral actions of the new mass preconditioning, (chir, m3, m4, mo)."""
+    return [tuple(a) for a in mpseq.actions("new", case["m1"], [case["m2"]], 1.0)]
+
+
+def _inputs(case, seed):
+    """Everything a pass reads, apart from the context."""
+    k = case["kind"]
+    s = {"U": _links(case, seed)}
+    if k in ("apply", "solve"):
+        s["b"] = _gauss(_shape5(case), seed, 10)
+    elif k in ("hinv", "force", "heatbath", "batch"):
+        s["phi"] = _gauss(_shape4(case), seed, 20)
+    elif k == "trajectory":  # an action's spectrum lies within a factor of two of 1: its fields are close to Gaussian
+        s["phis"] = [_gauss(_shape4(case), seed, 20 + 4 * i) for i in range(3)]
+        s["P"] = torch.randn((4,) + _shape4(case)[:4] + (8,), dtype=torch.float64, device=DEV, generator=_gen(seed, 40))
+    elif k.startswith("cnn"):
+        s["w"] = _cnn_weights(seed)
+        e = _gauss(_shape5(case), seed, 50)
+        if k == "cnn_apply":
+            s["b"] = e
+        else:  # the pair (Dhat^dag Dhat e, e) on the odd sites
+            L = _Lattice(case, s["U"])
+            s["e"] = e * L.odd
+            s["rho"] = L.schur_dag(L.schur(s["e"], 0.01, 0.1), 0.01, 0.1)
+    return s
+
+
+def prepare(case, seed):
+    s = _inputs(case, seed)
+    dims = (case["lx"], case["ly"], case["lz"], case["lt"])
+    ctx = E.Context(dims, case["Ns"], M0, IN.optimal_omega(case["Ns"]))
+    ctx.set_gauge(s["U"])
+    s.update(ctx=ctx, case=dict(case))
+    if "prec" in case:
+        s["p"] = E.params(tol=TOL, prec=case["prec"], max_iter=20000, use_graph=case.get("graph", 0))
+    if case.get("tuned"):  # a schedule kept from an earlier autotuning run: t-walk with the x neighbours from LDS
+        want = [c for c in ctx.schedule_candidates(E.FP64) if c[0] == 5 and c[2:5] == [4, 4, 16]]
+        ctx.set_schedule(want[0] if want else ctx.schedule_candidates(E.FP64)[-1], E.FP64)
+    if case["kind"].startswith("cnn"):
+        ctx.set_precond(s["w"].cpu().numpy())
+    return s
+
+
+def run(s):
+    c, ctx, k = s["case"], s["ctx"], s["case"]["kind"]
+    if k == "apply":
+        return ctx.apply(c["op"], s["b"], c["mp"], c["mm"], prec=c["prec"])
+    if k == "solve":
+        return ctx.solve_ht(s["b"], c["m1"], c["m2"], s["p"])[0]
+    if k == "hinv":
+        r = ctx.hinv(s["phi"], c["m1"], c["m2"], s["p"])
+        return {"out": r.out, "S": r.S}
+    if k == "batch":
+        rs = ctx.chiral_action_batch(_actions(c), [s["phi"]] * 3, s["p"])
+        return [{"out": r.out, "S": r.S} for r in rs]
+    if k == "force":
+        F, S, _ = ctx.chiral_force(-1, c["m1"], c["m1"], c["m2"], s["phi"], s["p"])
+        return {"F": F, "S": S}
+    if k == "heatbath":
+        return ctx.chiral_heatbath(-1, c["m1"], c["m1"], c["m2"], s["phi"], p=s["p"])[0]
+    if k == "trajectory":
+        U, P = s["U"].clone(), s["P"].clone()
+        acts = [(1 if i == 2 else 2,) + a + (s["phis"][i],) for i, a in enumerate(_actions(c))]
+        info = ctx.md_trajectory(U, P, acts, 6.2, 1.0, [c["k0"], c["k1"], c["k2"]], p=s["p"], chrono=True)
+        return {"U": U, "P": P, "H0": info["H0"], "H1": info["H1"]}
+    if k == "gauge":
+        return ctx.gauge_force(s["U"], c["beta"])
+    if k == "cnn_apply":
+        return ctx.cnn_apply(s["b"])
+    loss, grad = ctx.cnn_train_step(s["rho"], s["e"], lr=c["lr"], want_grad=True)
+    return {"loss": loss, "grad": grad}
+
+
+# ------------------------------------------------------------------ what a pass cannot do without
+def _iters(case, m3, m4):
+    """CG iterations of a solve to 1e-11, roughly (measured: about 60 at heavy masses, 1 / sqrt(m) growth below)."""
+    return 50 + 45 / math.sqrt(max(min(m3, m4), 1e-3))
+
+
+def work(case):
+    V, Ns, k = case["lx"] * case["ly"] * case["lz"] * case["lt"], case["Ns"], case["kind"]
+    f5, f4, links = 192.0 * V * Ns, 192.0 * V, 4 * 144.0 * V
+    hop, site = 1320.0 * V * Ns, 24 * 10.0 * V * Ns  # all 5D sites: hop over 8 neighbours, s-space operator
+    cg = 2 * hop + 2 * site + 24 * 12.0 * V * Ns / 2  # one iteration: four half-lattice hops and the updates
+    if k == "apply":
+        n = 2 if case["op"] == "SCHUR_NORMAL" else 1
+        return {"bytes": 2 * f5 + links, "flops": n * (hop + site)}
+    if k == "gauge":
+        return {"bytes": links + 4 * 64.0 * V, "flops": 4.0 * V * 13 * 198}
+    if k.startswith("cnn"):
+        rows = V * Ns / 2
+        macs = 81 * (24 * 32 + 32 * 32 + 32 * 32 + 32 * 24) * rows
+        return {"bytes": 2 * f5, "flops": 2 * macs * (1 if k == "cnn_apply" else 3)}
+    b = {0: 192, 1: 96, 2: 52}[case["prec"]]  # bytes of a Krylov column
+    it = V * Ns / 2 * b * 18.5  # bytes of an iteration, every field read or written once by each kernel
+    m1, m2 = case["m1"], case["m2"]
+    if k == "solve":
+        n, io = _iters(case, m1, m2), 2 * f5
+    elif k == "hinv":
+        n, io = _iters(case, m1, m1) + _iters(case, m1, m2), 2 * f4
+    elif k == "batch":
+        n, io = sum(_iters(case, a[1], a[2]) for a in _actions(case)), 4 * f4
+    elif k == "force":
+        n, io = _iters(case, m1, m1), f4 + 4 * 64.0 * V
+    elif k == "heatbath":
+        n, io = 5 * _iters(case, m1, m1), 2 * f4
+    else:
+        acts = _actions(case)
+        n = sum((2 * (case["k1"] if i == 2 else case["k2"]) + 1) * _iters(case, a[1], a[2]) for i, a in enumerate(acts))
+        io = (2 * case["k0"]) * (2 * links + 2 * 4 * 64.0 * V)
+    return {"bytes": n * it + io + links, "flops": n * cg}
+
+
+# ------------------------------------------------------------------ plain 64-bit reference
+class _Lattice:
+    """The operators of the method on full canonical 5D fields [s][t][z][y][x][spin][colour], in torch."""
+
+    def __init__(self, case, U):
+        self.Ns, self.omega = case["Ns"], IN.optimal_omega(case["Ns"])
+        self.U = U.clone()
+        self.U[-1, ..., 3, :, :] *= -1  # antiperiodic in t
+        n = [case["lt"], case["lz"], case["ly"], case["lx"]]
+        g = torch.zeros(n, dtype=torch.int64, device=DEV)
+        for d in range(4):
+            g += torch.arange(n[d], device=DEV).reshape([-1 if i == d else 1 for i in range(4)])
+        self.odd = (g % 2 == 1)[None, ..., None, None].to(torch.complex128)
+        self.mats = {}
+
+    @staticmethod
+    def gamma(p, mu):
+        u0, u1, d0, d1 = (p[..., i, :] for i in range(4))
+        if mu == 0:
+            r = (-1j * d1, -1j * d0, 1j * u1, 1j * u0)
+        elif mu == 1:
+            r = (-d1, d0, u1, -u0)
+        elif mu == 2:
+            r = (-1j * d0, 1j * d1, 1j * u0, -1j * u1)
+        else:
+            r = (d0, d1, u0, u1)
+        return torch.stack(r, -2)
+
+    @staticmethod
+    def g5(p):
+        return torch.cat((p[..., :2, :], -p[..., 2:, :]), -2)
+
+    @staticmethod
+    def link(U, p, dag):
+        if dag:
+            U = U.conj().transpose(-1, -2)
+        U = U[..., None, :, :]  # over spins
+        return torch.stack([U[..., c, 0] * p[..., 0] + U[..., c, 1] * p[..., 1] + U[..., c, 2] * p[..., 2] for c in range(3)], -1)
+
+    def hop(self, p):
+        """sum_mu (1 - gamma) U p(x + mu) + (1 + gamma) U^dag p(x - mu), slice by slice."""
+        out = torch.empty_like(p)
+        for s in range(p.shape[0]):
+            q, acc = p[s], None
+            for mu in range(4):
+                Um, d = self.U[..., mu, :, :], 3 - mu
+                f = self.link(Um, torch.roll(q, -1, d), False)
+                b = torch.roll(self.link(Um, q, True), 1, d)
+                t = f + b + self.gamma(b - f, mu)
+                acc = t if acc is None else acc + t
+            out[s] = acc
+        return out
+
+    def smat(self, what, mp, mm):
+        """Dense Ns x Ns matrices of the upper and the lower spins."""
+        key = (what, mp, mm)
+        if key not in self.mats:
+            n, w, res = self.Ns, self.omega, []
+            for m, low in ((mp, False), (mm, True)):
+                L = np.eye(n, k=-1)
+                L[0, n - 1] = -m
+                if low:
+                    L = L.T
+                Mx = np.diag(w ** -0.5) @ (np.eye(n) - L) @ np.linalg.inv(np.eye(n) + L) @ np.diag(w ** -0.5)
+                A = (4 - M0) * np.eye(n) + Mx
+                W = np.diag(w) @ (np.eye(n) + L)
+                R = {"M": Mx, "MT": Mx.T, "Ainv": np.linalg.inv(A), "AinvT": np.linalg.inv(A).T, "W": W, "WT": W.T,
+                     "1-L": np.eye(n) - L, "1-LT": (np.eye(n) - L).T}[what]
+                res.append(torch.from_numpy(np.ascontiguousarray(R)).to(DEV, torch.complex128))
+            self.mats[key] = res
+        return self.mats[key]
+
+    def s_op(self, p, what, mp, mm):
+        up, lo = self.smat(what, mp, mm)
+        n = p.shape[0]
+        return torch.cat([(A @ h.reshape(n, -1)).reshape(h.shape) for A, h in ((up, p[..., :2, :].contiguous()),
+                                                                              (lo, p[..., 2:, :].contiguous()))], -2)
+
+    def dw(self, p):
+        return (4 - M0) * p - 0.5 * self.hop(p)
+
+    def dt(self, p, mp, mm):
+        return self.dw(p) + self.s_op(p, "M", mp, mm)
+
+    def dt_dag(self, p, mp, mm):
+        return self.g5(self.dw(self.g5(p))) + self.s_op(p, "MT", mp, mm)
+
+    def schur(self, v, mp, mm):
+        v = v * self.odd
+        return v - 0.25 * self.s_op(self.hop(self.s_op(self.hop(v), "Ainv", mp, mm)), "Ainv", mp, mm)
+
+    def schur_dag(self, v, mp, mm):
+        v = v * self.odd
+        t = self.g5(self.hop(self.g5(self.s_op(v, "AinvT", mp, mm))))
+        return v - 0.25 * self.g5(self.hop(self.g5(self.s_op(t, "AinvT", mp, mm))))
+
+    def apply(self, op, p, mp, mm):
+        if op == "DT":
+            return self.dt(p, mp, mm)
+        if op == "DT_DAG":
+            return self.dt_dag(p, mp, mm)
+        if op == "HT":
+            return self.g5(self.dt(p, mp, mm)).flip(0)
+        if op == "DW":
+            return self.dw(p)
+        if op == "HOP":
+            return self.hop(p)
+        if op == "AT_INV":
+            return self.s_op(p, "Ainv", mp, mm)
+        if op == "DODWF":
+            return self.dw(self.s_op(p, "W", mp, mm)) + self.s_op(p, "1-L", mp, mm)
+        if op == "DODWF_DAG":
+            return self.s_op(self.g5(self.dw(self.g5(p))), "WT", mp, mm) + self.s_op(p, "1-LT", mp, mm)
+        if op == "SCHUR":
+            return self.schur(p, mp, mm)
+        if op == "SCHUR_DAG":
+            return self.schur_dag(p, mp, mm)
+        return self.schur_dag(self.schur(p, mp, mm), mp, mm)
+
+    def solve_ht(self, b, mp, mm):
+        """H_T x = b by conjugate gradients on the Schur complement, repeated on the defect."""
+        c = self.g5(b).flip(0)
+        x = torch.zeros_like(b)
+        cn = float(torch.linalg.vector_norm(c))
+        for _ in range(6):
+            res = c - self.dt(x, mp, mm)
+            rel = float(torch.linalg.vector_norm(res)) / cn
+            if rel < 3e-15:
+                break
+            ue = self.s_op(res * (1 - self.odd), "Ainv", mp, mm)
+            rhs = self.s_op(self.odd * (res + 0.5 * self.hop(ue)), "Ainv", mp, mm)
+            r = self.schur_dag(rhs, mp, mm)
+            d, p = torch.zeros_like(r), r.clone()
+            rr = r0 = float((r.conj() * r).sum().real)
+            for _ in range(3000):
+                if rr <= r0 * max(1e-12, 2e-16 / rel) ** 2 or rr == 0.0:
+                    break
+                w = self.schur(p, mp, mm)
+                al = rr / float((w.conj() * w).sum().real)
+                d += al * p
+                r -= al * self.schur_dag(w, mp, mm)
+                new = float((r.conj() * r).sum().real)
+                p = r + (new / rr) * p
+                rr = new
+            xe = self.s_op((1 - self.odd) * (res + 0.5 * self.hop(d)), "Ainv", mp, mm)
+            x = x + d + xe
+        return x
+
+    def action(self, chir, m3, m4, mo, phi):
+        """(A phi, H_T^-1 Om P phi) of a chiral action."""
+        Om = torch.tensor([(-1) ** (s + 1) / math.sqrt(self.omega[s]) for s in range(self.Ns)], dtype=torch.complex128, device=DEV)
+        ph = torch.zeros_like(phi)
+        sl = slice(0, 2) if chir > 0 else slice(2, 4)
+        ph[..., sl, :] = phi[..., sl, :]
+        x = self.solve_ht(Om.reshape(-1, 1, 1, 1, 1, 1, 1) * ph[None], m3, m4)
+        kf = _kfac(mo, m4 if chir < 0 else m3)
+        y = (Om @ x.reshape(self.Ns, -1)).reshape(phi.shape)
+        out = torch.zeros_like(phi)
+        out[..., sl, :] = (ph + chir * kf * y)[..., sl, :]
+        return out, x
+
+
+def _kfac(mj, mi):
+    return 2 * (mj - mi) / ((1 + mj) * (1 + mi))
+
+
+def _im_tr(M):
+    """Im Tr(lambda^a M), a = 1 .. 8."""
+    m = [[M[..., i, j] for j in range(3)] for i in range(3)]
+    return torch.stack([m[1][0].imag + m[0][1].imag, m[0][1].real - m[1][0].real, m[0][0].imag - m[1][1].imag,
+                        m[2][0].imag + m[0][2].imag, m[0][2].real - m[2][0].real, m[2][1].imag + m[1][2].imag,
+                        m[1][2].real - m[2][1].real,
+                        (m[0][0].imag + m[1][1].imag - 2 * m[2][2].imag) / math.sqrt(3)], -1)
+
+
+def _force(L, chir, m3, m4, mo, phi):
+    """dS/dw^a for U -> exp(i w^a lambda^a / 2) U of every link, and S."""
+    out, x = L.action(chir, m3, m4, mo, phi)
+    S = float((phi.conj() * out).sum().real)
+    ck = chir * _kfac(mo, m4 if chir < 0 else m3)
+    y = L.g5(x).flip(0)
+    F = []
+    for mu in range(4):
+        d, Um = 4 - mu, L.U[..., mu, :, :]
+        xf, yf = torch.roll(x, -1, d), torch.roll(y, -1, d)
+        a, b = xf - L.gamma(xf, mu), x + L.gamma(x, mu)
+        B1 = torch.stack([torch.stack([(a[..., i] * y[..., j].conj()).sum((0, -1)) for j in range(3)], -1) for i in range(3)], -2)
+        B2 = torch.stack([torch.stack([(b[..., i] * yf[..., j].conj()).sum((0, -1)) for j in range(3)], -1) for i in range(3)], -2)
+        F.append(-(ck / 4) * _im_tr(_mm3(Um, B1) - _mm3(B2, Um.conj().transpose(-1, -2))))
+    return torch.stack(F), S
+
+
+def _gauge_force(U, beta):
+    F = []
+    dag = lambda m: m.conj().transpose(-1, -2)  # noqa: E731
+    for mu in range(4):
+        Um, A = U[..., mu, :, :], 0
+        for nu in range(4):
+            if nu == mu:
+                continue
+            Un, dm, dn = U[..., nu, :, :], 3 - mu, 3 - nu
+            Unm = torch.roll(Un, -1, dm)
+            A = A + _mm3(_mm3(Unm, dag(torch.roll(Um, -1, dn))), dag(Un))
+            A = A + torch.roll(_mm3(dag(_mm3(Um, Unm)), Un), 1, dn)
+        F.append((beta / 6) * _im_tr(_mm3(Um, A)))
+    return torch.stack(F)
+
+
+class _Net:
+    """The convolution network on the compressed odd-site lattice, rows [t][z][y][xh][s][channel]."""
+
+    def __init__(self, case, w):
+        self.case = case
+        P = w.double().reshape(4, -1)
+        self.W = [P[l, :81 * 1024].reshape(81, 32, 32) for l in range(4)]
+        self.b = [P[l, 81 * 1024:] for l in range(4)]
+        lt, lz, ly, lxh = case["lt"], case["lz"], case["ly"], case["lx"] // 2
+        g = (torch.arange(lt, device=DEV)[:, None, None, None] + torch.arange(lz, device=DEV)[:, None, None]
+             + torch.arange(ly, device=DEV)[:, None])
+        self.x = (2 * torch.arange(lxh, device=DEV) + (g + 1) % 2)  # x of the odd site (xh, y, z, t)
+
+    def rows(self, f):
+        ix = self.x[None, ..., None, None].expand(f.shape[:4] + (self.x.shape[3],) + f.shape[5:])
+        o = torch.gather(f, 4, ix).reshape(f.shape[0], *self.x.shape, 12)
+        o = torch.view_as_real(o).reshape(f.shape[0], *self.x.shape, 24).permute(1, 2, 3, 4, 0, 5)
+        return torch.nn.functional.pad(o, (0, 8)).contiguous()
+
+    def field(self, r):
+        c = self.case
+        o = torch.view_as_complex(r[..., :24].permute(4, 0, 1, 2, 3, 5).reshape(c["Ns"], *self.x.shape, 12, 2).contiguous())
+        out = torch.zeros(_shape5(c), dtype=torch.complex128, device=DEV)
+        ix = self.x[None, ..., None].expand(o.shape)
+        return out.reshape(c["Ns"], *_shape4(c)[:4], 12).scatter_(4, ix, o).reshape(_shape5(c))
+
+    @staticmethod
+    def shifts():
+        for tap in range(81):
+            yield tap, (tap // 27 - 1, (tap // 9) % 3 - 1, (tap // 3) % 3 - 1, tap % 3 - 1)
+
+    def forward(self, X):
+        acts = [X]
+        for W, b in zip(self.W, self.b):
+            Y = b.expand_as(X).clone()
+            for tap, d in self.shifts():
+                Y += torch.roll(X, [-i for i in d], (0, 1, 2, 3)) @ W[tap].T
+            X = Y
+            acts.append(X)
+        return acts
+
+    def grad(self, acts, dY):
+        out = []
+        for l in range(3, -1, -1):
+            X, n = acts[l], dY.shape[-1]
+            dW, dX = torch.empty((81, 32, 32), dtype=torch.float64, device=DEV), torch.zeros_like(X)
+            for tap, d in self.shifts():
+                Xs = torch.roll(X, [-i for i in d], (0, 1, 2, 3))
+                dW[tap] = dY.reshape(-1, n).T @ Xs.reshape(-1, 32)
+                if l:
+                    dX += torch.roll(dY @ self.W[l][tap], list(d), (0, 1, 2, 3))
+            db = dY.reshape(-1, n).sum(0)
+            cin, cout = (24, 32, 32, 32)[l], (32, 32, 32, 24)[l]
+            dW[:, cout:, :] = 0
+            dW[:, :, cin:] = 0
+            db[cout:] = 0
+            out.insert(0, torch.cat((dW.reshape(-1), db)))
+            dY = dX
+        return torch.cat(out)
+
+
+def exact(case, seed):
+    k = case["kind"]
+    V5 = case["lx"] * case["ly"] * case["lz"] * case["lt"] * case["Ns"]
+    if k == "trajectory" or (k in ("solve", "hinv", "batch", "force") and V5 > 100_000) or (k == "heatbath" and V5 > 20_000):
+        return None
+    s = _inputs(case, seed)
+    if k == "gauge":
+        return _gauge_force(s["U"], case["beta"])
+    if k.startswith("cnn"):
+        N = _Net(case, s["w"])
+        if k == "cnn_apply":
+            X = N.rows(s["b"])
+            n = torch.linalg.vector_norm(X)
+            return N.field(n * N.forward(X / n)[-1])
+        X, T = N.rows(s["rho"]), N.rows(s["e"])
+        n = torch.linalg.vector_norm(X)
+        acts, T = N.forward(X / n), T / n
+        dY = acts[-1] - T
+        return {"loss": float((dY * dY).sum() / (T * T).sum()), "grad": N.grad(acts, dY).cpu().numpy()}
+    L = _Lattice(case, s["U"])
+    if k == "apply":
+        return L.apply(case["op"], s["b"], case["mp"], case["mm"])
+    m1, m2 = case["m1"], case["m2"]
+    if k == "solve":
+        return L.solve_ht(s["b"], m1, m2)
+    act = lambda *a: L.action(*a, s["phi"])[0]  # noqa: E731
+    dot = lambda o: float((s["phi"].conj() * o).sum().real)  # noqa: E731
+    if k == "hinv":
+        o = act(-1, m1, m1, m2) + act(1, m1, m2, m2)
+        return {"out": o, "S": dot(o)}
+    if k == "batch":
+        return [{"out": o, "S": dot(o)} for o in (act(*a) for a in _actions(case))]
+    if k == "force":
+        F, S = _force(L, -1, m1, m1, m2, s["phi"])
+        return {"F": F, "S": S}
+    # heat-bath: A^(-1/2) P_- eta by its Chebyshev series on an interval that holds the spectrum of A
+    lo, hi, n = 0.85 * (1 + m1) / (1 + m2), 1.1, 40
+    t = np.cos(np.pi * (np.arange(n) + 0.5) / n)
+    f = (0.5 * (hi - lo) * t + 0.5 * (hi + lo)) ** -0.5
+    co = [2 / n * float((f * np.cos(j * np.pi * (np.arange(n) + 0.5) / n)).sum()) for j in range(n)]
+    eta = s["phi"].clone()
+    eta[..., :2, :] = 0
+    A = lambda v: (2 * L.action(-1, m1, m1, m2, v)[0] - (hi + lo) * v) / (hi - lo)  # noqa: E731
+    a, b = eta, A(eta)
+    out = 0.5 * co[0] * a + co[1] * b
+    for j in range(2, n):
+        if abs(co[j]) < 1e-15:
+            break
+        a, b = b, 2 * A(b) - a
+        out = out + co[j] * b
+    return out
