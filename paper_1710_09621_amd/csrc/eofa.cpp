@@ -118,7 +118,8 @@ struct eofa_ctx {
     hipStream_t cap_st = nullptr;
     std::map<std::vector<uintptr_t>, hipGraphExec_t> graphs;
     long graph_replays = 0;
-    // workgroup schedules of the hop kernels per storage (0: FP64, 1: FP32, 2: FP16 columns), set by the autotuner
+    // workgroup schedules of the hop kernels per storage (0: FP64, 1: FP32, 2: FP16 columns): default_sched, or set by
+    // the autotuner
     Sched sched[3] = {{0, 0, 1, 1, 1, 1, 0}, {0, 0, 1, 1, 1, 1, 0}, {0, 0, 1, 1, 1, 1, 0}};
     double tuned_ms[3] = {0, 0, 0};
 };
@@ -409,12 +410,13 @@ void cg_iteration(eofa_ctx* ctx, cpx<R>* x, cpx<R>* r, cpx<R>* p, cpx<R>* u, cpx
     {
         auto a = hop_args<R>(ctx, 1);
         a.in = u; a.out = w; a.out2 = wt; a.aux = p; a.opA = Ai; a.opB = Ad; a.cz = (R)-0.25; a.caux = 1;
-        a.red = red_of(ctx, 0, EPI_CG_W); a.done = done;
+        a.red = red_of(ctx, 0, EPI_CG_W); a.done = done; a.defer = true;  // K3 does not read alpha: it finishes |w|^2
         hop<R>(ctx, false, HM_SCHUR_W, true, a, k0 + EOFA_K_SCHUR_W);
     }
     {
         auto a = hop_args<R>(ctx, 0);
         a.in = wt; a.out = at; a.opA = Ad; a.cz = 1; a.caux = 0; a.done = done;
+        a.fin = red_of(ctx, 0, EPI_CG_W); a.fin_n = hop_partials(ctx->g, ctx->Ns, a.sc, 1);
         hop<R>(ctx, true, HM_SITE, false, a, k0 + EOFA_K_HOP_DAG);
     }
     {
@@ -424,7 +426,6 @@ void cg_iteration(eofa_ctx* ctx, cpx<R>* x, cpx<R>* r, cpx<R>* p, cpx<R>* u, cpx
         hop<R>(ctx, true, HM_SCHUR_Q, true, a, k0 + EOFA_K_SCHUR_Q);
     }
     timed(ctx, k0 + EOFA_K_XP, [&] { HIPCHK(launch_cg_xp<R>(x, p, r, ctx->scal, ctx->nh, ctx->st)); });
-    HIPCHK(launch_sync_done(ctx->scal, 1, ctx->st));
 }
 
 // ------------------------------------------------------------------ FP64 CG on Dhat^dag Dhat
@@ -495,8 +496,10 @@ CgOut cg64(eofa_ctx* ctx, const Work64& W, double mp, double mm, double tol_n, i
 }
 
 void ensure_partials_mr(eofa_ctx* ctx) {
-    // batch kernels: one partial per 256 sites x s; launch_mdot: up to 1024 blocks
-    const int need = std::max((int)(((size_t)ctx->g.Vh * ctx->Ns + 255) / 256) + 1, 1024);
+    // batch kernels: one partial per workgroup of a launch of one system (the split form is taken by fewer systems
+    // first); launch_mdot: up to 1024 blocks
+    const int need = std::max((int)std::max(hop_mr_partials(ctx->g, ctx->Ns, 1), hop_mr_partials(ctx->g, ctx->Ns, NRMAX)) + 1,
+                              1024);
     if (ctx->partials_mr && ctx->pstride >= need) return;
     if (ctx->partials_mr) HIPCHK(hipFree(ctx->partials_mr));
     // rows: NRMAX systems of the batch kernels, or 2 x 9 (re, im) dot products of launch_mdot
@@ -986,8 +989,11 @@ void sync_scal_batch(eofa_ctx* ctx, int nr) {
 template <typename R> HopArgsMR<R> mr_args(eofa_ctx* ctx, int par, int nr, bool half = false) {
     HopArgsMR<R> a{};
     HopArgs<R> b = hop_args<R>(ctx, par);
-    a.g = b.g; a.sc = half ? ctx->sched[2] : b.sc; a.par = par; a.nr = nr; a.Uown = b.Uown; a.Uoth = b.Uoth;
+    a.g = b.g; a.sc = half ? ctx->sched[2] : b.sc; a.par = par;
+    if (a.sc.mode >= 3) a.sc = block_sched(ctx->g, ctx->Ns);
+    a.nr = nr; a.Uown = b.Uown; a.Uoth = b.Uoth;
     a.scal = ctx->scal + BATCH_OFF;
+    a.done = a.scal + SC_DONE;
     a.partials = ctx->partials_mr;
     a.pstride = ctx->pstride;
     return a;
@@ -1010,11 +1016,12 @@ template <typename R, bool H = false> void cg_iteration_mr(eofa_ctx* ctx, std::v
             a.in[r] = V(sys[r].u); a.out[r] = V(sys[r].w); a.out2[r] = V(sys[r].wt); a.aux[r] = V(sys[r].p);
             a.opA[r] = sys[r].Ai; a.opB[r] = sys[r].Ad;
         }
-        a.cz = (R)-0.25; a.caux = 1; a.epi = EPI_CG_W;
+        a.cz = (R)-0.25; a.caux = 1; a.epi = EPI_CG_W; a.defer = true;
         HIPCHK(launch_hop_mr<R>(ctx->Ns, false, HM_SCHUR_W, a, ctx->st, H));
     }
     {
         auto a = mr_args<R>(ctx, 0, nr, H);
+        a.fin_partials = a.partials; a.fin_n = hop_mr_partials(ctx->g, ctx->Ns, nr); a.fin_epi = EPI_CG_W;
         for (int r = 0; r < nr; r++) { a.in[r] = V(sys[r].wt); a.out[r] = V(sys[r].at); a.opA[r] = sys[r].Ad; }
         a.cz = 1; a.caux = 0;
         HIPCHK(launch_hop_mr<R>(ctx->Ns, true, HM_SITE, a, ctx->st, H));
@@ -2005,6 +2012,9 @@ eofa_status eofa_create(eofa_ctx** out, const int dims[4], int Ns, double m0, co
         }
         ctx->g = Geom{dims[0], dims[1], dims[2], dims[3], dims[0] / 2, (int)(V / 2)};
         ctx->nh = (size_t)(V / 2) * 12 * Ns;
+        ctx->sched[0] = default_sched(ctx->g, Ns, sizeof(double), false);
+        ctx->sched[1] = default_sched(ctx->g, Ns, sizeof(float), false);
+        ctx->sched[2] = default_sched(ctx->g, Ns, sizeof(float), true);
         // one partial per block: hop kernels use <= nh / 256 blocks, grid-stride reductions <= 4096
         const size_t maxblk = (ctx->nh + 255) / 256 + 4096;
         HIPCHK(hipMalloc(&ctx->partials, sizeof(double) * maxblk));

@@ -316,7 +316,7 @@ enum : int {
     SC_RR0 = 4,     // |r_0|^2 (stop reference)
     SC_DONE = 5,    // 1 when converged (read by graph replays)
     SC_TOL2 = 6,    // stop threshold on |r|^2 / |r_0|^2
-    SC_DONEX = 7,   // the x/p update of the converged iteration has been applied (lags SC_DONE by one kernel)
+    SC_DONEX = 7,   // SC_DONE as it was before the last residual reduction: the x/p update that follows is skipped
     SC_TMP = 8,     // 8..29 free slots for norms
     SC_ITERS = 30,  // CG iterations applied since the counter was cleared (counted on the device)
     SC_N = 32
@@ -347,8 +347,10 @@ __device__ __forceinline__ void finish_partials(const double* partials, unsigned
             S[SC_WW] = s;
             S[SC_ALPHA] = S[SC_RR] / s;
             break;
-        case EPI_CG_R:          // s = |r_new|^2
+        case EPI_CG_R:          // s = |r_new|^2; the x/p update that follows belongs to this iteration
+            S[SC_DONEX] = S[SC_DONE];
             if (S[SC_DONE] != 0.0) break;
+            S[SC_ITERS] += 1.0;
             S[SC_BETA] = s / S[SC_RR];
             S[SC_RR] = s;
             if (s <= S[SC_TOL2] * S[SC_RR0]) S[SC_DONE] = 1.0;

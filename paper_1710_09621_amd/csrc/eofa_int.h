@@ -18,7 +18,8 @@ enum : int { HM_LIN = 0, HM_SITE = 1, HM_SCHUR_W = 2, HM_SCHUR_Q = 3, HM_DT = 4,
 // sites of a t-slab and walks tt consecutive slabs; the segments form an nyb x (segments / nyb) grid
 // and the workgroups that run together on an XCD take a ty x tz patch of it; ord = KB of LDS reserved
 // per workgroup (caps the workgroups per CU).  mode 5: mode 3 with the x-direction columns read from LDS,
-// for segments that hold whole x-lines.  The other kernels read modes 3 and 5 as mode 0.
+// for segments that hold whole x-lines.  Mode 6: mode 5 with two lanes per site and slice.  The batch kernels
+// run block_sched's order under modes 3, 5 and 6.
 struct Sched {
     int mode, xcd, ty, tz, tt, nyb, ord;
 };
@@ -41,6 +42,9 @@ template <typename R> struct HopArgs {
     const double* scal;       // device scalars (alpha)
     const double* done;       // early-exit flag for graph replays (may be null)
     Red red;
+    bool defer;               // leave this launch's partial sums to a later launch (its fin / fin_n)
+    Red fin;                  // fin_n > 0: finish the fin_n partial sums that an earlier launch deferred
+    unsigned fin_n;
 };
 
 // Multi-RHS form of the CG-iteration hops: nr independent systems (own fields, own mass tables,
@@ -51,6 +55,7 @@ template <typename R> struct HopArgsMR {
     Geom g;
     Sched sc;
     int par, nr;
+    int rpb;                // systems per workgroup (set by the launcher)
     const cpx<R>* Uown;
     const cpx<R>* Uoth;
     const cpx<R>* in[NRMAX];
@@ -60,35 +65,50 @@ template <typename R> struct HopArgsMR {
     const cpx<R>* aux2[NRMAX];
     const SiteOp* opA[NRMAX];
     const SiteOp* opB[NRMAX];
-    R cz, caux;
-    double* scal;       // nr blocks of SC_N scalars
-    double* partials;   // partials[r * pstride + block]
+    R cz, caux, diag;
+    const cpx<R>* self;     // diagonal term of D_T / D_w (one system)
+    double* scal;           // nr blocks of SC_N scalars
+    const double* done;     // done[r * SC_N] != 0: skip system r (may be null)
+    double* partials;       // partials[r * pstride + block]
     int pstride;
-    int epi;            // reduction epilogue (EPI_CG_W / EPI_CG_R) for the reducing modes
+    int epi;                // reduction epilogue (EPI_CG_W / EPI_CG_R) for the reducing modes
+    bool defer;             // as in HopArgs
+    const double* fin_partials;
+    unsigned fin_n;
+    int fin_epi;
 };
 // half: FP16-column Krylov fields (R = float; see load_h / store_h in kernels.hip)
 template <typename R> hipError_t launch_hop_mr(int Ns, bool dag, int mode, const HopArgsMR<R>& a, hipStream_t st,
                                                bool half = false);
+// Partial sums that a reducing launch of nr systems writes per system (for fin_n).
+unsigned hop_partials(const Geom& g, int Ns, const Sched& sc, int nr);
+unsigned hop_mr_partials(const Geom& g, int Ns, int nr);
+// direction-split form of the hop (hop_split.hip): whether a launch of nr systems takes it, its workgroups per
+// system, and the launch itself (no finishing kernel)
+bool hop_split(const Geom& g, int Ns, int nr);
+int hop_split_blocks(const Geom& g, int Ns);
+template <typename R> hipError_t launch_hop_split(int Ns, bool dag, int mode, bool red, const HopArgsMR<R>& a,
+                                                  hipStream_t st, bool half = false);
 // FP16 bytes of one half field: 12 Vh Ns (re, im) binary16 pairs + Vh Ns FP32 column norms
 inline size_t half_field_bytes_h(const Geom& g, int Ns) { return (size_t)g.Vh * Ns * (12 * 4 + 4); }
-// x_r (FP32) += alpha_r p_r ; p_r (FP16 columns) = r_r (FP32) + beta_r p_r, then SC_DONEX = SC_DONE
+// x_r (FP32) += alpha_r p_r ; p_r (FP16 columns) = r_r (FP32) + beta_r p_r unless SC_DONEX is set
 hipError_t launch_cg_xp_mr_h(int Ns, int nr, cpx<float>* const* x, void* const* p, cpx<float>* const* r, double* scal,
                              int Vh, hipStream_t st);
 hipError_t launch_f2h(int Ns, const cpx<float>* in, void* out, int Vh, hipStream_t st);
 hipError_t launch_h2d(int Ns, const void* in, cd* out, int Vh, hipStream_t st);
-// x_r += alpha_r p_r ; p_r = r_r + beta_r p_r for the systems whose SC_DONEX is clear, then SC_DONEX = SC_DONE
+// x_r += alpha_r p_r ; p_r = r_r + beta_r p_r for the systems whose SC_DONEX is clear
 template <typename R> hipError_t launch_cg_xp_mr(int nr, cpx<R>* const* x, cpx<R>* const* p, cpx<R>* const* r,
                                                  double* scal, size_t n, hipStream_t st);
 
 template <typename R> hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& a, hipStream_t st);
 int tw_grid(const Geom& g, int Ns, const Sched& sc);
+Sched block_sched(const Geom& g, int Ns);
+Sched default_sched(const Geom& g, int Ns, size_t real_bytes, bool half);
 template <typename R> hipError_t launch_site(int Ns, bool dag, const cpx<R>* in, cpx<R>* out, const SiteOp* op, int Vh,
                                              hipStream_t st);
-// x += alpha p ; p = r + beta p unless scal[SC_DONEX] is set (follow with launch_sync_done)
+// x += alpha p ; p = r + beta p unless scal[SC_DONEX] is set
 template <typename R> hipError_t launch_cg_xp(cpx<R>* x, cpx<R>* p, const cpx<R>* r, double* scal, size_t n,
                                               hipStream_t st);
-// for each of nr scalar blocks (stride SC_N): SC_ITERS += 1 if SC_DONEX is clear, then SC_DONEX = SC_DONE
-hipError_t launch_sync_done(double* scal, int nr, hipStream_t st);
 template <typename R> hipError_t launch_axpby(R a, const cpx<R>* x, R b, cpx<R>* y, size_t n, const Red* red,
                                               hipStream_t st);
 template <typename R> hipError_t launch_norm2(const cpx<R>* x, size_t n, const Red& red, hipStream_t st);

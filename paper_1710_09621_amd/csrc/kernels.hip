@@ -4,6 +4,7 @@
 #include <algorithm>
 
 #include "eofa_int.h"
+#include "hop_dev.h"
 
 namespace eofa {
 
@@ -20,118 +21,6 @@ namespace eofa {
 // Scheduling fence between the directions of the hop: keeps the compiler from hoisting every neighbour load
 // to the top (which spills at 256 VGPRs in FP64).
 #define HOP_FENCE() __builtin_amdgcn_sched_barrier(0)
-
-// Cache policy of the hop's outputs: they are not read again by the same launch, so they bypass the
-// caches that hold the re-read neighbour spinors.
-template <typename R> __device__ __forceinline__ void st_out(cpx<R>* p, const cpx<R>& v) {
-    __builtin_nontemporal_store(v.x, &p->x);
-    __builtin_nontemporal_store(v.y, &p->y);
-}
-template <typename T> __device__ __forceinline__ void st_raw(T* p, const T& v) { __builtin_nontemporal_store(v, p); }
-// The epilogues' site-local inputs (aux, aux2) are read once per launch: nontemporal loads, so that they do not
-// displace the re-read neighbour spinors either.
-template <typename R> __device__ __forceinline__ cpx<R> ld_once(const cpx<R>* p) {
-    return {__builtin_nontemporal_load(&p->x), __builtin_nontemporal_load(&p->y)};
-}
-
-// ---- FP16 storage of a Krylov half field (EOFA_MIXED_FP16): per (cb, s) column the 12 complex
-// components as binary16 (re, im) pairs in 3 blocks of 4 (16 bytes, one load per block):
-// F[cb][jb < 3][Ns][4 pairs], each column scaled by its own FP32 norm = the largest |real component| of
-// its 24 reals, stored after the 12 Vh Ns pairs.  value = norm * half, |half| <= 1.
-typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
-
-template <int NS> __device__ __forceinline__ const float* h_norms(const void* f, int Vh) {
-    return (const float*)((const h8_t*)f + (size_t)3 * Vh * NS);
-}
-
-// NT: nontemporal loads (a column read once per launch)
-template <int NS, bool NT = false>
-__device__ __forceinline__ void load_h(cpx<float> p[12], const void* __restrict__ f, size_t cb, int s, int Vh) {
-    const h8_t* d = (const h8_t*)f + cb * 3 * NS + s;
-    const float* np = h_norms<NS>(f, Vh) + cb * NS + s;
-    const float n = NT ? __builtin_nontemporal_load(np) : *np;
-#pragma unroll
-    for (int jb = 0; jb < 3; jb++) {
-        const h8_t v = NT ? __builtin_nontemporal_load(d + jb * NS) : d[jb * NS];
-#pragma unroll
-        for (int k = 0; k < 4; k++) p[4 * jb + k] = {n * (float)v[2 * k], n * (float)v[2 * k + 1]};
-    }
-}
-
-template <int NS>
-__device__ __forceinline__ void store_h(void* __restrict__ f, size_t cb, int s, int Vh, const cpx<float> v[12]) {
-    float m = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 12; j++) m = fmaxf(m, fmaxf(fabsf(v[j].x), fabsf(v[j].y)));
-    const float inv = m > 0.0f ? 1.0f / m : 0.0f;
-    h8_t* d = (h8_t*)f + cb * 3 * NS + s;
-#pragma unroll
-    for (int jb = 0; jb < 3; jb++) {
-        h8_t h;
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            h[2 * k] = (_Float16)(v[4 * jb + k].x * inv);
-            h[2 * k + 1] = (_Float16)(v[4 * jb + k].y * inv);
-        }
-        st_raw(d + jb * NS, h);
-    }
-    st_raw((float*)h_norms<NS>(f, Vh) + cb * NS + s, m);
-}
-
-// 12 components of (cb, s) from a field in storage H (FP16 columns) or plain cpx<R>; NT: nontemporal loads
-template <int NS, bool H, bool NT = false, typename R>
-__device__ __forceinline__ void load_col(cpx<R> p[12], const void* __restrict__ f, size_t cb, int s, int Vh) {
-    if constexpr (H) {
-        load_h<NS, NT>(p, f, cb, s, Vh);
-    } else {
-        const cpx<R>* src = (const cpx<R>*)f + cb * 12 * NS + s;
-#pragma unroll
-        for (int j = 0; j < 12; j++) p[j] = NT ? ld_once(src + j * NS) : src[j * NS];
-    }
-}
-
-template <int NS, bool H, typename R>
-__device__ __forceinline__ void store_col(void* __restrict__ f, size_t cb, int s, int Vh, const cpx<R> v[12]) {
-    if constexpr (H) {
-        store_h<NS>(f, cb, s, Vh, v);
-    } else {
-        cpx<R>* dst = (cpx<R>*)f + cb * 12 * NS + s;
-#pragma unroll
-        for (int j = 0; j < 12; j++) st_out(dst + j * NS, v[j]);
-    }
-}
-
-// An FP16 column of a field in storage H without its norm (p = raw binary16 values widened) and the norm n.
-template <int NS>
-__device__ __forceinline__ float load_h_raw(cpx<float> p[12], const void* __restrict__ f, size_t cb, int s, int Vh) {
-    const h8_t* d = (const h8_t*)f + cb * 3 * NS + s;
-#pragma unroll
-    for (int jb = 0; jb < 3; jb++) {
-        const h8_t v = d[jb * NS];
-#pragma unroll
-        for (int k = 0; k < 4; k++) p[4 * jb + k] = {(float)v[2 * k], (float)v[2 * k + 1]};
-    }
-    return h_norms<NS>(f, Vh)[cb * NS + s];
-}
-
-// reconstruct() of n w: the column norm of an FP16 neighbour folded into the accumulation (one FMA per real
-// instead of a multiply on every loaded component and an add)
-template <int MU, int S, typename R>
-__device__ __forceinline__ void reconstruct_n(cpx<R> acc[12], const cpx<R> w[6], R n) {
-    const R sn = S > 0 ? n : -n;
-#pragma unroll
-    for (int c = 0; c < 3; c++) {
-        cpx<R> w0 = w[c], w1 = w[3 + c], t0, t1;  // t = B^dag w
-        if constexpr (MU == 0) { t0 = ci(w1); t1 = ci(w0); }
-        else if constexpr (MU == 1) { t0 = w1; t1 = cneg(w0); }
-        else if constexpr (MU == 2) { t0 = ci(w0); t1 = cneg(ci(w1)); }
-        else { t0 = w0; t1 = w1; }
-        acc[c].x = fma(n, w0.x, acc[c].x); acc[c].y = fma(n, w0.y, acc[c].y);
-        acc[3 + c].x = fma(n, w1.x, acc[3 + c].x); acc[3 + c].y = fma(n, w1.y, acc[3 + c].y);
-        acc[6 + c].x = fma(sn, t0.x, acc[6 + c].x); acc[6 + c].y = fma(sn, t0.y, acc[6 + c].y);
-        acc[9 + c].x = fma(sn, t1.x, acc[9 + c].x); acc[9 + c].y = fma(sn, t1.y, acc[9 + c].y);
-    }
-}
 
 // One direction mu of the hop: forward (1 - S gamma) U in(x+mu) and backward (1 + S gamma) U^dag in(x-mu).
 // Uf / Ub point at the 9 complex entries of U_mu(x) and U_mu(x-mu) (global memory or LDS).  FP16 columns (H)
@@ -191,8 +80,9 @@ __device__ __forceinline__ void stage_links(cpx<R> (*sU)[8][9], const cpx<R>* __
 #pragma unroll
     for (int q = 0; q < NQ; q++) {  // every load in flight before the first LDS write; no branches
         const int e = min(s + q * NS, 71), l = e / 9, k = e % 9;
-        // selects, not nb[2 * (l - 4) + 1]: a runtime index would move nb out of registers
-        const int nbl = l == 4 ? nb[1] : l == 5 ? nb[3] : l == 6 ? nb[5] : (TW ? nb[6] : nb[7]);
+        // arithmetic on the four candidates: an index into nb[], and at Ns = 32 a chain of selects too, becomes a
+        // table in scratch memory or LDS (FP32 hop on 12 x 6 x 10 x 8 at Ns = 32: 26.5 us with the table)
+        const int nbl = (l == 4) * nb[1] + (l == 5) * nb[3] + (l == 6) * nb[5] + (l == 7) * nb[TW ? 6 : 7];
         const cpx<R>* src = (l < 4) ? Uown + ((size_t)cb * 4 + l) * 9 + k : Uoth + ((size_t)nbl * 4 + (l - 4)) * 9 + k;
         v[q] = *(const v2*)src;
     }
@@ -891,18 +781,19 @@ __global__ __launch_bounds__(256, HOP_WAVES) void k_hop_mr(const HopArgsMR<R> a)
     extern __shared__ double hop_mr_dyn[];
     SiteOpL<NS>* sOps = (SiteOpL<NS>*)hop_mr_dyn;
     constexpr int NOP = MODE == HM_SITE ? 1 : MODE == HM_SCHUR_W ? 2 : 0;
+    const int r0 = blockIdx.y * a.rpb, nr = min(a.nr - r0, a.rpb);  // this workgroup's systems
     if constexpr (NOP > 0) {
         SiteOpShare<NS> sh[NRMAX * NOP];
 #pragma unroll
         for (int r = 0; r < NRMAX; r++)
-            if (r < a.nr) {
-                siteop_fetch<NS>(sh[NOP * r], *a.opA[r]);
-                if constexpr (NOP == 2) siteop_fetch<NS>(sh[NOP * r + 1], *a.opB[r]);
+            if (r < nr) {
+                siteop_fetch<NS>(sh[NOP * r], *a.opA[r0 + r]);
+                if constexpr (NOP == 2) siteop_fetch<NS>(sh[NOP * r + 1], *a.opB[r0 + r]);
             }
         stage_links<NS>(sU, a.Uown, a.Uoth, cb, nb, s, [&] {
 #pragma unroll
             for (int r = 0; r < NRMAX; r++)
-                if (r < a.nr) {
+                if (r < nr) {
                     siteop_store<NS>(sOps[NOP * r], sh[NOP * r]);
                     if constexpr (NOP == 2) siteop_store<NS>(sOps[NOP * r + 1], sh[NOP * r + 1]);
                 }
@@ -911,7 +802,8 @@ __global__ __launch_bounds__(256, HOP_WAVES) void k_hop_mr(const HopArgsMR<R> a)
         stage_links<NS>(sU, a.Uown, a.Uoth, cb, nb, s);
     }
     const size_t base = (size_t)cb * 12 * NS + s;
-    for (int r = 0; r < a.nr; r++) {
+    for (int q = 0; q < nr; q++) {
+        const int r = r0 + q;
         const double* S = a.scal + r * SC_N;
         if (S[SC_DONE] != 0.0) continue;  // uniform over the grid
         cpx<R> z[12], v[12];
@@ -920,9 +812,9 @@ __global__ __launch_bounds__(256, HOP_WAVES) void k_hop_mr(const HopArgsMR<R> a)
         if constexpr (MODE == HM_SITE) {
 #pragma unroll
             for (int j = 0; j < 12; j++) v[j] = cscale(a.cz, z[j]);
-            site_op<NS, DAG>(v, sOps[r], s, lane);
+            site_op<NS, DAG>(v, sOps[q], s, lane);
         } else if constexpr (MODE == HM_SCHUR_W) {
-            site_op<NS, false>(z, sOps[2 * r], s, lane);
+            site_op<NS, false>(z, sOps[2 * q], s, lane);
             cpx<R> t[12];
             load_col<NS, H, true>(t, a.aux[r], (size_t)cb, s, a.g.Vh);
 #pragma unroll
@@ -949,7 +841,7 @@ __global__ __launch_bounds__(256, HOP_WAVES) void k_hop_mr(const HopArgsMR<R> a)
             for (int j = 0; j < 12; j++) nrm += (double)v[j].x * v[j].x + (double)v[j].y * v[j].y;
             if (!valid) nrm = 0.0;
             if constexpr (MODE == HM_SCHUR_W) {
-                site_op<NS, true>(v, sOps[2 * r + 1], s, lane);
+                site_op<NS, true>(v, sOps[2 * q + 1], s, lane);
                 if (valid) store_col<NS, H>(a.out2[r], (size_t)cb, s, a.g.Vh, v);
             }
             const double bs = block_sum256(nrm, lds);
@@ -962,7 +854,10 @@ __global__ __launch_bounds__(256, HOP_WAVES) void k_hop_mr(const HopArgsMR<R> a)
 __global__ __launch_bounds__(256) void k_finish_mr(const double* __restrict__ partials, int pstride, unsigned n,
                                                    double* scal, int epi) {
     double* S = scal + blockIdx.x * SC_N;
-    if (S[SC_DONE] != 0.0) return;
+    if (S[SC_DONE] != 0.0) {
+        if (epi == EPI_CG_R && threadIdx.x == 0) S[SC_DONEX] = 1.0;
+        return;
+    }
     finish_partials(partials + (size_t)blockIdx.x * pstride, n, S, 0, epi);
 }
 
@@ -1077,16 +972,6 @@ __global__ __launch_bounds__(256) void k_h2d(const void* __restrict__ in, cd* __
         cd* dst = out + cb * 12 * NS + s;
 #pragma unroll
         for (int j = 0; j < 12; j++) dst[j * NS] = {(double)v[j].x, (double)v[j].y};
-    }
-}
-
-// After the x/p update of an iteration: count it if it was applied, then let SC_DONEX catch up with SC_DONE
-// (the update of the converging iteration itself is applied; later ones are skipped).
-__global__ void k_sync_done(double* scal, int nr) {
-    if (threadIdx.x < nr) {
-        double* S = scal + threadIdx.x * SC_N;
-        if (S[SC_DONEX] == 0.0) S[SC_ITERS] += 1.0;
-        S[SC_DONEX] = S[SC_DONE];
     }
 }
 
@@ -1458,6 +1343,48 @@ int tw_grid(const Geom& g, int Ns, const Sched& sc) {
     return (int)(nseg * (g.Lt / sc.tt));
 }
 
+static int pow2_divisor(int n, int cap) {  // the largest power of two <= cap that divides n
+    int p = 1;
+    while (2 * p <= cap && n % (2 * p) == 0) p *= 2;
+    return p;
+}
+
+// Workgroup order by rule, for kernels that visit one tile of 256 lanes per workgroup.  Lines of eight workgroups stay
+// in linear order: workgroup b runs on XCD b % 8, so every XCD keeps one slab of y and finds its z and t neighbours
+// in its own L2 (three FP16-column systems on 16^3 x 32, Ns = 16: 193.6 ms a solve, 198.1 in tiles).  Other whole
+// lines take XCD-contiguous 3D tiles (FP64 hop, linear -> tiles: 24^3 x 48 1120 -> 742 us, 32^3 x 64 3355 -> 2253),
+// lattices without whole lines XCD-contiguous ranges (20^3 x 40: 578 -> 404).
+Sched block_sched(const Geom& g, int Ns) {
+    const long lanes_line = (long)g.Lxh * g.Ly * Ns;
+    const int nyb = lanes_line % 256 == 0 ? (int)(lanes_line / 256) : 0;
+    if (nyb == 0) return Sched{0, 1, 1, 1, 1, 1, 0};
+    if (nyb == 8) return Sched{0, 0, 1, 1, 1, nyb, 0};
+    const Sched tile{1, 1, pow2_divisor(nyb, 4), pow2_divisor(g.Lz, 4), pow2_divisor(g.Lt, 8), nyb, 0};
+    return tile.ty * tile.tz * tile.tt >= 16 ? tile : Sched{0, 1, 1, 1, 1, nyb, 0};
+}
+
+// The schedule of a context that was never tuned.  FP64, and FP32 fields above the 256 MB Infinity Cache, take the
+// t-walk with the x neighbours from LDS where it fits and fills the chip (one FP64 solve on 16^3 x 32: 164 ms in
+// linear order, 149 ms; FP64 hop on 32^3 x 64: 2253 us in tiles, 2165 us; FP32 there 1260 -> 1182 us, but 77 -> 92
+// us on 16^3 x 32); the rest block_sched.
+Sched default_sched(const Geom& g, int Ns, size_t real_bytes, bool half) {
+    const Sched bs = block_sched(g, Ns);
+    if (!half && bs.nyb > 1 && (real_bytes == 8 || (size_t)g.Vh * Ns * 24 * real_bytes > ((size_t)256 << 20)))
+        for (int tt = g.Lt; tt >= 16 && tt % 2 == 0; tt /= 2) {
+            const Sched tw{Ns == 16 ? 6 : 5, 1, pow2_divisor(bs.nyb, 4), pow2_divisor(g.Lz, 4), tt, bs.nyb, 0};
+            if (tw.ty * tw.tz >= 8 && tw_grid(g, Ns, tw) >= 256) return tw;
+        }
+    return bs;
+}
+
+unsigned hop_partials(const Geom& g, int Ns, const Sched& sc, int nr) {
+    if (sc.mode == 3 || sc.mode == 5 || sc.mode == 6) return (unsigned)tw_grid(g, Ns, sc);
+    return hop_mr_partials(g, Ns, nr);
+}
+unsigned hop_mr_partials(const Geom& g, int Ns, int nr) {
+    return hop_split(g, Ns, nr) ? (unsigned)hop_split_blocks(g, Ns) : (unsigned)(((size_t)g.Vh * Ns + 255) / 256);
+}
+
 // LDS that a launch of kern may reserve on top of its static LDS (gfx950: 160 KB per workgroup).
 template <typename K> static size_t lds_room(K kern) {
     hipFuncAttributes at{};
@@ -1469,6 +1396,21 @@ template <typename R>
 hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& a, hipStream_t st) {
     const size_t nthreads = (size_t)a.g.Vh * Ns;
     const bool tw = a.sc.mode == 3 || a.sc.mode == 5 || a.sc.mode == 6;
+    const bool reduces = red || mode == HM_SCHUR_W || mode == HM_SCHUR_Q;
+    if (!tw && hop_split(a.g, Ns, 1)) {
+        HopArgsMR<R> m{};
+        m.g = a.g; m.par = a.par; m.nr = 1; m.Uown = a.Uown; m.Uoth = a.Uoth;
+        m.in[0] = a.in; m.out[0] = a.out; m.out2[0] = a.out2; m.aux[0] = a.aux; m.aux2[0] = a.aux2;
+        m.opA[0] = a.opA; m.opB[0] = a.opB; m.self = a.self;
+        m.cz = a.cz; m.caux = a.caux; m.diag = a.diag;
+        m.scal = (double*)a.scal; m.done = a.done; m.partials = a.red.partials;
+        if (a.fin_n) { m.scal = a.fin.scal; m.fin_partials = a.fin.partials; m.fin_n = a.fin_n; m.fin_epi = a.fin.epi; }
+        const hipError_t e = launch_hop_split<R>(Ns, dag, mode, red, m, st);
+        if (e != hipSuccess) return e;
+        if (reduces && !a.defer) finish(a.red, (unsigned)hop_split_blocks(a.g, Ns), st);
+        return hipGetLastError();
+    }
+    if (a.fin_n) finish(a.fin, a.fin_n, st);
     const int grid = tw ? tw_grid(a.g, Ns, a.sc) : (int)((nthreads + 255) / 256);
     if (grid <= 0) return hipErrorInvalidValue;
     const size_t pad = tw ? (size_t)a.sc.ord * 1024 : 0;  // LDS reserved to cap workgroups per CU
@@ -1509,25 +1451,50 @@ hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& a,
     NS_SWITCH(Ns, if (dag) { HOP_MODES(true) } else { HOP_MODES(false) });
 #undef HOP_MODES
 #undef HOP_L
-    if (red || mode == HM_SCHUR_W || mode == HM_SCHUR_Q) finish(a.red, (unsigned)grid, st);
+    if (reduces && !a.defer) finish(a.red, (unsigned)grid, st);
     return hipGetLastError();
 }
 template hipError_t launch_hop<double>(int, bool, int, bool, const HopArgs<double>&, hipStream_t);
 template hipError_t launch_hop<float>(int, bool, int, bool, const HopArgs<float>&, hipStream_t);
 
+// Systems per workgroup of a batch launch of `grid` workgroups a system: one after the other on large lattices (the
+// links are staged once for all of them), side by side while the launch would leave the chip short of workgroups.
+// An FP16-column iteration of six systems on 8^3 x 16 at Ns = 16 (256 workgroups a system): 260 us one after the
+// other, 226 us side by side; of three systems 149 -> 128 us.  1024 = four workgroups per CU; 512 measured 243 us.
+constexpr int kFillBlocks = 1024;
+static int hop_mr_rpb(int grid, int nr) {
+    int rpb = nr;
+    while (rpb > 1 && grid * ((nr + rpb - 1) / rpb) < kFillBlocks) rpb--;
+    return rpb;
+}
+
 template <typename R>
-hipError_t launch_hop_mr(int Ns, bool dag, int mode, const HopArgsMR<R>& a, hipStream_t st, bool half) {
+hipError_t launch_hop_mr(int Ns, bool dag, int mode, const HopArgsMR<R>& args, hipStream_t st, bool half) {
+    HopArgsMR<R> a = args;
     if (a.nr < 1 || a.nr > NRMAX) return hipErrorInvalidValue;
     if (half && sizeof(R) != 4) return hipErrorInvalidValue;
-    const int grid = (int)(((size_t)a.g.Vh * Ns + 255) / 256);
-    if (grid > a.pstride) return hipErrorInvalidValue;
+    const unsigned npart = hop_mr_partials(a.g, Ns, a.nr);
+    if (npart > (unsigned)a.pstride) return hipErrorInvalidValue;
+    const bool finishes = mode != HM_SITE && !a.defer;
+    if (hop_split(a.g, Ns, a.nr)) {
+        const hipError_t e = launch_hop_split<R>(Ns, dag, mode, false, a, st, half);
+        if (e != hipSuccess) return e;
+        if (finishes)
+            hipLaunchKernelGGL(k_finish_mr, dim3(a.nr), dim3(256), 0, st, a.partials, a.pstride, npart, a.scal, a.epi);
+        return hipGetLastError();
+    }
+    if (a.fin_n)
+        hipLaunchKernelGGL(k_finish_mr, dim3(a.nr), dim3(256), 0, st, a.fin_partials, a.pstride, a.fin_n, a.scal, a.fin_epi);
+    const int grid = (int)npart;
+    a.rpb = hop_mr_rpb(grid, a.nr);
+    const int gy = (a.nr + a.rpb - 1) / a.rpb;
 #define MR_L(D, M)                                                                                       \
     do {                                                                                                 \
-        const size_t ops = (size_t)a.nr * (M == HM_SITE ? 1 : M == HM_SCHUR_W ? 2 : 0) * sizeof(SiteOpL<NS>); \
+        const size_t ops = (size_t)a.rpb * (M == HM_SITE ? 1 : M == HM_SCHUR_W ? 2 : 0) * sizeof(SiteOpL<NS>); \
         if constexpr (sizeof(R) == 4) {                                                                  \
-            if (half) { hipLaunchKernelGGL((k_hop_mr<NS, D, M, R, true>), dim3(grid), dim3(256), ops, st, a); break; } \
+            if (half) { hipLaunchKernelGGL((k_hop_mr<NS, D, M, R, true>), dim3(grid, gy), dim3(256), ops, st, a); break; } \
         }                                                                                                \
-        hipLaunchKernelGGL((k_hop_mr<NS, D, M, R, false>), dim3(grid), dim3(256), ops, st, a);          \
+        hipLaunchKernelGGL((k_hop_mr<NS, D, M, R, false>), dim3(grid, gy), dim3(256), ops, st, a);          \
     } while (0)
 #define MR_MODES(D)                                            \
     switch (mode) {                                            \
@@ -1544,9 +1511,8 @@ hipError_t launch_hop_mr(int Ns, bool dag, int mode, const HopArgsMR<R>& a, hipS
     }
 #undef MR_MODES
 #undef MR_L
-    if (mode != HM_SITE)
-        hipLaunchKernelGGL(k_finish_mr, dim3(a.nr), dim3(256), 0, st, a.partials, a.pstride, (unsigned)grid, a.scal,
-                           a.epi);
+    if (finishes)
+        hipLaunchKernelGGL(k_finish_mr, dim3(a.nr), dim3(256), 0, st, a.partials, a.pstride, npart, a.scal, a.epi);
     return hipGetLastError();
 }
 template hipError_t launch_hop_mr<double>(int, bool, int, const HopArgsMR<double>&, hipStream_t, bool);
@@ -1569,7 +1535,6 @@ hipError_t launch_cg_xp_mr_h(int Ns, int nr, cpx<float>* const* x, void* const* 
     default: return hipErrorInvalidValue;
     }
 #undef XPH
-    hipLaunchKernelGGL(k_sync_done, dim3(1), dim3(64), 0, st, scal, nr);
     return hipGetLastError();
 }
 
@@ -1595,7 +1560,6 @@ hipError_t launch_cg_xp_mr(int nr, cpx<R>* const* x, cpx<R>* const* p, cpx<R>* c
         hipLaunchKernelGGL((k_cg_xp_mr<R, true>), dim3(xp_grid<R>(n), nr), dim3(256), 0, st, a, scal, n);
     else
         hipLaunchKernelGGL((k_cg_xp_mr<R, false>), dim3(xp_grid<R>(n), nr), dim3(256), 0, st, a, scal, n);
-    hipLaunchKernelGGL(k_sync_done, dim3(1), dim3(64), 0, st, scal, nr);
     return hipGetLastError();
 }
 template hipError_t launch_cg_xp_mr<double>(int, cd* const*, cd* const*, cd* const*, double*, size_t, hipStream_t);
@@ -1622,11 +1586,6 @@ hipError_t launch_cg_xp(cpx<R>* x, cpx<R>* p, const cpx<R>* r, double* scal, siz
 }
 template hipError_t launch_cg_xp<double>(cd*, cd*, const cd*, double*, size_t, hipStream_t);
 template hipError_t launch_cg_xp<float>(cpx<float>*, cpx<float>*, const cpx<float>*, double*, size_t, hipStream_t);
-
-hipError_t launch_sync_done(double* scal, int nr, hipStream_t st) {
-    hipLaunchKernelGGL(k_sync_done, dim3(1), dim3(64), 0, st, scal, nr);
-    return hipGetLastError();
-}
 
 template <typename R>
 hipError_t launch_axpby(R a, const cpx<R>* x, R b, cpx<R>* y, size_t n, const Red* red, hipStream_t st) {
