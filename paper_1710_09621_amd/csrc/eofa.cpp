@@ -519,23 +519,24 @@ double norm2_half(eofa_ctx* ctx, const cd* v) {
 constexpr int kAutoCheckEvery = 16;
 
 // ------------------------------------------------------------------ mixed precision CG
-// FP64 normal residual r = Dhat^dag (bh - Dhat x) into W.r; returns |r|^2 (host sync).
+// FP64 normal residual r = Dhat^dag (bh - Dhat x) (x = null: of x = 0), into W.r or, with rf, in FP32 into rf;
+// returns |r|^2 (host sync).
 double normal_residual64(eofa_ctx* ctx, const Work64& W, const cd* x, const cd* bh, const SiteOp* Ai,
-                         const SiteOp* Ad) {
-    {
-        auto a = hop_args<double>(ctx, 0);
-        a.in = x; a.out = W.u; a.opA = Ai; a.cz = 1.0; a.caux = 0.0;
-        hop<double>(ctx, false, HM_SITE, false, a);
-    }
-    {
+                         const SiteOp* Ad, cpx<float>* rf = nullptr) {
+    const cd* rho = bh;  // bh - Dhat x, with A^{-dag} rho in W.wt
+    if (x) {
+        {
+            auto a = hop_args<double>(ctx, 0);
+            a.in = x; a.out = W.u; a.opA = Ai; a.cz = 1.0; a.caux = 0.0;
+            hop<double>(ctx, false, HM_SITE, false, a);
+        }
         auto a = hop_args<double>(ctx, 1);
-        a.in = W.u; a.out = W.w; a.out2 = W.wt; a.aux = x; a.opA = Ai; a.opB = Ad; a.cz = -0.25; a.caux = 1.0;
-        a.red = red_of(ctx, SC_TMP + 10, EPI_STORE);
-        hop<double>(ctx, false, HM_SCHUR_W, true, a);
+        a.in = W.u; a.out = W.w; a.out2 = W.wt; a.aux = x; a.aux2 = bh; a.opA = Ai; a.opB = Ad; a.cz = -0.25; a.caux = 1.0;
+        hop<double>(ctx, false, HM_SCHUR_RES, false, a);
+        rho = W.w;
+    } else {
+        HIPCHK(launch_site<double>(ctx->Ns, true, bh, W.wt, Ad, ctx->g.Vh, ctx->st));
     }
-    // rho = bh - Dhat x ; r = Dhat^dag rho
-    HIPCHK(launch_axpby<double>(1.0, bh, -1.0, W.w, ctx->nh, nullptr, ctx->st));
-    HIPCHK(launch_site<double>(ctx->Ns, true, W.w, W.wt, Ad, ctx->g.Vh, ctx->st));
     {
         auto a = hop_args<double>(ctx, 0);
         a.in = W.wt; a.out = W.at; a.opA = Ad; a.cz = 1.0; a.caux = 0.0;
@@ -543,7 +544,7 @@ double normal_residual64(eofa_ctx* ctx, const Work64& W, const cd* x, const cd* 
     }
     {
         auto a = hop_args<double>(ctx, 1);
-        a.in = W.at; a.out = W.r; a.aux = W.w; a.caux = 1.0; a.cz = -0.25;
+        a.in = W.at; a.out = W.r; a.outf = rf; a.aux = rho; a.caux = 1.0; a.cz = -0.25;
         a.red = red_of(ctx, SC_TMP + 11, EPI_STORE);
         hop<double>(ctx, true, HM_LIN, true, a);
     }
@@ -568,20 +569,22 @@ CgOut cg_mixed(eofa_ctx* ctx, const Work64& W, double mp, double mm, double tol_
     CgOut o;
     if (delta <= 0 || delta >= 1) delta = 0.1;
     if (check_every <= 0) check_every = 1;
-    HIPCHK(hipMemsetAsync(W.xcg, 0, nh * sizeof(cd), ctx->st));
-    double rr = normal_residual64(ctx, W, W.xcg, W.bh, Ai, Ad);
+    double rr = normal_residual64(ctx, W, nullptr, W.bh, Ai, Ad, F.r);
     o.applies = 2;
     const double rr0 = rr;
-    if (rr0 == 0.0) { o.converged = true; return o; }
-    HIPCHK(launch_convert_d2f(W.r, F.r, nh, ctx->st));
+    bool first = true;  // W.xcg holds nothing yet
+    if (rr0 == 0.0) {
+        HIPCHK(hipMemsetAsync(W.xcg, 0, nh * sizeof(cd), ctx->st));
+        o.converged = true;
+        return o;
+    }
     HIPCHK(hipMemcpyAsync(F.p, F.r, nh * sizeof(cpx<float>), hipMemcpyDeviceToDevice, ctx->st));
     HIPCHK(hipMemsetAsync(F.x, 0, nh * sizeof(cpx<float>), ctx->st));
     int stall = 0;
     while (o.iters < maxit) {
         // inner FP32 iterations until |r|^2 <= max(delta^2, target) * rr (the last replaced residual)
         const double tol2 = std::max(delta * delta, tol_n * tol_n * rr0 / rr);
-        HIPCHK(launch_scal_set(ctx->scal, SC_RR, rr, SC_RR0, rr, SC_TOL2, tol2, ctx->st));
-        HIPCHK(launch_scal_set(ctx->scal, SC_DONE, 0.0, SC_DONEX, 0.0, SC_ITERS, 0.0, ctx->st));
+        HIPCHK(launch_scal_arm(ctx->scal, rr, rr, tol2, ctx->st));
         const int base = o.iters;
         int launched = 0;
         while (base + launched < maxit) {
@@ -597,15 +600,19 @@ CgOut cg_mixed(eofa_ctx* ctx, const Work64& W, double mp, double mm, double tol_
             sync_scal(ctx);
             const int inner = (int)ctx->hscal[SC_ITERS];
             o.iters = base + inner;
-            if (!std::isfinite(ctx->hscal[SC_RR])) { ctx->err = "mixed CG breakdown"; return o; }
+            if (!std::isfinite(ctx->hscal[SC_RR])) {
+                if (first) HIPCHK(hipMemsetAsync(W.xcg, 0, nh * sizeof(cd), ctx->st));
+                ctx->err = "mixed CG breakdown";
+                return o;
+            }
             if (ctx->hscal[SC_DONE] != 0.0 || inner >= kMaxCycle) break;
         }
         o.applies += 2 * (o.iters - base);
         // reliable update: x_hi += x_lo ; r = Dhat^dag (bh - Dhat x_hi) in FP64
-        HIPCHK(launch_accum_f(W.xcg, F.x, nh, ctx->st));
-        HIPCHK(hipMemsetAsync(F.x, 0, nh * sizeof(cpx<float>), ctx->st));
+        HIPCHK(launch_accum_f(W.xcg, F.x, nh, first, ctx->st));
+        first = false;
         const double rr_prev = rr;
-        rr = normal_residual64(ctx, W, W.xcg, W.bh, Ai, Ad);
+        rr = normal_residual64(ctx, W, W.xcg, W.bh, Ai, Ad, F.r);
         o.applies += 2;
         if (updates) (*updates)++;
         if (!std::isfinite(rr)) { ctx->err = "mixed CG: non-finite residual"; return o; }
@@ -613,7 +620,6 @@ CgOut cg_mixed(eofa_ctx* ctx, const Work64& W, double mp, double mm, double tol_
         // stagnation (less than 2x in norm over 8 replacements): hand back to the FP64 defect correction
         stall = (rr > 0.25 * rr_prev) ? stall + 1 : 0;
         if (stall >= 8) return o;
-        HIPCHK(launch_convert_d2f(W.r, F.r, nh, ctx->st));
     }
     return o;
 }
@@ -846,6 +852,11 @@ double residual64(eofa_ctx* ctx, const Work64& W, double mp, double mm) {
 }
 
 double norm2_64(eofa_ctx* ctx, const Vec2& v) {
+    if (v.h[1] == v.h[0] + ctx->nh) {  // the halves of a workspace vector lie side by side
+        HIPCHK(launch_norm2<double>(v.h[0], 2 * ctx->nh, red_of(ctx, SC_TMP + 2, EPI_STORE), ctx->st));
+        sync_scal(ctx);
+        return ctx->hscal[SC_TMP + 2];
+    }
     for (int par = 0; par < 2; par++) HIPCHK(launch_norm2<double>(v.h[par], ctx->nh, red_of(ctx, SC_TMP + 2 + par, EPI_STORE), ctx->st));
     sync_scal(ctx);
     return ctx->hscal[SC_TMP + 2] + ctx->hscal[SC_TMP + 3];
@@ -854,15 +865,18 @@ double norm2_64(eofa_ctx* ctx, const Vec2& v) {
 CgOut cg_single_fp16(eofa_ctx* ctx, const Work64& W, double mp, double mm, double tol_n, int maxit, int ce,
                      const eofa_solve_params& P, int* updates);
 
-// Even-odd solve of D_T d = rhs (rhs = W.res), result added to W.x.
-CgOut eo_correct64(eofa_ctx* ctx, const Work64& W, double mp, double mm, double tol_n, int maxit, int check_every,
-                   const eofa_solve_params& P, int* updates, int* fell_back) {
+// Even-odd solve of D_T d = rhs: fresh: rhs = W.c and the result becomes W.x; else rhs = W.res, the result is added.
+CgOut eo_correct64(eofa_ctx* ctx, const Work64& W0, bool fresh, double mp, double mm, double tol_n, int maxit,
+                   int check_every, const eofa_solve_params& P, int* updates, int* fell_back) {
     const SiteOp* Ai = site_tab(ctx, SK_AINV, mp, mm);
-    // u_e = A^{-1} res_e ; bh = A^{-1} (res_o + 1/2 H_oe u_e)
-    HIPCHK(launch_site<double>(ctx->Ns, false, W.res.h[0], W.u, Ai, ctx->g.Vh, ctx->st));
+    const Vec2 rhs = fresh ? W0.c : W0.res;
+    Work64 W = W0;
+    if (fresh) W.xcg = W0.x.h[1];  // the odd half of the solution is solved in place
+    // u_e = A^{-1} rhs_e ; bh = A^{-1} (rhs_o + 1/2 H_oe u_e)
+    HIPCHK(launch_site<double>(ctx->Ns, false, rhs.h[0], W.u, Ai, ctx->g.Vh, ctx->st));
     {
         auto a = hop_args<double>(ctx, 1);
-        a.in = W.u; a.out = W.bh; a.aux = W.res.h[1]; a.caux = 1.0; a.cz = 0.5; a.opA = Ai;
+        a.in = W.u; a.out = W.bh; a.aux = rhs.h[1]; a.caux = 1.0; a.cz = 0.5; a.opA = Ai;
         hop<double>(ctx, false, HM_SITE, false, a);
     }
     CgOut o;
@@ -877,14 +891,16 @@ CgOut eo_correct64(eofa_ctx* ctx, const Work64& W, double mp, double mm, double 
     } else {
         o = cg_mixed(ctx, W, mp, mm, tol_n, maxit, check_every, P.reliable_delta, updates, P.use_graph != 0);
     }
-    // d_e = A^{-1} (res_e + 1/2 H_eo d_o) -> u ; x += d
+    // d_e = A^{-1} (rhs_e + 1/2 H_eo d_o) ; x (+)= d
     {
         auto a = hop_args<double>(ctx, 0);
-        a.in = W.xcg; a.out = W.u; a.aux = W.res.h[0]; a.caux = 1.0; a.cz = 0.5; a.opA = Ai;
+        a.in = W.xcg; a.out = fresh ? W.x.h[0] : W.u; a.aux = rhs.h[0]; a.caux = 1.0; a.cz = 0.5; a.opA = Ai;
         hop<double>(ctx, false, HM_SITE, false, a);
     }
-    HIPCHK(launch_axpby<double>(1.0, W.u, 1.0, W.x.h[0], ctx->nh, nullptr, ctx->st));
-    HIPCHK(launch_axpby<double>(1.0, W.xcg, 1.0, W.x.h[1], ctx->nh, nullptr, ctx->st));
+    if (!fresh) {
+        HIPCHK(launch_axpby<double>(1.0, W.u, 1.0, W.x.h[0], ctx->nh, nullptr, ctx->st));
+        HIPCHK(launch_axpby<double>(1.0, W.xcg, 1.0, W.x.h[1], ctx->nh, nullptr, ctx->st));
+    }
     o.applies += 1;
     return o;
 }
@@ -894,10 +910,10 @@ SolveOut solve_dt(eofa_ctx* ctx, const Work64& W, double mp, double mm, const eo
 
 int auto_check_every(const eofa_solve_params& P) { return P.check_every > 0 ? P.check_every : kAutoCheckEvery; }
 
-// Defect correction on D_T x = c with W.x holding the current solution and W.res = c - D_T x:
-// even-odd Krylov solves of the defect until ||c - D_T x|| / ||c|| <= tol.
+// Defect correction on D_T x = c with W.x holding the current solution and W.res = c - D_T x (fresh: x = 0, and W.x and
+// W.res hold nothing): even-odd Krylov solves of the defect until ||c - D_T x|| / ||c|| <= tol.
 void refine(eofa_ctx* ctx, const Work64& W, double mp, double mm, const eofa_solve_params& P, double cn2, double rel,
-            SolveOut& so) {
+            SolveOut& so, bool fresh = false) {
     const int ce = auto_check_every(P);
     so.relres = rel;
     eofa_solve_params Q = P;  // switched to plain FP64 CG if a correction fails to halve the defect
@@ -907,8 +923,8 @@ void refine(eofa_ctx* ctx, const Work64& W, double mp, double mm, const eofa_sol
         if (attempt > 0) so.restarts++;
         // inner target on the normal residual, relative to the current defect
         double tol_n = std::max(0.25 * P.tol / rel, 1e-15);
-        CgOut o = eo_correct64(ctx, W, mp, mm, std::min(tol_n, 0.5), P.max_iter - so.iters, ce, Q, &so.updates,
-                               &so.fell_back);
+        CgOut o = eo_correct64(ctx, W, fresh && attempt == 0, mp, mm, std::min(tol_n, 0.5), P.max_iter - so.iters, ce,
+                               Q, &so.updates, &so.fell_back);
         so.iters += o.iters;
         so.applies += o.applies;
         double r2 = residual64(ctx, W, mp, mm);
@@ -937,12 +953,12 @@ SolveOut solve_dt_fp64(eofa_ctx* ctx, const Work64& W, double mp, double mm, con
             return so;
         }
     }
-    for (int par = 0; par < 2; par++) {
-        HIPCHK(hipMemsetAsync(W.x.h[par], 0, ctx->nh * sizeof(cd), ctx->st));
-        HIPCHK(hipMemcpyAsync(W.res.h[par], W.c.h[par], ctx->nh * sizeof(cd), hipMemcpyDeviceToDevice, ctx->st));
+    if (cn2 == 0.0) {
+        for (int par = 0; par < 2; par++) HIPCHK(hipMemsetAsync(W.x.h[par], 0, ctx->nh * sizeof(cd), ctx->st));
+        so.ok = true;
+        return so;
     }
-    if (cn2 == 0.0) { so.ok = true; return so; }
-    refine(ctx, W, mp, mm, P, cn2, 1.0, so);
+    refine(ctx, W, mp, mm, P, cn2, 1.0, so, true);
     return so;
 }
 
@@ -960,6 +976,7 @@ struct Sys {
     void *x, *r, *p, *u, *w, *wt, *at;  // Krylov vectors in the batch precision
     double rr0 = 0;
     bool conv = false;
+    bool empty = true;  // xhi holds nothing yet
     int iters = 0, updates = 0;
 };
 
@@ -1061,24 +1078,23 @@ void cg_batch(eofa_ctx* ctx, const Work64& W, std::vector<Sys>& sys, double tol_
     auto arm = [&](int r, double rr, double rr_ref) {
         const double tol2 = mixed ? std::max(delta * delta, tol_n * tol_n * sys[r].rr0 / rr) : tol_n * tol_n;
         double* S = sys_scal(ctx, r);
-        HIPCHK(launch_scal_set(S, SC_RR, rr, SC_RR0, rr_ref, SC_TOL2, tol2, ctx->st));
-        HIPCHK(launch_scal_set(S, SC_DONE, 0.0, SC_DONEX, 0.0, SC_ITERS, 0.0, ctx->st));
+        HIPCHK(launch_scal_arm(S, rr, rr_ref, tol2, ctx->st));
         sys[r].base = sys[r].iters;  // SC_ITERS counts this cycle's iterations
         sys[r].cycle = 0;
     };
     for (int r = 0; r < nr; r++) {
         Sys& y = sys[r];
-        HIPCHK(hipMemsetAsync(y.xhi, 0, ctx->nh * sizeof(cd), ctx->st));
         HIPCHK(hipMemsetAsync(y.x, 0, nb, ctx->st));
-        double rr = normal_residual64(ctx, W, y.xhi, y.bh, y.Ai, y.Ad);   // r = Dhat^dag bh in W.r
+        double rr = normal_residual64(ctx, W, nullptr, y.bh, y.Ai, y.Ad, mixed ? (cpx<float>*)y.r : nullptr);
         y.rr0 = rr;
         if (rr == 0.0) {
             y.conv = true;
+            y.empty = false;
+            HIPCHK(hipMemsetAsync(y.xhi, 0, ctx->nh * sizeof(cd), ctx->st));
             HIPCHK(launch_scal_set(sys_scal(ctx, r), SC_DONE, 1.0, SC_DONEX, 1.0, -1, 0, ctx->st));
             continue;
         }
-        if (mixed) HIPCHK(launch_convert_d2f(W.r, (cpx<float>*)y.r, ctx->nh, ctx->st));
-        else HIPCHK(hipMemcpyAsync(y.r, W.r, nb, hipMemcpyDeviceToDevice, ctx->st));
+        if (!mixed) HIPCHK(hipMemcpyAsync(y.r, W.r, nb, hipMemcpyDeviceToDevice, ctx->st));
         if constexpr (H) HIPCHK(launch_f2h(ctx->Ns, (const cpx<float>*)y.r, y.p, ctx->g.Vh, ctx->st));
         else HIPCHK(hipMemcpyAsync(y.p, y.r, nb, hipMemcpyDeviceToDevice, ctx->st));
         arm(r, rr, rr);
@@ -1112,12 +1128,18 @@ void cg_batch(eofa_ctx* ctx, const Work64& W, std::vector<Sys>& sys, double tol_
             y.cycle = (int)hs[SC_ITERS];
             y.iters = y.base + y.cycle;
             if (hs[SC_DONE] == 0.0 && !(mixed && y.cycle >= kMaxCycle)) continue;
-            if (!std::isfinite(hs[SC_RR])) { ctx->err = "batched CG breakdown"; y.conv = true; continue; }
+            if (!std::isfinite(hs[SC_RR])) {
+                if (y.empty) HIPCHK(hipMemsetAsync(y.xhi, 0, ctx->nh * sizeof(cd), ctx->st));
+                y.empty = false;
+                ctx->err = "batched CG breakdown";
+                y.conv = true;
+                continue;
+            }
             if (!mixed) { y.conv = true; HIPCHK(hipMemcpyAsync(y.xhi, y.x, nb, hipMemcpyDeviceToDevice, ctx->st)); continue; }
             // reliable update of system r (its delta target reached, or its cycle cut at kMaxCycle)
-            HIPCHK(launch_accum_f(y.xhi, (const cpx<float>*)y.x, ctx->nh, ctx->st));
-            HIPCHK(hipMemsetAsync(y.x, 0, nb, ctx->st));
-            double rr = normal_residual64(ctx, W, y.xhi, y.bh, y.Ai, y.Ad);
+            HIPCHK(launch_accum_f(y.xhi, (cpx<float>*)y.x, ctx->nh, y.empty, ctx->st));
+            y.empty = false;
+            double rr = normal_residual64(ctx, W, y.xhi, y.bh, y.Ai, y.Ad, (cpx<float>*)y.r);
             y.updates++;
             // stagnation: the reduced-precision iteration no longer reduces the FP64 residual (the
             // defect correction above the batch then continues in FP64)
@@ -1128,7 +1150,6 @@ void cg_batch(eofa_ctx* ctx, const Work64& W, std::vector<Sys>& sys, double tol_
                 HIPCHK(launch_scal_set(sys_scal(ctx, r), SC_DONE, 1.0, SC_DONEX, 1.0, -1, 0, ctx->st));
                 continue;
             }
-            HIPCHK(launch_convert_d2f(W.r, (cpx<float>*)y.r, ctx->nh, ctx->st));
             arm(r, rr, rr);
         }
     }
@@ -1137,7 +1158,7 @@ void cg_batch(eofa_ctx* ctx, const Work64& W, std::vector<Sys>& sys, double tol_
             if (!y.conv) HIPCHK(hipMemcpyAsync(y.xhi, y.x, nb, hipMemcpyDeviceToDevice, ctx->st));
     if (mixed)
         for (Sys& y : sys)
-            if (!y.conv) HIPCHK(launch_accum_f(y.xhi, (const cpx<float>*)y.x, ctx->nh, ctx->st));
+            if (!y.conv) HIPCHK(launch_accum_f(y.xhi, (cpx<float>*)y.x, ctx->nh, y.empty, ctx->st));
 }
 
 // Dhat W.xcg = W.bh with FP16-column Krylov vectors: a one-system batch (FP64 reliable updates)
@@ -1152,8 +1173,8 @@ CgOut cg_single_fp16(eofa_ctx* ctx, const Work64& W, double mp, double mm, doubl
     y.Ai = site_tab(ctx, SK_AINV, mp, mm);
     y.Ad = site_tab(ctx, SK_AINV_DAG, mp, mm);
     y.bh = W.bh;
+    y.xhi = W.xcg;
     cg_batch<float, true>(ctx, W, sys, tol_n, maxit, ce, P.reliable_delta, P.use_graph != 0);
-    HIPCHK(hipMemcpyAsync(W.xcg, y.xhi, ctx->nh * sizeof(cd), hipMemcpyDeviceToDevice, ctx->st));
     CgOut o;
     o.iters = y.iters;
     o.applies = 2 * y.iters + 2 * y.updates + 2;
@@ -1204,12 +1225,10 @@ std::vector<double> omega_vec(const eofa_ctx* ctx) {
 // W.c = R5 gamma_5 (Om (x) P_chir phi), i.e. c_s = chir Om_{Ns+1-s} P_chir phi, on both parities.
 void make_source(eofa_ctx* ctx, const Work64& W, int chir, const void* phi) {
     const int Ns = ctx->Ns;
-    std::vector<double> Om = omega_vec(ctx), coef(Ns);
-    for (int s = 0; s < Ns; s++) coef[s] = chir * Om[Ns - 1 - s];
-    double* dcoef = ctx->scal + SC_N;
-    HIPCHK(launch_set_vec(dcoef, Ns, coef.data(), ctx->st));
-    for (int par = 0; par < 2; par++)
-        HIPCHK(launch_source((const cd*)phi, W.c.h[par], ctx->g, par, Ns, chir, dcoef, ctx->st));
+    const std::vector<double> Om = omega_vec(ctx);
+    SVec coef{};
+    for (int s = 0; s < Ns; s++) coef.v[s] = chir * Om[Ns - 1 - s];
+    HIPCHK(launch_source((const cd*)phi, W.c.h, ctx->g, Ns, chir, coef, ctx->st));
 }
 
 // bh = A^{-1} (c_o + H_oe A^{-1} c_e / 2), the Schur right-hand side of D_T x = c.
@@ -1230,14 +1249,13 @@ void reconstruct(eofa_ctx* ctx, const Work64& W, const SiteOp* Ai, const cd* xo)
 
 // out = P_chir phi + chir k Om^T P_chir x (written, or added with accumulate); returns Re phi^dag (this part).
 double combine(eofa_ctx* ctx, const Work64& W, int chir, double k, const void* phi, void* out, int accumulate) {
-    std::vector<double> Om = omega_vec(ctx);
-    double* dOm = ctx->scal + SC_N + 64;
-    HIPCHK(launch_set_vec(dOm, ctx->Ns, Om.data(), ctx->st));
-    for (int par = 0; par < 2; par++)
-        HIPCHK(launch_combine((const cd*)phi, W.x.h[par], (cd*)out, ctx->g, par, ctx->Ns, chir, chir * k, dOm, accumulate,
-                              red_of(ctx, SC_TMP + 4 + par, EPI_STORE), ctx->st));
+    const std::vector<double> Om = omega_vec(ctx);
+    SVec om{};
+    for (int s = 0; s < ctx->Ns; s++) om.v[s] = Om[s];
+    HIPCHK(launch_combine((const cd*)phi, W.x.h, (cd*)out, ctx->g, ctx->Ns, chir, chir * k, om, accumulate,
+                          red_of(ctx, SC_TMP + 4, EPI_STORE), ctx->st));
     sync_scal(ctx);
-    return ctx->hscal[SC_TMP + 4] + ctx->hscal[SC_TMP + 5];
+    return ctx->hscal[SC_TMP + 4];
 }
 
 double action_k(int chir, double m3, double m4, double mo) { return (chir < 0) ? kfac(mo, m4) : kfac(mo, m3); }
@@ -1290,6 +1308,7 @@ eofa_status batch_solve(eofa_ctx* ctx, int n, const double* mp, const double* mm
         auto t0 = std::chrono::steady_clock::now();
         std::vector<Sys> sys(nr);
         carve_batch(ctx, *P, sys);
+        double cn2[NRMAX];
         for (int r = 0; r < nr; r++) {
             const int j = g0 + r;
             Sys& y = sys[r];
@@ -1298,7 +1317,8 @@ eofa_status batch_solve(eofa_ctx* ctx, int n, const double* mp, const double* mm
             y.Ai = site_tab(ctx, SK_AINV, y.mp, y.mm);
             y.Ad = site_tab(ctx, SK_AINV_DAG, y.mp, y.mm);
             fill_c(W, j);
-            REQUIRE(std::isfinite(norm2_64(ctx, W.c)), EOFA_EINVAL, "source has non-finite entries");
+            cn2[r] = norm2_64(ctx, W.c);
+            REQUIRE(std::isfinite(cn2[r]), EOFA_EINVAL, "source has non-finite entries");
             prep_schur(ctx, W, y.Ai, y.bh);
         }
         const double tol_n = 0.25 * P->tol;
@@ -1314,14 +1334,13 @@ eofa_status batch_solve(eofa_ctx* ctx, int n, const double* mp, const double* mm
             Sys& y = sys[r];
             auto t1 = std::chrono::steady_clock::now();
             fill_c(W, j);
-            const double cn2 = norm2_64(ctx, W.c);
             reconstruct(ctx, W, y.Ai, y.xhi);
             SolveOut so;
             so.iters = y.iters;
             so.updates = y.updates;
             so.applies = 2 * y.iters + 2 * y.updates + 2;
-            const double rel = cn2 > 0 ? std::sqrt(residual64(ctx, W, y.mp, y.mm) / cn2) : 0.0;
-            refine(ctx, W, y.mp, y.mm, *P, cn2 > 0 ? cn2 : 1.0, rel, so);
+            const double rel = cn2[r] > 0 ? std::sqrt(residual64(ctx, W, y.mp, y.mm) / cn2[r]) : 0.0;
+            refine(ctx, W, y.mp, y.mm, *P, cn2[r] > 0 ? cn2[r] : 1.0, rel, so);
             done(W, j, so);
             const double te = std::chrono::duration<double>(std::chrono::steady_clock::now() - t1).count();
             fill_info(info ? &info[j] : nullptr, so, tb + te);
@@ -2656,7 +2675,7 @@ eofa_status eofa_training_pairs(eofa_ctx* ctx, double mp, double mm, unsigned lo
         // CG as in cg64, with snapshots of x into the odd sites of e5[i]
         HIPCHK(hipMemsetAsync(W.xcg, 0, nh * sizeof(cd), ctx->st));
         HIPCHK(launch_scal_set(ctx->scal, SC_TOL2, 1e-24, -1, 0, -1, 0, ctx->st));
-        double rr = normal_residual64(ctx, W, W.xcg, W.bh, Ai, Ad);
+        double rr = normal_residual64(ctx, W, nullptr, W.bh, Ai, Ad);
         HIPCHK(hipMemcpyAsync(W.p, W.r, nh * sizeof(cd), hipMemcpyDeviceToDevice, ctx->st));
         HIPCHK(launch_scal_set(ctx->scal, SC_RR, rr, SC_RR0, rr, SC_DONE, 0.0, ctx->st));
         HIPCHK(launch_scal_set(ctx->scal, SC_DONEX, 0.0, SC_ITERS, 0.0, -1, 0, ctx->st));

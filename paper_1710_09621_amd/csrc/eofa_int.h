@@ -6,7 +6,12 @@
 
 namespace eofa {
 
-enum : int { HM_LIN = 0, HM_SITE = 1, HM_SCHUR_W = 2, HM_SCHUR_Q = 3, HM_DT = 4, HM_DW = 5 };
+enum : int { HM_LIN = 0, HM_SITE = 1, HM_SCHUR_W = 2, HM_SCHUR_Q = 3, HM_DT = 4, HM_DW = 5, HM_SCHUR_RES = 6 };
+
+// Whether a mode exists for the normal (dag = false) or the gamma_5 hop gamma_5 form.
+constexpr bool hop_has(int mode, bool dag) {
+    return mode == HM_LIN || mode == HM_SITE || mode == HM_DT || dag == (mode == HM_SCHUR_Q);
+}
 
 // Order in which workgroups visit the lattice (chosen per lattice by the autotuner).
 // The cb index space of one parity is viewed as [t][z][yb] with yb = workgroup index along
@@ -36,6 +41,7 @@ template <typename R> struct HopArgs {
     const cpx<R>* aux;        // parity par
     const cpx<R>* aux2;       // parity par
     const cpx<R>* self;       // parity par (diagonal term of D_T / D_w)
+    cpx<float>* outf;         // HM_LIN: not null: out goes here in FP32 instead
     const SiteOp* opA;
     const SiteOp* opB;
     R cz, caux, diag;
@@ -67,6 +73,7 @@ template <typename R> struct HopArgsMR {
     const SiteOp* opB[NRMAX];
     R cz, caux, diag;
     const cpx<R>* self;     // diagonal term of D_T / D_w (one system)
+    cpx<float>* outf;       // as in HopArgs (one system)
     double* scal;           // nr blocks of SC_N scalars
     const double* done;     // done[r * SC_N] != 0: skip system r (may be null)
     double* partials;       // partials[r * pstride + block]
@@ -139,19 +146,25 @@ hipError_t launch_fill0(void* dst, size_t bytes, hipStream_t st);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t st);
 // sets S[s_i] = v_i for the slots s_i >= 0 (stream-ordered, no host buffer)
 hipError_t launch_scal_set(double* S, int s0, double v0, int s1, double v1, int s2, double v2, hipStream_t st);
-hipError_t launch_convert_d2f(const cd* in, cpx<float>* out, size_t n, hipStream_t st);
-hipError_t launch_convert_f2d(const cpx<float>* in, cd* out, size_t n, hipStream_t st);
-hipError_t launch_accum_f(cd* xhi, const cpx<float>* xlo, size_t n, hipStream_t st);
+// starts a cycle of CG iterations: SC_RR, SC_RR0 and SC_TOL2 set, SC_DONE, SC_DONEX and SC_ITERS cleared
+hipError_t launch_scal_arm(double* S, double rr, double rr0, double tol2, hipStream_t st);
+// xhi += xlo (first: xhi = xlo), then xlo = 0
+hipError_t launch_accum_f(cd* xhi, cpx<float>* xlo, size_t n, bool first, hipStream_t st);
 template <typename R> hipError_t launch_pack5(const cd* canon, cpx<R>* half, const Geom& g, int par, int Ns, int refl,
                                               hipStream_t st);
 template <typename R> hipError_t launch_unpack5(const cpx<R>* half, cd* canon, const Geom& g, int par, int Ns, int refl,
                                                 hipStream_t st);
 template <typename R> hipError_t launch_pack_links(const cd* U, cpx<R>* Up, const Geom& g, int par, double tbc,
                                                    hipStream_t st);
-hipError_t launch_source(const cd* phi, cd* half, const Geom& g, int par, int Ns, int chir, const double* coef,
+// an s-space vector travelling as a kernel argument
+struct SVec {
+    double v[32];
+};
+// both parities: half[par]
+hipError_t launch_source(const cd* phi, cd* const half[2], const Geom& g, int Ns, int chir, const SVec& coef,
                          hipStream_t st);
-hipError_t launch_combine(const cd* phi, const cd* xh, cd* out, const Geom& g, int par, int Ns, int chir, double ck,
-                          const double* Om, int accumulate, const Red& red, hipStream_t st);
+hipError_t launch_combine(const cd* phi, const cd* const xh[2], cd* out, const Geom& g, int Ns, int chir, double ck,
+                          const SVec& Om, int accumulate, const Red& red, hipStream_t st);
 
 // ---- site-local operator tables (sitetab.cpp)
 enum SiteKind : int { SK_AINV = 0, SK_AINV_DAG = 1, SK_M = 2, SK_M_DAG = 3, SK_A = 4, SK_A_DAG = 5, SK_OM1L = 6,

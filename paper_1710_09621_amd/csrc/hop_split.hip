@@ -181,14 +181,15 @@ __global__ __launch_bounds__(256) void k_hop_split(const HopArgsMR<R> a) {
     }
     // what the epilogue of spin w reads, requested with the columns
     const bool up = w < 2;
-    constexpr bool OPA = MODE == HM_SITE || MODE == HM_SCHUR_W || MODE == HM_DT, OPB = MODE == HM_SCHUR_W;
+    constexpr bool SCHUR = MODE == HM_SCHUR_W || MODE == HM_SCHUR_RES;
+    constexpr bool OPA = SCHUR || MODE == HM_SITE || MODE == HM_DT, OPB = SCHUR;
     ChirReg<NS, R> tA, tB;
     if constexpr (OPA) chir_fetch<NS, R>(tA, a.opA[r]->h[up ? 0 : 1], s);
     if constexpr (OPB) chir_fetch<NS, R>(tB, a.opB[r]->h[up ? 0 : 1], s);
     cpx<R> ax[3], ax2[3], sf[3];
-    const bool aux = MODE == HM_SCHUR_W || MODE == HM_SCHUR_Q || (MODE != HM_DW && a.aux[r] != nullptr);
+    const bool aux = SCHUR || MODE == HM_SCHUR_Q || (MODE != HM_DW && a.aux[r] != nullptr);
     if (aux) load_spin<NS, H, R>(ax, a.aux[r], (size_t)cb, s, w, a.g.Vh);
-    if constexpr (MODE == HM_SCHUR_Q) load_spin<NS, false, R>(ax2, a.aux2[r], (size_t)cb, s, w, a.g.Vh);
+    if constexpr (MODE == HM_SCHUR_Q || MODE == HM_SCHUR_RES) load_spin<NS, false, R>(ax2, a.aux2[r], (size_t)cb, s, w, a.g.Vh);
     if constexpr (MODE == HM_DT || MODE == HM_DW) load_spin<NS, false, R>(sf, a.self, (size_t)cb, s, w, a.g.Vh);
     R alpha = 0;
     if constexpr (MODE == HM_SCHUR_Q) alpha = (R)a.scal[r * SC_N + SC_ALPHA];
@@ -246,12 +247,13 @@ __global__ __launch_bounds__(256) void k_hop_split(const HopArgsMR<R> a) {
             if (aux) { v[c].x = fma(a.caux, ax[c].x, v[c].x); v[c].y = fma(a.caux, ax[c].y, v[c].y); }
         }
         if constexpr (MODE == HM_SITE) site_op_spin<NS, DAG>(v, tA, up, s, lane);
-    } else if constexpr (MODE == HM_SCHUR_W) {
+    } else if constexpr (SCHUR) {
         site_op_spin<NS, false>(z, tA, up, s, lane);
 #pragma unroll
         for (int c = 0; c < 3; c++) {
             v[c].x = fma(a.cz, z[c].x, a.caux * ax[c].x);
             v[c].y = fma(a.cz, z[c].y, a.caux * ax[c].y);
+            if constexpr (MODE == HM_SCHUR_RES) v[c] = csub(ax2[c], v[c]);
         }
     } else if constexpr (MODE == HM_SCHUR_Q) {
 #pragma unroll
@@ -271,12 +273,19 @@ __global__ __launch_bounds__(256) void k_hop_split(const HopArgsMR<R> a) {
             if (aux) { v[c].x = fma(a.caux, ax[c].x, v[c].x); v[c].y = fma(a.caux, ax[c].y, v[c].y); }
         }
     }
-    store_spin<NS, H && MODE != HM_SCHUR_Q>(a.out[r], (size_t)cb, s, w, a.g.Vh, v, valid, mx[0]);
+    if (MODE == HM_LIN && a.outf) {
+        cpx<float> vf[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++) vf[c] = {(float)v[c].x, (float)v[c].y};
+        store_spin<NS, false>(a.outf, (size_t)cb, s, w, a.g.Vh, vf, valid, mx[0]);
+    } else {
+        store_spin<NS, H && MODE != HM_SCHUR_Q>(a.out[r], (size_t)cb, s, w, a.g.Vh, v, valid, mx[0]);
+    }
     if constexpr (RED) {
 #pragma unroll
         for (int c = 0; c < 3; c++) nrm += (double)v[c].x * v[c].x + (double)v[c].y * v[c].y;
     }
-    if constexpr (MODE == HM_SCHUR_W) {
+    if constexpr (SCHUR) {
         site_op_spin<NS, true>(v, tB, up, s, lane);
         store_spin<NS, H>(a.out2[r], (size_t)cb, s, w, a.g.Vh, v, valid, mx[H ? 1 : 0]);
     }
@@ -306,7 +315,8 @@ hipError_t launch_hop_split(int Ns, bool dag, int mode, bool red, const HopArgsM
     if (a.nr < 1 || a.nr > NRMAX) return hipErrorInvalidValue;
     const int grid = hop_split_blocks(a.g, Ns) + (a.fin_n ? 1 : 0);
 #define SPLIT_L(D, M, RD)                                                                                           \
-    do {                                                                                                            \
+    if constexpr (!hop_has(M, D) || (M == HM_SCHUR_RES && sizeof(R) == 4)) return hipErrorInvalidValue;             \
+    else do {                                                                                                            \
         if constexpr (sizeof(R) == 4 && NS >= 8 && (M == HM_SITE || M == HM_SCHUR_W || M == HM_SCHUR_Q)) {           \
             if (half) {                                                                                             \
                 hipLaunchKernelGGL((k_hop_split<NS, D, M, M != HM_SITE, R, true>), dim3(grid, a.nr), dim3(256), 0, st, a); \
@@ -324,6 +334,7 @@ hipError_t launch_hop_split(int Ns, bool dag, int mode, bool red, const HopArgsM
     case HM_SCHUR_Q: SPLIT_L(D, HM_SCHUR_Q, true); break;                                          \
     case HM_DT: if (red) SPLIT_L(D, HM_DT, true); else SPLIT_L(D, HM_DT, false); break;            \
     case HM_DW: SPLIT_L(D, HM_DW, false); break;                                                   \
+    case HM_SCHUR_RES: SPLIT_L(D, HM_SCHUR_RES, false); break;                                     \
     default: return hipErrorInvalidValue;                                                          \
     }
     switch (Ns) {

@@ -16,6 +16,7 @@ namespace eofa {
 //   HM_SITE    out = A (caux*aux + cz*z)                       A = site op (A_T^{-1} or A_T^{-dag})
 //   HM_SCHUR_W out = w = caux*aux + cz*A(z);  out2 = B(w);  sum |w|^2 -> alpha   (Dhat p, A^{-dag} Dhat p)
 //   HM_SCHUR_Q q = caux*aux + cz*z;  out = aux2 - alpha*q;  sum |out|^2 -> beta  (CG residual update)
+//   HM_SCHUR_RES out = aux2 - (caux*aux + cz*A(z));  out2 = B(out)   (defect bh - Dhat x, A^{-dag} of it)
 //   HM_DT      out = caux*aux + cz*((4-m0) self + A(self) - z/2)                (D_T, A = M or M^T)
 //   HM_DW      out = caux*aux + cz*((4-m0) self - z/2)                          (D_w on every slice)
 // Scheduling fence between the directions of the hop: keeps the compiler from hoisting every neighbour load
@@ -184,13 +185,14 @@ __device__ __forceinline__ double hop_epilogue(const HopArgs<R>& a, cpx<R> z[12]
         for (int j = 0; j < 12; j++) v[j] = cscale(a.cz, z[j]);
         if (a.aux) add_aux(v, a.aux + base, a.caux);
         if constexpr (MODE == HM_SITE) site_op<NS, DAG>(v, opA, s, lane);
-    } else if constexpr (MODE == HM_SCHUR_W) {
+    } else if constexpr (MODE == HM_SCHUR_W || MODE == HM_SCHUR_RES) {
         site_op<NS, false>(z, opA, s, lane);
 #pragma unroll
         for (int j = 0; j < 12; j++) {
             cpx<R> t = ld_once(a.aux + base + j * NS);
             v[j].x = fma(a.cz, z[j].x, a.caux * t.x);
             v[j].y = fma(a.cz, z[j].y, a.caux * t.y);
+            if constexpr (MODE == HM_SCHUR_RES) v[j] = csub(ld_once(a.aux2 + base + j * NS), v[j]);
         }
     } else if constexpr (MODE == HM_SCHUR_Q) {
         const R alpha = (R)a.scal[SC_ALPHA];
@@ -218,10 +220,15 @@ __device__ __forceinline__ double hop_epilogue(const HopArgs<R>& a, cpx<R> z[12]
         if (a.aux) add_aux(v, a.aux + base, a.caux);
     }
     if (valid) {
+        if (MODE == HM_LIN && a.outf) {
 #pragma unroll
-        for (int j = 0; j < 12; j++) st_out(a.out + base + j * NS, v[j]);
+            for (int j = 0; j < 12; j++) st_out(a.outf + base + j * NS, cpx<float>{(float)v[j].x, (float)v[j].y});
+        } else {
+#pragma unroll
+            for (int j = 0; j < 12; j++) st_out(a.out + base + j * NS, v[j]);
+        }
     }
-    if constexpr (MODE == HM_SCHUR_W) {
+    if constexpr (MODE == HM_SCHUR_W || MODE == HM_SCHUR_RES) {
         if constexpr (RED) {
 #pragma unroll
             for (int j = 0; j < 12; j++) nrm += (double)v[j].x * v[j].x + (double)v[j].y * v[j].y;
@@ -243,13 +250,13 @@ __device__ __forceinline__ double hop_epilogue(const HopArgs<R>& a, cpx<R> z[12]
 template <int NS> struct OpsShare { SiteOpShare<NS> A, B; };
 template <int NS, int MODE, typename R>
 __device__ __forceinline__ void ops_fetch(OpsShare<NS>& sh, const HopArgs<R>& a) {
-    if constexpr (MODE == HM_SITE || MODE == HM_SCHUR_W || MODE == HM_DT) siteop_fetch<NS>(sh.A, *a.opA);
-    if constexpr (MODE == HM_SCHUR_W) siteop_fetch<NS>(sh.B, *a.opB);
+    if constexpr (MODE != HM_LIN && MODE != HM_SCHUR_Q && MODE != HM_DW) siteop_fetch<NS>(sh.A, *a.opA);
+    if constexpr (MODE == HM_SCHUR_W || MODE == HM_SCHUR_RES) siteop_fetch<NS>(sh.B, *a.opB);
 }
 template <int NS, int MODE>
 __device__ __forceinline__ void ops_store(SiteOpL<NS>& sA, SiteOpL<NS>& sB, const OpsShare<NS>& sh) {
-    if constexpr (MODE == HM_SITE || MODE == HM_SCHUR_W || MODE == HM_DT) siteop_store<NS>(sA, sh.A);
-    if constexpr (MODE == HM_SCHUR_W) siteop_store<NS>(sB, sh.B);
+    if constexpr (MODE != HM_LIN && MODE != HM_SCHUR_Q && MODE != HM_DW) siteop_store<NS>(sA, sh.A);
+    if constexpr (MODE == HM_SCHUR_W || MODE == HM_SCHUR_RES) siteop_store<NS>(sB, sh.B);
 }
 
 template <int NS, bool DAG, int MODE, bool RED, typename R>
@@ -577,13 +584,14 @@ __device__ __forceinline__ double hop_epilogue_h(const HopArgs<R>& a, cpx<R> z[6
             }
         }
         if constexpr (MODE == HM_SITE) site_op_half<NS, DAG>(v, opA, s, lane);
-    } else if constexpr (MODE == HM_SCHUR_W) {
+    } else if constexpr (MODE == HM_SCHUR_W || MODE == HM_SCHUR_RES) {
         site_op_half<NS, false>(z, opA, s, lane);
 #pragma unroll
         for (int j = 0; j < 6; j++) {
             cpx<R> t = ld_once(a.aux + base + J(j));
             v[j].x = fma(a.cz, z[j].x, a.caux * t.x);
             v[j].y = fma(a.cz, z[j].y, a.caux * t.y);
+            if constexpr (MODE == HM_SCHUR_RES) v[j] = csub(ld_once(a.aux2 + base + J(j)), v[j]);
         }
     } else if constexpr (MODE == HM_SCHUR_Q) {
         const R alpha = (R)a.scal[SC_ALPHA];
@@ -616,13 +624,18 @@ __device__ __forceinline__ double hop_epilogue_h(const HopArgs<R>& a, cpx<R> z[6
             }
         }
     }
+    if (MODE == HM_LIN && a.outf) {
 #pragma unroll
-    for (int j = 0; j < 6; j++) st_out(a.out + base + J(j), v[j]);
-    if constexpr (RED || MODE == HM_SCHUR_W) {
+        for (int j = 0; j < 6; j++) st_out(a.outf + base + J(j), cpx<float>{(float)v[j].x, (float)v[j].y});
+    } else {
+#pragma unroll
+        for (int j = 0; j < 6; j++) st_out(a.out + base + J(j), v[j]);
+    }
+    if constexpr (RED) {
 #pragma unroll
         for (int j = 0; j < 6; j++) nrm += (double)v[j].x * v[j].x + (double)v[j].y * v[j].y;
     }
-    if constexpr (MODE == HM_SCHUR_W) {
+    if constexpr (MODE == HM_SCHUR_W || MODE == HM_SCHUR_RES) {
         site_op_half<NS, true>(v, opB, s, lane);
 #pragma unroll
         for (int j = 0; j < 6; j++) st_out(a.out2 + base + J(j), v[j]);
@@ -755,7 +768,7 @@ __global__ __launch_bounds__(512, 1) void k_hop_tws(const HopArgs<R> a) {
     const double nrm = threadIdx.x < 256
         ? tws_walk<NS, DAG, MODE, RED, 0>(a, sU, sA, sB, xl, xch, carry, i, st, t0, TC, s, lane, ls, q)
         : tws_walk<NS, DAG, MODE, RED, 1>(a, sU, sA, sB, xl, xch, carry, i, st, t0, TC, s, lane, ls, q);
-    if constexpr (RED || MODE == HM_SCHUR_W) {
+    if constexpr (RED) {
         __shared__ double lds[8];
         finish_sum(a.red, block_sum512(nrm, lds));
     }
@@ -1035,21 +1048,14 @@ __global__ __launch_bounds__(256) void k_norm2(const cpx<R>* __restrict__ x, siz
     finish_sum(red, block_sum256(nrm, lds));
 }
 
-// precision conversion: out = (To) in
-template <typename Ti, typename To>
-__global__ __launch_bounds__(256) void k_convert(const cpx<Ti>* __restrict__ in, cpx<To>* __restrict__ out, size_t n) {
+// x_hi += (double) x_lo (FIRST: x_hi = x_lo), then x_lo = 0
+template <typename R, bool FIRST>
+__global__ __launch_bounds__(256) void k_accum_lo(cd* __restrict__ xhi, cpx<R>* __restrict__ xlo, size_t n) {
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-        cpx<Ti> v = in[i];
-        out[i] = {(To)v.x, (To)v.y};
-    }
-}
-
-// x_hi += (double) x_lo
-template <typename R>
-__global__ __launch_bounds__(256) void k_accum_lo(cd* __restrict__ xhi, const cpx<R>* __restrict__ xlo, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-        cpx<R> v = xlo[i];
-        cd h = xhi[i];
+        const cpx<R> v = xlo[i];
+        xlo[i] = {0, 0};
+        cd h = {0.0, 0.0};
+        if constexpr (!FIRST) h = xhi[i];
         xhi[i] = {h.x + (double)v.x, h.y + (double)v.y};
     }
 }
@@ -1179,11 +1185,16 @@ __global__ __launch_bounds__(256) void k_pack_links(const cd* __restrict__ U, cp
     }
 }
 
-// EOFA source: c_s = coef[s] * P_chir phi at every site of parity par (coef[s] = chir * Om_{Ns-1-s},
-// i.e. c = R5 gamma_5 (Om (x) P_chir phi)).  One thread per (cb, j, s).
-__global__ __launch_bounds__(256) void k_source(const cd* __restrict__ phi, cd* __restrict__ half, Geom g, int par,
-                                                int Ns, int chir, const double* __restrict__ coef) {
+// EOFA source: c_s = coef[s] * P_chir phi at every site (coef[s] = chir * Om_{Ns-1-s}, i.e.
+// c = R5 gamma_5 (Om (x) P_chir phi)).  One thread per (par, cb, j, s), both parities in one launch.
+__global__ __launch_bounds__(256) void k_source(const cd* __restrict__ phi, cd* __restrict__ h0, cd* __restrict__ h1,
+                                                Geom g, int Ns, int chir, const SVec coef) {
+    __shared__ double cs[32];
+    if (threadIdx.x < 32) cs[threadIdx.x] = coef.v[threadIdx.x];
+    __syncthreads();
     const size_t n = (size_t)g.Vh * 12 * Ns;
+    const int par = blockIdx.y;
+    cd* __restrict__ half = par ? h1 : h0;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
         int s = (int)(i % Ns);
         int j = (int)((i / Ns) % 12);
@@ -1193,17 +1204,22 @@ __global__ __launch_bounds__(256) void k_source(const cd* __restrict__ phi, cd* 
         int spin = j / 3;
         bool keep = (chir > 0) ? (spin < 2) : (spin >= 2);
         cd v = phi[(size_t)lex * 12 + j];
-        double c = keep ? coef[s] : 0.0;
+        double c = keep ? cs[s] : 0.0;
         half[i] = {c * v.x, c * v.y};
     }
 }
 
-// EOFA combine: out = P_chir phi + ck * sum_s Om_s P_chir x_s on the sites of parity par, and the
-// partial sums of Re phi^dag out.  One thread per (cb, j).
-__global__ __launch_bounds__(256) void k_combine(const cd* __restrict__ phi, const cd* __restrict__ xh, cd* __restrict__ out,
-                                                 Geom g, int par, int Ns, int chir, double ck,
-                                                 const double* __restrict__ Om, int accumulate, Red red) {
+// EOFA combine: out = P_chir phi + ck * sum_s Om_s P_chir x_s at every site, and the partial sums of
+// Re phi^dag out (one per block, even sites' blocks first).  One thread per (par, cb, j).
+__global__ __launch_bounds__(256) void k_combine(const cd* __restrict__ phi, const cd* __restrict__ x0,
+                                                 const cd* __restrict__ x1, cd* __restrict__ out, Geom g, int Ns,
+                                                 int chir, double ck, const SVec Om, int accumulate, Red red) {
+    __shared__ double cs[32];
+    if (threadIdx.x < 32) cs[threadIdx.x] = Om.v[threadIdx.x];
+    __syncthreads();
     const size_t n = (size_t)g.Vh * 12;
+    const int par = blockIdx.y;
+    const cd* __restrict__ xh = par ? x1 : x0;
     double acc = 0.0;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
         int j = (int)(i % 12);
@@ -1217,7 +1233,7 @@ __global__ __launch_bounds__(256) void k_combine(const cd* __restrict__ phi, con
         if (keep) {
             double sx = 0.0, sy = 0.0;
             const cd* src = xh + ((size_t)cb * 12 + j) * Ns;
-            for (int s = 0; s < Ns; s++) { sx = fma(Om[s], src[s].x, sx); sy = fma(Om[s], src[s].y, sy); }
+            for (int s = 0; s < Ns; s++) { sx = fma(cs[s], src[s].x, sx); sy = fma(cs[s], src[s].y, sy); }
             o = {ph.x + ck * sx, ph.y + ck * sy};
         }
         cd* dst = out + (size_t)lex * 12 + j;
@@ -1227,7 +1243,8 @@ __global__ __launch_bounds__(256) void k_combine(const cd* __restrict__ phi, con
         if (keep) acc += ph.x * o.x + ph.y * o.y;
     }
     __shared__ double lds[4];
-    finish_sum(red, block_sum256(acc, lds));
+    const double bs = block_sum256(acc, lds);
+    if (threadIdx.x == 0) red.partials[(size_t)par * gridDim.x + blockIdx.x] = bs;
 }
 
 // dst = 0 / dst = src over n doubles (kernels rather than memset / memcpy nodes, so that a caller may capture
@@ -1274,6 +1291,17 @@ __global__ void k_scal_set(double* S, int s0, double v0, int s1, double v1, int 
         if (s0 >= 0) S[s0] = v0;
         if (s1 >= 0) S[s1] = v1;
         if (s2 >= 0) S[s2] = v2;
+    }
+}
+
+__global__ void k_scal_arm(double* S, double rr, double rr0, double tol2) {
+    if (threadIdx.x == 0) {
+        S[SC_RR] = rr;
+        S[SC_RR0] = rr0;
+        S[SC_TOL2] = tol2;
+        S[SC_DONE] = 0.0;
+        S[SC_DONEX] = 0.0;
+        S[SC_ITERS] = 0.0;
     }
 }
 
@@ -1401,7 +1429,7 @@ hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& a,
         HopArgsMR<R> m{};
         m.g = a.g; m.par = a.par; m.nr = 1; m.Uown = a.Uown; m.Uoth = a.Uoth;
         m.in[0] = a.in; m.out[0] = a.out; m.out2[0] = a.out2; m.aux[0] = a.aux; m.aux2[0] = a.aux2;
-        m.opA[0] = a.opA; m.opB[0] = a.opB; m.self = a.self;
+        m.opA[0] = a.opA; m.opB[0] = a.opB; m.self = a.self; m.outf = a.outf;
         m.cz = a.cz; m.caux = a.caux; m.diag = a.diag;
         m.scal = (double*)a.scal; m.done = a.done; m.partials = a.red.partials;
         if (a.fin_n) { m.scal = a.fin.scal; m.fin_partials = a.fin.partials; m.fin_n = a.fin_n; m.fin_epi = a.fin.epi; }
@@ -1415,7 +1443,8 @@ hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& a,
     if (grid <= 0) return hipErrorInvalidValue;
     const size_t pad = tw ? (size_t)a.sc.ord * 1024 : 0;  // LDS reserved to cap workgroups per CU
 #define HOP_L(D, M, RD)                                                                                  \
-    do {                                                                                                 \
+    if constexpr (!hop_has(M, D) || (M == HM_SCHUR_RES && sizeof(R) == 4)) return hipErrorInvalidValue;  \
+    else do {                                                                                            \
         if constexpr (NS == 16) {                                                                        \
             if (tw && a.sc.mode == 6) {                                                                  \
                 hipLaunchKernelGGL((k_hop_tws<NS, D, M, RD, R>), dim3(grid), dim3(512), 0, st, a);          \
@@ -1446,6 +1475,7 @@ hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& a,
     case HM_SCHUR_Q: HOP_L(D, HM_SCHUR_Q, true); break;                                     \
     case HM_DT: if (red) HOP_L(D, HM_DT, true); else HOP_L(D, HM_DT, false); break;        \
     case HM_DW: HOP_L(D, HM_DW, false); break;                                              \
+    case HM_SCHUR_RES: HOP_L(D, HM_SCHUR_RES, false); break;                                \
     default: return hipErrorInvalidValue;                                                   \
     }
     NS_SWITCH(Ns, if (dag) { HOP_MODES(true) } else { HOP_MODES(false) });
@@ -1489,7 +1519,8 @@ hipError_t launch_hop_mr(int Ns, bool dag, int mode, const HopArgsMR<R>& args, h
     a.rpb = hop_mr_rpb(grid, a.nr);
     const int gy = (a.nr + a.rpb - 1) / a.rpb;
 #define MR_L(D, M)                                                                                       \
-    do {                                                                                                 \
+    if constexpr (!hop_has(M, D)) return hipErrorInvalidValue;                                           \
+    else do {                                                                                            \
         const size_t ops = (size_t)a.rpb * (M == HM_SITE ? 1 : M == HM_SCHUR_W ? 2 : 0) * sizeof(SiteOpL<NS>); \
         if constexpr (sizeof(R) == 4) {                                                                  \
             if (half) { hipLaunchKernelGGL((k_hop_mr<NS, D, M, R, true>), dim3(grid, gy), dim3(256), ops, st, a); break; } \
@@ -1651,16 +1682,14 @@ hipError_t launch_scal_set(double* S, int s0, double v0, int s1, double v1, int 
     return hipGetLastError();
 }
 
-hipError_t launch_convert_d2f(const cd* in, cpx<float>* out, size_t n, hipStream_t st) {
-    hipLaunchKernelGGL((k_convert<double, float>), dim3(nblk(n)), dim3(256), 0, st, in, out, n);
+hipError_t launch_scal_arm(double* S, double rr, double rr0, double tol2, hipStream_t st) {
+    hipLaunchKernelGGL(k_scal_arm, dim3(1), dim3(64), 0, st, S, rr, rr0, tol2);
     return hipGetLastError();
 }
-hipError_t launch_convert_f2d(const cpx<float>* in, cd* out, size_t n, hipStream_t st) {
-    hipLaunchKernelGGL((k_convert<float, double>), dim3(nblk(n)), dim3(256), 0, st, in, out, n);
-    return hipGetLastError();
-}
-hipError_t launch_accum_f(cd* xhi, const cpx<float>* xlo, size_t n, hipStream_t st) {
-    hipLaunchKernelGGL((k_accum_lo<float>), dim3(nblk(n)), dim3(256), 0, st, xhi, xlo, n);
+
+hipError_t launch_accum_f(cd* xhi, cpx<float>* xlo, size_t n, bool first, hipStream_t st) {
+    if (first) hipLaunchKernelGGL((k_accum_lo<float, true>), dim3(nblk(n)), dim3(256), 0, st, xhi, xlo, n);
+    else hipLaunchKernelGGL((k_accum_lo<float, false>), dim3(nblk(n)), dim3(256), 0, st, xhi, xlo, n);
     return hipGetLastError();
 }
 
@@ -1688,17 +1717,19 @@ hipError_t launch_pack_links(const cd* U, cpx<R>* Up, const Geom& g, int par, do
 template hipError_t launch_pack_links<double>(const cd*, cd*, const Geom&, int, double, hipStream_t);
 template hipError_t launch_pack_links<float>(const cd*, cpx<float>*, const Geom&, int, double, hipStream_t);
 
-hipError_t launch_source(const cd* phi, cd* half, const Geom& g, int par, int Ns, int chir, const double* coef,
+hipError_t launch_source(const cd* phi, cd* const half[2], const Geom& g, int Ns, int chir, const SVec& coef,
                          hipStream_t st) {
-    hipLaunchKernelGGL(k_source, dim3(nblk((size_t)g.Vh * 12 * Ns)), dim3(256), 0, st, phi, half, g, par, Ns, chir, coef);
+    hipLaunchKernelGGL(k_source, dim3(nblk((size_t)g.Vh * 12 * Ns), 2), dim3(256), 0, st, phi, half[0], half[1], g, Ns,
+                       chir, coef);
     return hipGetLastError();
 }
 
-hipError_t launch_combine(const cd* phi, const cd* xh, cd* out, const Geom& g, int par, int Ns, int chir, double ck,
-                          const double* Om, int accumulate, const Red& red, hipStream_t st) {
-    hipLaunchKernelGGL(k_combine, dim3(nblk((size_t)g.Vh * 12)), dim3(256), 0, st, phi, xh, out, g, par, Ns, chir, ck,
-                       Om, accumulate, red);
-    finish(red, (unsigned)nblk((size_t)g.Vh * 12), st);
+hipError_t launch_combine(const cd* phi, const cd* const xh[2], cd* out, const Geom& g, int Ns, int chir, double ck,
+                          const SVec& Om, int accumulate, const Red& red, hipStream_t st) {
+    const int grid = std::min(nblk((size_t)g.Vh * 12), 2048);  // both parities' partial sums fit the reduction buffer
+    hipLaunchKernelGGL(k_combine, dim3(grid, 2), dim3(256), 0, st, phi, xh[0], xh[1], out, g, Ns, chir, ck, Om,
+                       accumulate, red);
+    finish(red, 2u * grid, st);
     return hipGetLastError();
 }
 
