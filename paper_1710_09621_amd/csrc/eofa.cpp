@@ -428,6 +428,36 @@ void cg_iteration(eofa_ctx* ctx, cpx<R>* x, cpx<R>* r, cpx<R>* p, cpx<R>* u, cpx
     timed(ctx, k0 + EOFA_K_XP, [&] { HIPCHK(launch_cg_xp<R>(x, p, r, ctx->scal, ctx->nh, ctx->st)); });
 }
 
+// Most iterations between host checks when the caller leaves it to the library (check_every = 0); it also is the
+// longest block of a captured graph.
+constexpr int kAutoCheckEvery = 16;
+
+// Length of the blocks of iterations between host checks.  A given check_every is taken as it is.  Otherwise a block
+// ends where the residual is expected to reach its target by the rate measured so far (in CG iterations per factor e
+// of |r|^2): iterations past the target exit at once on the device, but each still costs its six launches, and a
+// reliable-update cycle (a factor 10 in |r|) is shorter than 16 iterations on small lattices, where 44% of the
+// iterations launched in blocks of 16 were such idle ones (trajectory on 8^4, FP16 columns: 317 -> 262 ms).
+// Captured blocks come in multiples of 4, so that at most four graphs are kept per set of buffers.
+struct BlockRule {
+    int ce;        // > 0: fixed block length
+    bool graph;
+    int first;     // block length while no rate is known
+    double rate = 0;  // iterations per unit of log |r|^2
+
+    int length(double rr, double target) const {
+        if (ce > 0) return ce;
+        int n = first;
+        if (rate > 0 && rr > target) n = (int)std::min(std::ceil(rate * std::log(rr / target)), (double)kAutoCheckEvery);
+        else if (rate > 0) n = 1;
+        n = std::max(n, 2);
+        return graph ? (n + 3) / 4 * 4 : n;
+    }
+    // iters iterations took |r|^2 from rr0 to rr
+    void learn(int iters, double rr0, double rr) {
+        if (iters > 0 && rr > 0 && rr < rr0) rate = iters / std::log(rr0 / rr);
+    }
+};
+
 // ------------------------------------------------------------------ FP64 CG on Dhat^dag Dhat
 struct CgOut {
     int iters = 0;
@@ -469,13 +499,15 @@ CgOut cg64(eofa_ctx* ctx, const Work64& W, double mp, double mm, double tol_n, i
     o.applies = 1;
     sync_scal(ctx);
     if (ctx->hscal[SC_DONE] != 0.0) { o.converged = true; return o; }
-    if (check_every <= 0) check_every = 1;
+    BlockRule rule{check_every, graph, kAutoCheckEvery};
+    const double rr0 = ctx->hscal[SC_RR];
+    double rr = rr0;
     int launched = 0;
     while (launched < maxit) {
         // u = A^{-1} H_eo p ; w = Dhat p, wt = A^{-dag} w, |w|^2 -> alpha ; at = A^{-dag} g5 H_eo g5 wt ;
         // r -= alpha (w - g5 H_oe g5 at / 4), |r|^2 -> beta ; x += alpha p, p = r + beta p
-        const int blk = std::min(check_every, maxit - launched);
-        if (graph && blk == check_every) {
+        const int len = rule.length(rr, tol_n * tol_n * rr0), blk = std::min(len, maxit - launched);
+        if (graph && blk == len) {
             graph_run(ctx, graph_key<double>(ctx, 1, blk, {W.xcg, W.r, W.p, W.u, W.w, W.wt, W.at, Ai, Ad}), [&] {
                 for (int k = 0; k < blk; k++) cg_iteration<double>(ctx, W.xcg, W.r, W.p, W.u, W.w, W.wt, W.at, Ai, Ad);
             });
@@ -491,6 +523,8 @@ CgOut cg64(eofa_ctx* ctx, const Work64& W, double mp, double mm, double tol_n, i
             return o;
         }
         if (ctx->hscal[SC_DONE] != 0.0) { o.converged = true; break; }
+        rr = ctx->hscal[SC_RR];
+        rule.learn(o.iters, rr0, rr);  // the rate over the whole solve: CG residuals are not monotonous
     }
     return o;
 }
@@ -513,10 +547,6 @@ double norm2_half(eofa_ctx* ctx, const cd* v) {
     return ctx->hscal[SC_TMP + 9];
 }
 
-// Iterations between host checks when the caller leaves it to the library.  Iterations past convergence
-// inside a block exit at once on the device, so a block costs at most a few launches of waste; 16 keeps the
-// host out of the loop and gives a captured graph 16 iterations at every volume.
-constexpr int kAutoCheckEvery = 16;
 
 // ------------------------------------------------------------------ mixed precision CG
 // FP64 normal residual r = Dhat^dag (bh - Dhat x) (x = null: of x = 0), into W.r or, with rf, in FP32 into rf;
@@ -556,6 +586,8 @@ double normal_residual64(eofa_ctx* ctx, const Work64& W, const cd* x, const cd* 
 // residual is recomputed anyway, so a reduced-precision recurrence that has stopped tracking the true
 // residual is caught by the stagnation test instead of iterating to max_iter.
 constexpr int kMaxCycle = 500;
+// First block of a mixed-precision solve, whose rate is not known yet.
+constexpr int kFirstCycle = 8;
 
 // Reliable-update CG: FP32 storage and arithmetic for the Krylov iteration, FP64 solution
 // accumulation and FP64 residual replacement whenever |r| has dropped by delta since the
@@ -568,7 +600,7 @@ CgOut cg_mixed(eofa_ctx* ctx, const Work64& W, double mp, double mm, double tol_
     const size_t nh = ctx->nh;
     CgOut o;
     if (delta <= 0 || delta >= 1) delta = 0.1;
-    if (check_every <= 0) check_every = 1;
+    BlockRule rule{check_every, graph, kFirstCycle};
     double rr = normal_residual64(ctx, W, nullptr, W.bh, Ai, Ad, F.r);
     o.applies = 2;
     const double rr0 = rr;
@@ -588,8 +620,9 @@ CgOut cg_mixed(eofa_ctx* ctx, const Work64& W, double mp, double mm, double tol_
         const int base = o.iters;
         int launched = 0;
         while (base + launched < maxit) {
-            const int blk = std::min(check_every, maxit - base - launched);
-            if (graph && blk == check_every) {
+            const int len = rule.length(launched ? ctx->hscal[SC_RR] : rr, tol2 * rr);
+            const int blk = std::min(len, maxit - base - launched);
+            if (graph && blk == len) {
                 graph_run(ctx, graph_key<float>(ctx, 2, blk, {F.x, F.r, F.p, F.u, F.w, F.wt, F.at, Ai, Ad}), [&] {
                     for (int k = 0; k < blk; k++) cg_iteration<float>(ctx, F.x, F.r, F.p, F.u, F.w, F.wt, F.at, Ai, Ad);
                 });
@@ -605,6 +638,7 @@ CgOut cg_mixed(eofa_ctx* ctx, const Work64& W, double mp, double mm, double tol_
                 ctx->err = "mixed CG breakdown";
                 return o;
             }
+            rule.learn(inner, rr, ctx->hscal[SC_RR]);
             if (ctx->hscal[SC_DONE] != 0.0 || inner >= kMaxCycle) break;
         }
         o.applies += 2 * (o.iters - base);
@@ -908,13 +942,11 @@ CgOut eo_correct64(eofa_ctx* ctx, const Work64& W0, bool fresh, double mp, doubl
 SolveOut solve_dt(eofa_ctx* ctx, const Work64& W, double mp, double mm, const eofa_solve_params& P,
                   bool guess = false);
 
-int auto_check_every(const eofa_solve_params& P) { return P.check_every > 0 ? P.check_every : kAutoCheckEvery; }
-
 // Defect correction on D_T x = c with W.x holding the current solution and W.res = c - D_T x (fresh: x = 0, and W.x and
 // W.res hold nothing): even-odd Krylov solves of the defect until ||c - D_T x|| / ||c|| <= tol.
 void refine(eofa_ctx* ctx, const Work64& W, double mp, double mm, const eofa_solve_params& P, double cn2, double rel,
             SolveOut& so, bool fresh = false) {
-    const int ce = auto_check_every(P);
+    const int ce = P.check_every;
     so.relres = rel;
     eofa_solve_params Q = P;  // switched to plain FP64 CG if a correction fails to halve the defect
     for (int attempt = 0; attempt < 20; attempt++) {
@@ -978,6 +1010,8 @@ struct Sys {
     bool conv = false;
     bool empty = true;  // xhi holds nothing yet
     int iters = 0, updates = 0;
+    double rr = 0, rr_cycle = 0, target = 0;  // |r|^2 at the last host check and at the cycle's start, and its target
+    BlockRule rule{0, false, 0};
 };
 
 void carve_batch(eofa_ctx* ctx, const eofa_solve_params& P, std::vector<Sys>& sys) {
@@ -1073,12 +1107,14 @@ void cg_batch(eofa_ctx* ctx, const Work64& W, std::vector<Sys>& sys, double tol_
     const int nr = (int)sys.size();
     const bool mixed = sizeof(R) == 4;
     if (delta <= 0 || delta >= 1) delta = 0.1;
-    if (ce <= 0) ce = 1;
+    for (Sys& y : sys) y.rule = BlockRule{ce, graph, mixed ? kFirstCycle : kAutoCheckEvery};
     const size_t nb = ctx->nh * sizeof(cpx<R>);
     auto arm = [&](int r, double rr, double rr_ref) {
         const double tol2 = mixed ? std::max(delta * delta, tol_n * tol_n * sys[r].rr0 / rr) : tol_n * tol_n;
         double* S = sys_scal(ctx, r);
         HIPCHK(launch_scal_arm(S, rr, rr_ref, tol2, ctx->st));
+        sys[r].rr = sys[r].rr_cycle = rr;
+        sys[r].target = tol2 * rr_ref;
         sys[r].base = sys[r].iters;  // SC_ITERS counts this cycle's iterations
         sys[r].cycle = 0;
     };
@@ -1099,22 +1135,23 @@ void cg_batch(eofa_ctx* ctx, const Work64& W, std::vector<Sys>& sys, double tol_
         else HIPCHK(hipMemcpyAsync(y.p, y.r, nb, hipMemcpyDeviceToDevice, ctx->st));
         arm(r, rr, rr);
     }
-    // blocks of ce iterations between host checks; each system counts its applied iterations on the device
+    // blocks of iterations between host checks; each system counts its applied iterations on the device
     int it = 0;
     while (it < maxit) {
-        bool all = true;
-        for (const Sys& y : sys) all &= y.conv;
-        if (all) break;
-        const int blk = std::min(ce, maxit - it);
-        if (graph && blk == ce) {
-            std::vector<uintptr_t> key = graph_key<R>(ctx, H ? 4 : 3, ce, {}, H);
+        int len = 0;  // the block ends where the first system is expected to reach its target
+        for (const Sys& y : sys)
+            if (!y.conv) len = len ? std::min(len, y.rule.length(y.rr, y.target)) : y.rule.length(y.rr, y.target);
+        if (len == 0) break;
+        const int blk = std::min(len, maxit - it);
+        if (graph && blk == len) {
+            std::vector<uintptr_t> key = graph_key<R>(ctx, H ? 4 : 3, blk, {}, H);
             for (const Sys& y : sys)
                 for (const void* q : {(const void*)y.Ai, (const void*)y.Ad, (const void*)y.x, (const void*)y.r,
                                       (const void*)y.p, (const void*)y.u, (const void*)y.w, (const void*)y.wt,
                                       (const void*)y.at})
                     key.push_back((uintptr_t)q);
             graph_run(ctx, std::move(key), [&] {
-                for (int k = 0; k < ce; k++) cg_iteration_mr<R, H>(ctx, sys);
+                for (int k = 0; k < blk; k++) cg_iteration_mr<R, H>(ctx, sys);
             });
         } else {
             for (int k = 0; k < blk; k++) cg_iteration_mr<R, H>(ctx, sys);
@@ -1127,6 +1164,8 @@ void cg_batch(eofa_ctx* ctx, const Work64& W, std::vector<Sys>& sys, double tol_
             if (y.conv) continue;
             y.cycle = (int)hs[SC_ITERS];
             y.iters = y.base + y.cycle;
+            y.rr = hs[SC_RR];
+            y.rule.learn(y.cycle, y.rr_cycle, y.rr);
             if (hs[SC_DONE] == 0.0 && !(mixed && y.cycle >= kMaxCycle)) continue;
             if (!std::isfinite(hs[SC_RR])) {
                 if (y.empty) HIPCHK(hipMemsetAsync(y.xhi, 0, ctx->nh * sizeof(cd), ctx->st));
@@ -1322,7 +1361,7 @@ eofa_status batch_solve(eofa_ctx* ctx, int n, const double* mp, const double* mm
             prep_schur(ctx, W, y.Ai, y.bh);
         }
         const double tol_n = 0.25 * P->tol;
-        const int ce = auto_check_every(*P);
+        const int ce = P->check_every;
         if (P->prec == EOFA_FP64) cg_batch<double>(ctx, W, sys, tol_n, P->max_iter, ce, P->reliable_delta, P->use_graph != 0);
         else if (P->prec == EOFA_MIXED_FP16)
             cg_batch<float, true>(ctx, W, sys, tol_n, P->max_iter, ce, P->reliable_delta, P->use_graph != 0);
