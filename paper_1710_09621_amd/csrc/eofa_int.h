@@ -154,8 +154,9 @@ template <typename R> hipError_t launch_pack5(const cd* canon, cpx<R>* half, con
                                               hipStream_t st);
 template <typename R> hipError_t launch_unpack5(const cpx<R>* half, cd* canon, const Geom& g, int par, int Ns, int refl,
                                                 hipStream_t st);
-template <typename R> hipError_t launch_pack_links(const cd* U, cpx<R>* Up, const Geom& g, int par, double tbc,
-                                                   hipStream_t st);
+// D[par], F[par]: the FP64 and FP32 links of parity par
+hipError_t launch_pack_links(const cd* U, cd* const D[2], cpx<float>* const F[2], const Geom& g, double tbc,
+                             hipStream_t st);
 // an s-space vector travelling as a kernel argument
 struct SVec {
     double v[32];

@@ -8,8 +8,7 @@
 // U_mu(x) enters S_g as -(beta / 3) Re Tr(U_mu(x) A_mu(x)) with A the sum of its six staples, so
 //   dS_g/dw^a = (beta / 3) Im Tr(T^a U A) = (beta / 6) Im Tr(lambda^a U A).
 // These kernels work on the canonical (periodic) link array; the fermion boundary phase is applied when the
-// links are packed for the hop.  They are memory- and ALU-light next to the fermion forces (one CG solve per
-// force), so they use one thread per link and plain 3x3 products.
+// links are packed for the hop.
 #include "hmc.h"
 
 namespace eofa {
@@ -105,8 +104,10 @@ __device__ __forceinline__ void i_algebra(const double p[8], double h, cd X[9]) 
     for (int k = 0; k < 9; k++) X[k] = {-h * Q[k].y, h * Q[k].x};  // i h Q
 }
 
-// exp(X) by scaling and squaring: Y = X / 2^s with |Y|_F <= 1/2, the Taylor polynomial of degree 18 in
-// Horner form (remainder at most |Y|^19 / 19! < 2e-23), then s squarings.
+// exp(X) of a traceless anti-Hermitian X by scaling and squaring: Y = X / 2^s with |Y|_F <= 1/2, the Taylor polynomial
+// of degree 18 (remainder at most |Y|^19 / 19! < 2e-23), then s squarings.  By Cayley-Hamilton Y^3 = a Y + i b with
+// a = tr(Y^2) / 2 and i b = det Y = tr(Y^3) / 3 (a, b real), so the Horner steps E <- 1 + Y E / n act on the three
+// coefficients of E = e0 + e1 Y + e2 Y^2 and one matrix product is left of the polynomial.
 __device__ __forceinline__ void su3_exp(const cd X[9], cd E[9]) {
     double n2 = 0;
 #pragma unroll
@@ -118,19 +119,35 @@ __device__ __forceinline__ void su3_exp(const cd X[9], cd E[9]) {
         sc *= 0.5;
         s++;
     }
-    cd Y[9];
+    cd Y[9], T[9];
 #pragma unroll
     for (int k = 0; k < 9; k++) Y[k] = {sc * X[k].x, sc * X[k].y};
-    // E = I + Y/1 (I + Y/2 (I + ... (I + Y/18)))
-    cd T[9];
+    mul_nn(Y, Y, T);
+    const double a = 0.5 * (T[0].x + T[4].x + T[8].x);
+    double b = 0;  // Im tr(Y Y^2) / 3
 #pragma unroll
-    for (int k = 0; k < 9; k++) E[k] = {(k % 4 == 0) ? 1.0 : 0.0, 0.0};
-#pragma unroll 1
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            const cd p = Y[3 * i + k], q = T[3 * k + i];
+            b = fma(p.x, q.y, fma(p.y, q.x, b));
+        }
+    b *= 1.0 / 3.0;
+    cd e0 = {1.0, 0.0}, e1 = {0.0, 0.0}, e2 = {0.0, 0.0};
+#pragma unroll
     for (int n = 18; n >= 1; n--) {
         const double inv = 1.0 / n;
-        mul_nn(Y, E, T);
+        const cd t0 = {1.0 - inv * (b * e2.y), inv * (b * e2.x)};
+        const cd t1 = {inv * fma(a, e2.x, e0.x), inv * fma(a, e2.y, e0.y)};
+        e2 = {inv * e1.x, inv * e1.y};
+        e1 = t1;
+        e0 = t0;
+    }
 #pragma unroll
-        for (int k = 0; k < 9; k++) E[k] = {((k % 4 == 0) ? 1.0 : 0.0) + inv * T[k].x, inv * T[k].y};
+    for (int k = 0; k < 9; k++) {
+        cd v = k % 4 == 0 ? e0 : cd{0.0, 0.0};
+        v = cmadd(v, e1, Y[k]);
+        E[k] = cmadd(v, e2, T[k]);
     }
 #pragma unroll 1
     for (int i = 0; i < s; i++) {
@@ -170,38 +187,121 @@ __global__ __launch_bounds__(256) void k_plaquette(const cd* __restrict__ U, Geo
     finish_sum(red, block_sum256(v, lds));
 }
 
-// Four lanes per link (a quad of consecutive lanes): lane nu forms the two staples of the plane (mu, nu) (none when
-// nu == mu), the quad sums them, and every lane forms M = U A and writes two of the eight components.
+typedef double v2d __attribute__((ext_vector_type(2)));
+
+// The 64 link matrices of a wave, lane l's at link index idx (lex * 4 + mu), read as 576 units of 16 bytes: unit
+// u = lane + 64 k is part u % 9 of the matrix of lane u / 9, so nine consecutive lanes read one matrix and a load
+// instruction touches about 13 cache lines instead of 64.
+__device__ __forceinline__ void fetch_links(const cd* __restrict__ U, int idx, int lane, v2d r[9]) {
+#pragma unroll
+    for (int k = 0; k < 9; k++) {
+        const int u = lane + 64 * k, o = (u * 7282) >> 16;  // u / 9 for u < 576
+        const int j = __shfl(idx, o, 64);
+        r[k] = *(const v2d*)(U + (size_t)j * 9 + (u - 9 * o));
+    }
+}
+// orders a wave's LDS writes and reads across its lanes
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+// hands the units of fetch_links over to their lanes through the wave's own LDS buffer (576 units)
+__device__ __forceinline__ void spread_links(v2d* buf, const v2d r[9], int lane, cd m[9]) {
+#pragma unroll
+    for (int k = 0; k < 9; k++) buf[lane + 64 * k] = r[k];
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 9; k++) {
+        const v2d v = buf[9 * lane + k];
+        m[k] = {v.x, v.y};
+    }
+}
+
+// A workgroup owns 16 consecutive sites, wave mu their links U_mu, with four lanes per link (a quad): lane nu forms the
+// two staples of the plane (mu, nu) (none when nu == mu), the quad sums them, and every lane forms M = U A and writes
+// two of the eight components.  The links of a lane's staples are scattered matrices of 144 bytes; read by the lanes
+// themselves (63 loads of one cache line per lane) they bound the kernel: 24^3 x 48 took 1121 us, 0.49 TB/s of its
+// 0.55 GB.  Read as consecutive units and handed over in LDS, one link at a time and each wave for itself, it took
+// 753 us; the waves share most of them, though: U_nu(x + mu) and U_mu(x + nu) are both in the links of the forward
+// neighbours, U_mu(x - nu) and U_nu(x - nu) in those of the backward neighbours, U_nu(x) and U_mu(x) in those of x.
+// Wave w reads the four links of x + w, later of x - w, for all four waves, and only U_nu(x + mu - nu) for itself
+// (29 loads): 626 us (16^3 x 32: 194 -> 131 us).
 __global__ __launch_bounds__(256) void k_gauge_force(const cd* __restrict__ U, Geom g, double beta,
                                                      double* __restrict__ F, double* __restrict__ P, double h,
                                                      int kick) {
-    const int V = 2 * g.Vh;
-    const int tid = blockIdx.x * 256 + threadIdx.x;
-    const int link = tid >> 2, nu = tid & 3;
-    const bool valid = link < 4 * V;  // whole quads are in or out: 4 V links, 256-lane blocks
-    const int mu = valid ? link / V : 0, lex = valid ? link - mu * V : 0;
-    cd A[9];
-#pragma unroll
-    for (int k = 0; k < 9; k++) A[k] = {0, 0};
-    if (valid && nu != mu) {
-        cd a[9], b[9], c[9], t[9];
-        const int xm = lex_step(g, lex, mu, +1);
-        // upper staple U_nu(x + mu) U_mu(x + nu)^dag U_nu(x)^dag
-        load_su3(U, xm, nu, a);
-        load_su3(U, lex_step(g, lex, nu, +1), mu, b);
-        load_su3(U, lex, nu, c);
-        mul_nd(a, b, t);
-        mul_nd(t, c, A);
-        // lower staple U_nu(x + mu - nu)^dag U_mu(x - nu)^dag U_nu(x - nu) = (U_mu(x - nu) U_nu(x + mu - nu))^dag U_nu(x - nu)
-        const int xd = lex_step(g, lex, nu, -1);
-        load_su3(U, lex_step(g, xm, nu, -1), nu, a);
-        load_su3(U, xd, mu, b);
-        load_su3(U, xd, nu, c);
-        mul_nn(b, a, t);
-        mul_dn(t, c, a);
-#pragma unroll
-        for (int k = 0; k < 9; k++) A[k] = cadd(A[k], a[k]);
+    constexpr int SB = 577;  // units of 16 sites' links, one more so that the quads' four buffers start in other banks
+    __shared__ v2d nbr[4 * SB], own[576];
+    const int V = 2 * g.Vh;  // a multiple of 16: every extent is even
+    const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, nu = lane & 3;
+    const int site = lane >> 2;
+    v2d* buf = nbr + mu * SB;
+    int b = blockIdx.x;
+    {   // hardware dispatches workgroup b to XCD b % 8: every XCD takes one contiguous range of the lattice
+        const int n = gridDim.x, x = b & 7, i = b >> 3, q = n >> 3, m = n & 7;
+        b = x * q + (x < m ? x : m) + i;
     }
+    const int lex = b * 16 + (lane >> 2);
+    // steps of +1 in mu and +-1 in nu (for nu != mu the coordinate nu of x + mu is that of x); arithmetic on the four
+    // directions: a runtime index would move the coordinates to scratch memory
+    int r = lex / g.Lx;
+    const int x = lex - r * g.Lx;
+    const int y = r % g.Ly;
+    r /= g.Ly;
+    const int z = r % g.Lz, tt = r / g.Lz;
+    const int st2 = g.Lx * g.Ly, st3 = st2 * g.Lz;
+    auto pick = [](int d, int a0, int a1, int a2, int a3) { return (d == 0) * a0 + (d == 1) * a1 + (d == 2) * a2 + (d == 3) * a3; };
+    auto up = [&](int d) {
+        const int st = pick(d, 1, g.Lx, st2, st3), L = pick(d, g.Lx, g.Ly, g.Lz, g.Lt);
+        return pick(d, x, y, z, tt) + 1 == L ? st - L * st : st;
+    };
+    auto down = [&](int d) {
+        const int st = pick(d, 1, g.Lx, st2, st3), L = pick(d, g.Lx, g.Ly, g.Lz, g.Lt);
+        return pick(d, x, y, z, tt) == 0 ? L * st - st : -st;
+    };
+    const bool plane = nu != mu;
+    const int xp = lex + up(mu), xm = lex + down(mu);
+    const int xpm = plane ? xp + down(nu) : xp;  // lanes with nu == mu drop their products
+    auto read = [](const v2d* q, cd m[9]) {
+#pragma unroll
+        for (int k = 0; k < 9; k++) m[k] = {q[k].x, q[k].y};
+    };
+    auto put = [&](const v2d r[9]) {
+#pragma unroll
+        for (int k = 0; k < 9; k++) buf[lane + 64 * k] = r[k];
+    };
+    cd A[9], a[9], cc[9], t[9];
+    v2d r0[9], r1[3];
+    fetch_links(U, xp * 4 + nu, lane, r0);  // the quad's lanes cover the four links of their site
+    const v2d* Ux = (const v2d*)(U + (size_t)b * 16 * 36);
+#pragma unroll
+    for (int k = 0; k < 3; k++) r1[k] = Ux[min((int)threadIdx.x + 256 * k, 575)];
+    put(r0);
+#pragma unroll
+    for (int k = 0; k < 3; k++)
+        if (threadIdx.x + 256 * k < 576) own[threadIdx.x + 256 * k] = r1[k];
+    fetch_links(U, xpm * 4 + nu, lane, r0);
+    __syncthreads();
+    // upper staple U_nu(x + mu) U_mu(x + nu)^dag U_nu(x)^dag
+    read(buf + 9 * lane, a);
+    read(nbr + nu * SB + 36 * site + 9 * mu, cc);
+    mul_nd(a, cc, t);
+    read(own + 9 * lane, cc);
+    mul_nd(t, cc, A);
+    __syncthreads();
+    // lower staple U_nu(x + mu - nu)^dag U_mu(x - nu)^dag U_nu(x - nu) = (U_mu(x - nu) U_nu(x + mu - nu))^dag U_nu(x - nu)
+    put(r0);
+    fetch_links(U, xm * 4 + nu, lane, r0);
+    wave_sync();
+    read(buf + 9 * lane, a);
+    wave_sync();
+    put(r0);
+    __syncthreads();
+    read(nbr + nu * SB + 36 * site + 9 * mu, cc);
+    mul_nn(cc, a, t);
+    read(nbr + nu * SB + 36 * site + 9 * nu, cc);
+    mul_dn(t, cc, a);
+#pragma unroll
+    for (int k = 0; k < 9; k++) A[k] = plane ? cadd(A[k], a[k]) : cd{0.0, 0.0};
     // quad sum ((A_0 + A_1) + (A_2 + A_3)), the same order in every lane
 #pragma unroll
     for (int k = 0; k < 9; k++) {
@@ -210,17 +310,16 @@ __global__ __launch_bounds__(256) void k_gauge_force(const cd* __restrict__ U, G
         A[k].x += __shfl_xor(A[k].x, 2, 4);
         A[k].y += __shfl_xor(A[k].y, 2, 4);
     }
-    if (!valid) return;
-    cd Um[9], M[9];
-    load_su3(U, lex, mu, Um);
-    mul_nn(Um, A, M);
+    cd M[9];
+    read(own + 36 * site + 9 * mu, cc);
+    mul_nn(cc, A, M);
     double o[8];
     im_tr_lambda(M, o);
     const double f = beta / 6.0;
     // components 2 nu and 2 nu + 1 (selects: a runtime index would move o[] to scratch memory)
     const double v0 = f * (nu == 0 ? o[0] : nu == 1 ? o[2] : nu == 2 ? o[4] : o[6]);
     const double v1 = f * (nu == 0 ? o[1] : nu == 1 ? o[3] : nu == 2 ? o[5] : o[7]);
-    double* q = (kick ? P : F) + (size_t)link * 8 + 2 * nu;
+    double* q = (kick ? P : F) + ((size_t)mu * V + lex) * 8 + 2 * nu;
     if (kick) {
         q[0] -= h * v0;
         q[1] -= h * v1;
@@ -248,22 +347,38 @@ __global__ __launch_bounds__(256) void k_kick(double* __restrict__ P, const doub
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) P[i] -= h * F[i];
 }
 
+// U <- exp(i h P) U, one thread per link in the order of U (64 links per wave, read and written as consecutive units).
+// With the exponential as a product of 18 matrix Horner steps and one cache line per lane and load it took 55 us on
+// 16^3 x 32 (185 MB); now 29 us, 6.4 TB/s (8^4: 10.2 -> 5.0 us).
 __global__ __launch_bounds__(256) void k_link_update(cd* __restrict__ U, const double* __restrict__ P, double h, Geom g) {
-    const int V = 2 * g.Vh;
-    const int tid = blockIdx.x * 256 + threadIdx.x;
-    if (tid >= 4 * V) return;
-    const int mu = tid / V, lex = tid - mu * V;
-    double p[8];
+    __shared__ v2d lds[4][576];
+    const int V = 2 * g.Vh;  // 4 V links: a multiple of 64
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int l0 = blockIdx.x * 256 + w * 64;
+    if (l0 >= 4 * V) return;  // whole waves
+    const int lex = (l0 + lane) >> 2, mu = lane & 3;
+    v2d* Uw = (v2d*)(U + (size_t)l0 * 9);
+    v2d r[9];
 #pragma unroll
-    for (int a = 0; a < 8; a++) p[a] = P[(size_t)tid * 8 + a];
+    for (int k = 0; k < 9; k++) r[k] = Uw[lane + 64 * k];
+    double p[8];
+    const v2d* Pl = (const v2d*)(P + ((size_t)mu * V + lex) * 8);
+#pragma unroll
+    for (int a = 0; a < 4; a++) {
+        const v2d v = Pl[a];
+        p[2 * a] = v.x;
+        p[2 * a + 1] = v.y;
+    }
     cd X[9], E[9], Uo[9], Un[9];
     i_algebra(p, h, X);
     su3_exp(X, E);
-    load_su3(U, lex, mu, Uo);
+    spread_links(lds[w], r, lane, Uo);
     mul_nn(E, Uo, Un);
-    cd* d = U + ((size_t)lex * 4 + mu) * 9;
 #pragma unroll
-    for (int k = 0; k < 9; k++) d[k] = Un[k];
+    for (int k = 0; k < 9; k++) lds[w][9 * lane + k] = v2d{Un[k].x, Un[k].y};
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 9; k++) Uw[lane + 64 * k] = lds[w][lane + 64 * k];
 }
 
 }  // namespace
@@ -276,9 +391,8 @@ hipError_t launch_plaquette(const cd* U, const Geom& g, const Red& red, hipStrea
 
 hipError_t launch_gauge_force(const cd* U, const Geom& g, double beta, double* F, double* P, double h, int kick,
                               hipStream_t st) {
-    const long n = 4 * 8 * (long)g.Vh;  // four lanes per link, 4 V links
-    if (n > (1l << 31) - 256) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_gauge_force, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, U, g, beta, F, P, h, kick);
+    if (4 * 8 * (long)g.Vh > (1l << 31) - 256) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_gauge_force, dim3(2 * g.Vh / 16), dim3(256), 0, st, U, g, beta, F, P, h, kick);
     return hipGetLastError();
 }
 

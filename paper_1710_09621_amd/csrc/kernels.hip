@@ -1167,11 +1167,15 @@ __global__ __launch_bounds__(256) void k_unpack5(const cpx<R>* __restrict__ half
     }
 }
 
-// links: canonical [lex][mu][3][3] -> packed [par][cb][mu][9], t-boundary phase folded into U_t(x_t = Lt-1)
-template <typename R>
-__global__ __launch_bounds__(256) void k_pack_links(const cd* __restrict__ U, cpx<R>* __restrict__ Up, Geom g,
-                                                    int par, double tbc) {
+// links: canonical [lex][mu][3][3] -> packed [par][cb][mu][9] in FP64 and FP32, t-boundary phase folded into
+// U_t(x_t = Lt-1); both parities in one launch
+__global__ __launch_bounds__(256) void k_pack_links(const cd* __restrict__ U, cd* __restrict__ D0, cd* __restrict__ D1,
+                                                    cpx<float>* __restrict__ F0, cpx<float>* __restrict__ F1, Geom g,
+                                                    double tbc) {
     const size_t n = (size_t)g.Vh * 36;
+    const int par = blockIdx.y;
+    cd* __restrict__ D = par ? D1 : D0;
+    cpx<float>* __restrict__ F = par ? F1 : F0;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
         int k = (int)(i % 9);
         int mu = (int)((i / 9) % 4);
@@ -1181,7 +1185,8 @@ __global__ __launch_bounds__(256) void k_pack_links(const cd* __restrict__ U, cp
         cd v = U[((size_t)lex * 4 + mu) * 9 + k];
         int t = lex / (g.Lx * g.Ly * g.Lz);
         if (mu == 3 && t == g.Lt - 1) { v.x *= tbc; v.y *= tbc; }
-        Up[i] = {(R)v.x, (R)v.y};
+        D[i] = v;
+        F[i] = {(float)v.x, (float)v.y};
     }
 }
 
@@ -1709,13 +1714,11 @@ hipError_t launch_unpack5(const cpx<R>* half, cd* canon, const Geom& g, int par,
 template hipError_t launch_unpack5<double>(const cd*, cd*, const Geom&, int, int, int, hipStream_t);
 template hipError_t launch_unpack5<float>(const cpx<float>*, cd*, const Geom&, int, int, int, hipStream_t);
 
-template <typename R>
-hipError_t launch_pack_links(const cd* U, cpx<R>* Up, const Geom& g, int par, double tbc, hipStream_t st) {
-    hipLaunchKernelGGL((k_pack_links<R>), dim3(nblk((size_t)g.Vh * 36)), dim3(256), 0, st, U, Up, g, par, tbc);
+hipError_t launch_pack_links(const cd* U, cd* const D[2], cpx<float>* const F[2], const Geom& g, double tbc,
+                             hipStream_t st) {
+    hipLaunchKernelGGL(k_pack_links, dim3(nblk((size_t)g.Vh * 36), 2), dim3(256), 0, st, U, D[0], D[1], F[0], F[1], g, tbc);
     return hipGetLastError();
 }
-template hipError_t launch_pack_links<double>(const cd*, cd*, const Geom&, int, double, hipStream_t);
-template hipError_t launch_pack_links<float>(const cd*, cpx<float>*, const Geom&, int, double, hipStream_t);
 
 hipError_t launch_source(const cd* phi, cd* const half[2], const Geom& g, int Ns, int chir, const SVec& coef,
                          hipStream_t st) {
