@@ -14,14 +14,17 @@ constexpr int CNN_NPARAM = CNN_LAYERS * CNN_LSZ;
 
 hipError_t cnn_conv_fwd(const unsigned short* X, const unsigned short* W, const float* bias, void* Y, bool out_f32,
                         const Geom& g, int Ns, int relu, hipStream_t st);
-int cnn_wgrad_chunks(int rows);
+// XT, dYT: site-transposed [cb][32][Ns]; part: cnn_wgrad_chunks x 81 x 1024 floats
+int cnn_wgrad_chunks(const Geom& g, int Ns);
 hipError_t cnn_wgrad(const unsigned short* dYT, const unsigned short* XT, float* part, float* gw, const Geom& g, int Ns,
                      int cin, int cout, hipStream_t st);
-// part: scratch of >= 256 x 32 doubles
-hipError_t cnn_bgrad(const float* dY, int rows, float* gb, int cout, double* part, hipStream_t st);
-hipError_t cnn_to_chmajor(const void* in, bool in_f32, unsigned short* out, int rows, hipStream_t st);
+// of the rows' output gradient dY (times act > 0 when act is given): BF16 rows (rows_out may be null), the
+// site-transposed copy and the bias gradient gb; part: scratch of CNN_PREP_PART doubles
+constexpr int CNN_PREP_PART = 1024 * 32;
+hipError_t cnn_dy_prep(const float* dY, const unsigned short* act, unsigned short* rows_out, unsigned short* dYT,
+                       double* part, float* gb, int cout, int rows, int Ns, hipStream_t st);
+hipError_t cnn_rows_to_site(const unsigned short* in, unsigned short* out, int rows, int Ns, hipStream_t st);
 hipError_t cnn_f32_to_bf16(const float* in, unsigned short* out, size_t n, hipStream_t st);
-hipError_t cnn_relu_bwd(float* d, const unsigned short* act, size_t n, hipStream_t st);
 hipError_t cnn_w_transpose(const float* w, unsigned short* wt, hipStream_t st);
 hipError_t cnn_adam(float* p, const float* g, float* m, float* v, size_t n, float lr, float b1, float b2, float eps,
                     float c1, float c2, float gscale, hipStream_t st);

@@ -436,7 +436,7 @@ constexpr int kAutoCheckEvery = 16;
 // ends where the residual is expected to reach its target by the rate measured so far (in CG iterations per factor e
 // of |r|^2): iterations past the target exit at once on the device, but each still costs its six launches, and a
 // reliable-update cycle (a factor 10 in |r|) is shorter than 16 iterations on small lattices, where 44% of the
-// iterations launched in blocks of 16 were such idle ones (trajectory on 8^4, FP16 columns: 317 -> 262 ms).
+// iterations launched in blocks of 16 were such idle ones (trajectory on 8^4, FP16 columns: 313 ms with blocks of 16, 251 ms).
 // Captured blocks come in multiples of 4, so that at most four graphs are kept per set of buffers.
 struct BlockRule {
     int ce;        // > 0: fixed block length
@@ -678,7 +678,8 @@ void cnn_alloc(eofa_ctx* ctx) {
         for (unsigned short** q : {&c.X0, &c.A[0], &c.A[1], &c.A[2], &c.dYb, &c.XT, &c.dYT})
             HIPCHK(hipMalloc(q, sizeof(unsigned short) * r32));
         for (float** q : {&c.Y, &c.T, &c.dY, &c.dA}) HIPCHK(hipMalloc(q, sizeof(float) * r32));
-        HIPCHK(hipMalloc(&c.part, sizeof(float) * (size_t)cnn_wgrad_chunks(rows) * 81 * 1024));
+        HIPCHK(hipMalloc(&c.part, std::max(sizeof(float) * (size_t)cnn_wgrad_chunks(ctx->g, ctx->Ns) * 81 * 1024,
+                                           sizeof(double) * (size_t)CNN_PREP_PART)));
         c.rows = rows;
     }
 }
@@ -731,14 +732,14 @@ double cnn_grad(eofa_ctx* ctx, const cd* rho, const cd* e) {
     const float* dcur = c.dY;
     for (int l = CNN_LAYERS - 1; l >= 0; l--) {
         const unsigned short* in = (l == 0) ? c.X0 : c.A[l - 1];
-        HIPCHK(cnn_to_chmajor(dcur, true, c.dYT, rows, ctx->st));
-        HIPCHK(cnn_to_chmajor(in, false, c.XT, rows, ctx->st));
+        // hidden layers: the ReLU masks the gradient of their output
+        const unsigned short* act = c.relu && l < CNN_LAYERS - 1 ? c.A[l] : nullptr;
+        HIPCHK(cnn_dy_prep(dcur, act, l > 0 ? c.dYb : nullptr, c.dYT, (double*)c.part,
+                           c.G + (size_t)l * CNN_LSZ + CNN_WSZ, CNN_COUT[l], rows, ctx->Ns, ctx->st));
+        HIPCHK(cnn_rows_to_site(in, c.XT, rows, ctx->Ns, ctx->st));
         HIPCHK(cnn_wgrad(c.dYT, c.XT, c.part, c.G + (size_t)l * CNN_LSZ, ctx->g, ctx->Ns, CNN_CIN[l], CNN_COUT[l], ctx->st));
-        HIPCHK(cnn_bgrad(dcur, rows, c.G + (size_t)l * CNN_LSZ + CNN_WSZ, CNN_COUT[l], (double*)c.part, ctx->st));
         if (l > 0) {
-            HIPCHK(cnn_f32_to_bf16(dcur, c.dYb, r32, ctx->st));
             HIPCHK(cnn_conv_fwd(c.dYb, c.Wt + (size_t)l * CNN_WSZ, nullptr, c.dA, true, ctx->g, ctx->Ns, 0, ctx->st));
-            if (c.relu) HIPCHK(cnn_relu_bwd(c.dA, c.A[l - 1], r32, ctx->st));
             dcur = c.dA;
         }
     }
