@@ -6,8 +6,15 @@
 // (xh, y, z, t) with periodic wrap.  Every layer is an implicit GEMM
 //     Y[row][n] = b[n] + sum_{tap < 81} sum_{k < 32} X[nbr(row, tap)][k] W[tap][n][k]
 // on v_mfma_f32_16x16x32_bf16 (BF16 operands, FP32 accumulation).  The weight gradient is a GEMM
-// whose reduction runs over rows; it uses site-transposed copies of X and dY, [cb][channel][s], so that 8
-// consecutive rows of one channel are one 16-byte operand and a site's channels lie side by side.
+// whose reduction runs over rows.
+//
+// BF16 operands lie in memory in the order in which the lanes of a wave hold them, units of 16 bytes, so that a load
+// instruction reads 1 KB (Ns = 8: pieces of 128 bytes) lane by lane: with the natural order, neighbouring lanes 64
+// bytes apart, the L1 needed two accesses for every 64 bytes and bound the convolutions.
+//   rows:    per site and group of G = min(16, Ns) slices  [k block of 8 channels][s][8 channels]   (row_unit)
+//   sites:   per site  [half of the channels][group of 8 slices][channel % 16][8 slices]           (site_unit)
+//   weights: per tap   [half of n][k block][n % 16][8 k]
+// FP32 rows (network output, target, gradients) are plain [row][32].
 #include <algorithm>
 
 #include "eofa_int.h"
@@ -33,240 +40,146 @@ struct CbGeom {
     int Vh;
 };
 
+// unit of the channels 8 kb .. 8 kb + 7 of slice s
+__device__ __forceinline__ size_t row_unit(size_t cb, int s, int kb, int Ns) {
+    const int G = Ns < 16 ? Ns : 16;
+    return cb * Ns * 4 + (s / G) * G * 4 + kb * G + s % G;
+}
+// unit of the slices s8 .. s8 + 7 (s8 % 8 == 0) of channel c
+__device__ __forceinline__ size_t site_unit(size_t cb, int s8, int c, int Ns) {
+    return cb * Ns * 4 + ((c >> 4) * (Ns >> 3) + (s8 >> 3)) * 16 + (c & 15);
+}
+typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
+
 // sites in y and z of a weight-gradient K step (32 rows at one xh)
 __host__ __device__ constexpr int wgrad_yg(int Ns) { return Ns <= 16 ? 2 : 1; }
 __host__ __device__ constexpr int wgrad_zg(int Ns) { return Ns == 8 ? 2 : 1; }
 
-// per-lane offsets of the three neighbours per dimension: off[d][0..2] for shifts -1, 0, +1
-__device__ __forceinline__ void cb_offsets(const CbGeom& g, int cb, int off[4][3]) {
-    int xh = cb % g.Lxh, r = cb / g.Lxh;
-    int y = r % g.Ly; r /= g.Ly;
-    int z = r % g.Lz;
-    int t = r / g.Lz;
-    const int sy = g.Lxh, sz = g.Lxh * g.Ly, st = sz * g.Lz;
-#pragma unroll
-    for (int d = -1; d <= 1; d++) {
-        off[0][d + 1] = (xh + d + g.Lxh) % g.Lxh;
-        off[1][d + 1] = ((y + d + g.Ly) % g.Ly) * sy;
-        off[2][d + 1] = ((z + d + g.Lz) % g.Lz) * sz;
-        off[3][d + 1] = ((t + d + g.Lt) % g.Lt) * st;
-    }
-}
-
-// tap = 27 (dt+1) + 9 (dz+1) + 3 (dy+1) + (dx+1); its mirror (-d) is 80 - tap.
-__device__ __forceinline__ int tap_cb(const int off[4][3], int tap) {
-    return off[0][tap % 3] + off[1][(tap / 3) % 3] + off[2][(tap / 9) % 3] + off[3][tap / 27];
-}
-
 // -------------------------------------------------------------------- forward conv
-// One wave computes 64 rows x 32 output channels (4 row tiles x 2 column tiles of 16x16).
-// X: [rows][32] bf16; W: [81][32 n][32 k] bf16; bias [32] f32 (may be null); Y: [rows][32] bf16 or f32.
-template <bool OUT_F32>
-__global__ __launch_bounds__(256) void k_conv_fwd(const unsigned short* __restrict__ X,
-                                                  const unsigned short* __restrict__ W,
-                                                  const float* __restrict__ bias, void* __restrict__ Y, CbGeom g,
-                                                  int rows, int relu) {
-    const int lane = threadIdx.x & 63;
-    const int wave = (blockIdx.x * 4) + (threadIdx.x >> 6);
-    const int row0 = wave * 64;
-    if (row0 >= rows) return;
-    const int li = lane & 15;   // row within a tile (A) / column within a tile (B, D)
-    const int kb = lane >> 4;   // which 8-wide k block
-    int off[4][4][3];
-    int srow[4];
-#pragma unroll
-    for (int t = 0; t < 4; t++) {
-        int r = row0 + t * 16 + li;
-        if (r >= rows) r = rows - 1;
-        const int cb = r / g.Ns;
-        srow[t] = r - cb * g.Ns;
-        cb_offsets(g, cb, off[t]);
+// X: bf16 rows; W: bf16 weights; bias [32] f32 (may be null); Y: bf16 rows or f32 rows.  The weights are the first
+// operand, so that a lane's four results are consecutive channels of one row.
+// The 16 rows of a matrix-core tile are slices of one site (Ns = 16; Ns = 8: two sites in y; Ns = 32: one half of the
+// slices), so a tile's A operand is 1 KB of consecutive memory and the tile of x + dx is the operand of the tap dx at x.
+// A wave owns LEN tiles along xh (a whole line: WHOLE, else a segment) on NL neighbouring lines in y, reads the
+// operands of one (dt, dz, dy) group of taps per line once (LEN loads, LEN + 2 for a segment) and uses each for the
+// three dx: 6 LEN NL MFMAs.  The next group's operands and weights are requested before this group's MFMAs.  Taps are
+// added in order, 0 .. 80.  No LDS halo: the operands come from L1 and L2; MFMAs and L1 accesses (14 KB per 48 MFMAs
+// of 16 cycles at LEN = 8) are close to balance.  16^3 x 32, Ns = 16: 160 us a layer (174 GFLOP), against 317 us with
+// a 4 x 4 x 2 x 2 block and its halo staged in LDS, where every tap re-read its operands.
+struct ConvJobs {
+    int nx, ny, nz, ns;  // segments, groups of NL lines, z extent, halves of the slices
+    int total;
+};
+
+template <int LEN, int NL, bool WHOLE, bool OUT_F32>
+__global__ __launch_bounds__(256, 2) void k_conv(const unsigned short* __restrict__ X, const unsigned short* __restrict__ W,
+                                              const float* __restrict__ bias, void* __restrict__ Y, CbGeom g, ConvJobs jobs,
+                                              int relu) {
+    constexpr int NF = WHOLE ? LEN : LEN + 2;
+    const int lane = threadIdx.x & 63, li = lane & 15, kb = lane >> 4;
+    int b = blockIdx.x;
+    {   // hardware dispatches workgroup b to XCD b % 8: every XCD takes one contiguous range of the lattice
+        const int n = gridDim.x, x = b & 7, i = b >> 3, q = n >> 3, m = n & 7;
+        b = x * q + (x < m ? x : m) + i;
     }
-    f32x4 acc[4][2];
+    int job = b * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (job >= jobs.total) return;
+    const int YT = g.Ns == 8 ? 2 : 1, ny = g.Ly / YT;
+    const int js = job % jobs.ns; job /= jobs.ns;
+    const int jx = job % jobs.nx; job /= jobs.nx;
+    const int jy = job % jobs.ny; job /= jobs.ny;
+    const int z = job % jobs.nz, t = job / jobs.nz;
+    // the last segment and the last group of lines may overlap the one before (the same values are written twice)
+    const int x0 = WHOLE ? 0 : min(jx * LEN, g.Lxh - LEN), y0 = min(jy * NL, ny - NL) * YT;
+    const int iy = g.Ns == 8 ? li >> 3 : 0, s = g.Ns == 8 ? li & 7 : js * 16 + li;
+    auto wrap = [](int v, int L) { return v < 0 ? v + L : v >= L ? v - L : v; };
+    const size_t sx = (size_t)g.Ns * 32;  // one site
+    const size_t lo = row_unit(0, s, kb, g.Ns) * 8;
+    // operands of the (dt, dz, dy) group tq: f[line][j], xh = x0 + j (WHOLE) or x0 - 1 + j
+    auto load_group = [&](int tq, bf16x8 (*f)[NF]) {
+        const int dy = tq % 3 - 1, dz = (tq / 3) % 3 - 1, dt = tq / 9 - 1;
+        const size_t zt = (size_t)g.Lxh * g.Ly * (wrap(z + dz, g.Lz) + (size_t)g.Lz * wrap(t + dt, g.Lt));
 #pragma unroll
-    for (int t = 0; t < 4; t++) {
-        acc[t][0] = {0, 0, 0, 0};
-        acc[t][1] = {0, 0, 0, 0};
-    }
-    for (int tap = 0; tap < 81; tap++) {
-        const unsigned short* wt = W + (size_t)tap * 1024;
-        const bf16x8 b0 = *(const bf16x8*)(wt + li * 32 + kb * 8);
-        const bf16x8 b1 = *(const bf16x8*)(wt + (16 + li) * 32 + kb * 8);
+        for (int l = 0; l < NL; l++) {
+            const unsigned short* p =
+                X + (zt + (size_t)g.Lxh * wrap(y0 + l * YT + iy + dy, g.Ly)) * sx + lo;
+            if constexpr (WHOLE) {
 #pragma unroll
-        for (int t = 0; t < 4; t++) {
-            const int nrow = tap_cb(off[t], tap) * g.Ns + srow[t];
-            const bf16x8 a = *(const bf16x8*)(X + (size_t)nrow * 32 + kb * 8);
-            acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b0, acc[t][0], 0, 0, 0);
-            acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b1, acc[t][1], 0, 0, 0);
-        }
-    }
-    // D layout: lane holds rows 4*kb + j (j < 4) of the tile, column li (+16 for the second half)
+                for (int j = 0; j < LEN; j++) f[l][j] = *(const bf16x8*)(p + j * sx);
+            } else {
+                f[l][0] = *(const bf16x8*)(p + (x0 == 0 ? g.Lxh - 1 : x0 - 1) * sx);
 #pragma unroll
-    for (int t = 0; t < 4; t++)
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const int n = h * 16 + li;
-            const float bn = bias ? bias[n] : 0.0f;
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const int r = row0 + t * 16 + kb * 4 + j;
-                if (r >= rows) continue;
-                float v = acc[t][h][j] + bn;
-                if (relu && v < 0.0f) v = 0.0f;
-                if constexpr (OUT_F32) ((float*)Y)[(size_t)r * 32 + n] = v;
-                else ((unsigned short*)Y)[(size_t)r * 32 + n] = bf16_bits(v);
+                for (int j = 0; j < LEN; j++) f[l][j + 1] = *(const bf16x8*)(p + (x0 + j) * sx);
+                f[l][LEN + 1] = *(const bf16x8*)(p + (x0 + LEN == g.Lxh ? 0 : x0 + LEN) * sx);
             }
         }
-}
-
-// -------------------------------------------------------------------- forward conv, LDS-tiled
-// A workgroup (2 waves) owns a 4 x 4 x 2 x 2 block of compressed sites (xh, y, z, t) and 2 s-slices
-// = 128 rows.  It stages the block with its one-site halo (6 x 6 x 4 x 4 sites x 2 slices x 64 B =
-// 72 KB) in LDS once, then every tap reads its A operands from LDS: global traffic is the halo
-// (9x the block) instead of one gathered row block per tap (81x).  Needs Lxh % 4 == 0, Ly % 4 == 0,
-// Lz, Lt, Ns even.
-constexpr int CT_X = 4, CT_Y = 4, CT_Z = 2, CT_T = 2, CT_S = 2;
-constexpr int CH_X = CT_X + 2, CH_Y = CT_Y + 2, CH_Z = CT_Z + 2, CH_T = CT_T + 2;
-constexpr int CH_SITES = CH_X * CH_Y * CH_Z * CH_T;  // 576
-constexpr int CT_ROWS = CT_X * CT_Y * CT_Z * CT_T * CT_S;  // 128
-
-template <bool OUT_F32>
-__global__ __launch_bounds__(128) void k_conv_fwd_lds(const unsigned short* __restrict__ X,
-                                                      const unsigned short* __restrict__ W,
-                                                      const float* __restrict__ bias, void* __restrict__ Y, CbGeom g,
-                                                      int relu) {
-    // 16-byte units: [halo site][slice][4 k-blocks]
-    __shared__ uint4 lds[CH_SITES * CT_S * 4];
-    const int nbx = g.Lxh / CT_X, nby = g.Ly / CT_Y, nbz = g.Lz / CT_Z, nbt = g.Lt / CT_T;
-    int b = blockIdx.x;
-    const int bx = b % nbx; b /= nbx;
-    const int by = b % nby; b /= nby;
-    const int bz = b % nbz; b /= nbz;
-    const int bt = b % nbt; b /= nbt;
-    const int s0 = b * CT_S;
-    const int x0 = bx * CT_X, y0 = by * CT_Y, z0 = bz * CT_Z, t0 = bt * CT_T;
-    // stage: halo site h -> its 2 rows (128 contiguous bytes) = 8 chunks of 16 B; 36 chunks per thread,
-    // loaded in batches of 12 independent loads (wrap by compare, no integer division by the extents)
-    auto wrap = [](int v, int L) { return v < 0 ? v + L : (v >= L ? v - L : v); };
-    constexpr int PER = CH_SITES * 8 / 128, BATCH = 12;
-    static_assert(PER % BATCH == 0, "staging batches");
-#pragma unroll
-    for (int i0 = 0; i0 < PER; i0 += BATCH) {
-        uint4 v[BATCH];
-#pragma unroll
-        for (int i = 0; i < BATCH; i++) {
-            const int c = threadIdx.x + 128 * (i0 + i);
-            int h = c >> 3;
-            const int part = c & 7;
-            const int hx = h % CH_X; h /= CH_X;
-            const int hy = h % CH_Y; h /= CH_Y;
-            const int hz = h % CH_Z;
-            const int ht = h / CH_Z;
-            const int gx = wrap(x0 + hx - 1, g.Lxh), gy = wrap(y0 + hy - 1, g.Ly);
-            const int gz = wrap(z0 + hz - 1, g.Lz), gt = wrap(t0 + ht - 1, g.Lt);
-            const size_t cb = (size_t)gx + (size_t)g.Lxh * (gy + (size_t)g.Ly * (gz + (size_t)g.Lz * gt));
-            v[i] = *(const uint4*)(X + (cb * g.Ns + s0) * 32 + part * 8);
-        }
-#pragma unroll
-        for (int i = 0; i < BATCH; i++) lds[threadIdx.x + 128 * (i0 + i)] = v[i];
-    }
-    __syncthreads();
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int li = lane & 15, kb = lane >> 4;
-    // tile rows: r = site * 2 + slice, site = ((lt * CT_Z + lz) * CT_Y + ly) * CT_X + lx; wave w owns rows [64w, 64w+64)
-    int abase[4];
-#pragma unroll
-    for (int t = 0; t < 4; t++) {
-        const int r = wave * 64 + t * 16 + li;
-        const int sl = r & 1;
-        int site = r >> 1;
-        const int lx = site % CT_X; site /= CT_X;
-        const int ly = site % CT_Y; site /= CT_Y;
-        const int lz = site % CT_Z;
-        const int lt = site / CT_Z;
-        const int hs = (lx + 1) + CH_X * ((ly + 1) + CH_Y * ((lz + 1) + CH_Z * (lt + 1)));
-        abase[t] = (hs * CT_S + sl) * 4 + kb;
-    }
-    f32x4 acc[4][2];
-#pragma unroll
-    for (int t = 0; t < 4; t++) {
-        acc[t][0] = {0, 0, 0, 0};
-        acc[t][1] = {0, 0, 0, 0};
-    }
-    // the weights of the next (dt, dz, dy) group of 3 taps are in flight while this group computes
-    const unsigned short* wl = W + li * 32 + kb * 8;
-    bf16x8 bw[3][2];
-#pragma unroll
-    for (int d = 0; d < 3; d++) {
-        bw[d][0] = *(const bf16x8*)(wl + (size_t)d * 1024);
-        bw[d][1] = *(const bf16x8*)(wl + (size_t)d * 1024 + 512);
-    }
-    // A fragments of a (dt, dz, dy) group of 3 taps: [dx][row tile]; the next group's are read from LDS
-    // while this group's 24 MFMAs run
-    auto load_group = [&](int tq, uint4 (*a)[4]) {
-        const int dy = tq % 3 - 1, dz = (tq / 3) % 3 - 1, dt = tq / 9 - 1;
-        const int off_yzt = CH_X * (dy + CH_Y * (dz + CH_Z * dt));
-#pragma unroll
-        for (int dx = -1; dx <= 1; dx++)
-#pragma unroll
-            for (int t = 0; t < 4; t++) a[dx + 1][t] = lds[abase[t] + (off_yzt + dx) * CT_S * 4];
     };
-    uint4 acur[3][4], anext[3][4];
-    load_group(0, acur);
-    for (int tq = 0; tq < 27; tq++) {
-        bf16x8 bn[3][2];
-        const int tn = (tq < 26 ? tq + 1 : tq);
+    const unsigned short* wl = W + lane * 8;
+    auto load_w = [&](int tq, bf16x8 (*w)[2]) {
 #pragma unroll
         for (int d = 0; d < 3; d++) {
-            bn[d][0] = *(const bf16x8*)(wl + (size_t)(3 * tn + d) * 1024);
-            bn[d][1] = *(const bf16x8*)(wl + (size_t)(3 * tn + d) * 1024 + 512);
+            w[d][0] = *(const bf16x8*)(wl + (size_t)(3 * tq + d) * 1024);
+            w[d][1] = *(const bf16x8*)(wl + (size_t)(3 * tq + d) * 1024 + 512);
         }
-        load_group(tn, anext);
+    };
+    f32x4 acc[NL][LEN][2];
+#pragma unroll
+    for (int l = 0; l < NL; l++)
+#pragma unroll
+        for (int j = 0; j < LEN; j++) acc[l][j][0] = acc[l][j][1] = {0, 0, 0, 0};
+    bf16x8 f[NL][NF], fn[NL][NF], w[3][2], wn[3][2];
+    load_group(0, f);
+    load_w(0, w);
+    for (int tq = 0; tq < 27; tq++) {
+        const int tn = tq < 26 ? tq + 1 : tq;
+        load_group(tn, fn);
+        load_w(tn, wn);
+        __builtin_amdgcn_sched_barrier(0);  // the requests stay ahead of the MFMAs
 #pragma unroll
         for (int d = 0; d < 3; d++)
 #pragma unroll
-            for (int t = 0; t < 4; t++) {
-                const bf16x8 a = __builtin_bit_cast(bf16x8, acur[d][t]);
-                acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bw[d][0], acc[t][0], 0, 0, 0);
-                acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bw[d][1], acc[t][1], 0, 0, 0);
-            }
+            for (int l = 0; l < NL; l++)
+#pragma unroll
+                for (int j = 0; j < LEN; j++) {
+                    const bf16x8 a = f[l][WHOLE ? (j + d - 1 + LEN) % LEN : j + d];
+                    acc[l][j][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[d][0], a, acc[l][j][0], 0, 0, 0);
+                    acc[l][j][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[d][1], a, acc[l][j][1], 0, 0, 0);
+                }
+#pragma unroll
+        for (int l = 0; l < NL; l++)
+#pragma unroll
+            for (int j = 0; j < NF; j++) f[l][j] = fn[l][j];
 #pragma unroll
         for (int d = 0; d < 3; d++) {
-            bw[d][0] = bn[d][0];
-            bw[d][1] = bn[d][1];
-#pragma unroll
-            for (int t = 0; t < 4; t++) acur[d][t] = anext[d][t];
+            w[d][0] = wn[d][0];
+            w[d][1] = wn[d][1];
         }
     }
+    // D layout: lane holds channels 16 h + 4 kb .. + 3 of row li of the tile
 #pragma unroll
-    for (int t = 0; t < 4; t++)
+    for (int h = 0; h < 2; h++) {
+        const int n = h * 16 + kb * 4;
+        const f32x4 bn = bias ? *(const f32x4*)(bias + n) : f32x4{0, 0, 0, 0};
 #pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const int n = h * 16 + li;
-            const float bn = bias ? bias[n] : 0.0f;
+        for (int l = 0; l < NL; l++) {
+            const size_t c0 = x0 + (size_t)g.Lxh * (y0 + l * YT + iy + (size_t)g.Ly * (z + (size_t)g.Lz * t));
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const int r = wave * 64 + t * 16 + kb * 4 + j;
-                const int sl = r & 1;
-                int site = r >> 1;
-                const int lx = site % CT_X; site /= CT_X;
-                const int ly = site % CT_Y; site /= CT_Y;
-                const int lz = site % CT_Z;
-                const int lt = site / CT_Z;
-                const size_t cb = (size_t)(x0 + lx) +
-                                  (size_t)g.Lxh * ((y0 + ly) + (size_t)g.Ly * ((z0 + lz) + (size_t)g.Lz * (t0 + lt)));
-                const size_t row = cb * g.Ns + s0 + sl;
-                float v = acc[t][h][j] + bn;
-                if (relu && v < 0.0f) v = 0.0f;
-                if constexpr (OUT_F32) ((float*)Y)[row * 32 + n] = v;
-                else ((unsigned short*)Y)[row * 32 + n] = bf16_bits(v);
+            for (int j = 0; j < LEN; j++) {
+                f32x4 v = acc[l][j][h] + bn;
+                if (relu)
+#pragma unroll
+                    for (int i = 0; i < 4; i++)
+                        if (v[i] < 0.0f) v[i] = 0.0f;
+                if constexpr (OUT_F32) {
+                    *(f32x4*)((float*)Y + ((c0 + j) * g.Ns + s) * 32 + n) = v;
+                } else {
+                    const u16x4 o = {bf16_bits(v[0]), bf16_bits(v[1]), bf16_bits(v[2]), bf16_bits(v[3])};
+                    *(u16x4*)((unsigned short*)Y + row_unit(c0 + j, s, n >> 3, g.Ns) * 8 + (n & 7)) = o;
+                }
             }
         }
-}
-
-static bool conv_tiles(const CbGeom& g) {
-    return g.Lxh % CT_X == 0 && g.Ly % CT_Y == 0 && g.Lz % CT_Z == 0 && g.Lt % CT_T == 0 && g.Ns % CT_S == 0;
+    }
 }
 
 // -------------------------------------------------------------------- weight gradient
@@ -276,12 +189,12 @@ static bool conv_tiles(const CbGeom& g) {
 // its (dt, dz, dy) group in registers, so a step reads one new X column and one dY column (4 KB, in full cache lines)
 // for the 12 MFMAs of the three taps dx.  Each wave of a workgroup takes one of the 27 groups over the workgroup's
 // columns; part[chunk][tap][32][32] are summed by k_wgrad_reduce.  Bound by what the L1 delivers (64 B per cycle and
-// CU, 12 MFMAs of 16 cycles per 4 KB).  16^3 x 32, Ns = 16: 256 us a layer (173 GFLOP), against 1199 us with
+// CU, 12 MFMAs of 16 cycles per 4 KB).  16^3 x 32, Ns = 16: 223 us a layer (173 GFLOP), against 1199 us with
 // operands gathered per tap from channel-major copies, in segments of half a cache line.
 template <int NS>
 __global__ __launch_bounds__(256) void k_conv_wgrad(const unsigned short* __restrict__ dYT,
                                                     const unsigned short* __restrict__ XT, float* __restrict__ part,
-                                                    CbGeom g, int nlines, int lines_per_chunk) {
+                                                    CbGeom g, int nlines) {
     constexpr int YG = wgrad_yg(NS), ZG = wgrad_zg(NS), STEP = 32 * NS;
     const int lane = threadIdx.x & 63, tq = blockIdx.y * 4 + (threadIdx.x >> 6), chunk = blockIdx.x;
     if (tq >= 27) return;
@@ -294,22 +207,25 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(const unsigned short* __rest
     auto wrap = [](int v, int L) { return v < 0 ? v + L : v >= L ? v - L : v; };
     auto ld = [](const unsigned short* q, bf16x8 f[2]) {
         f[0] = *(const bf16x8*)q;
-        f[1] = *(const bf16x8*)(q + 16 * NS);
+        f[1] = *(const bf16x8*)(q + 16 * NS);  // the other half of the channels
     };
     f32x4 acc[3][2][2];  // [dx][n tile][k tile]
 #pragma unroll
     for (int d = 0; d < 3; d++)
 #pragma unroll
         for (int k = 0; k < 4; k++) acc[d][k >> 1][k & 1] = {0, 0, 0, 0};
-    const int l1 = min(nlines, (chunk + 1) * lines_per_chunk);
-    for (int l = chunk * lines_per_chunk; l < l1; l++) {
+    // Chunks of one XCD (workgroup b runs on XCD b % 8) take the lines of one contiguous range in turn, so that what
+    // runs at one time reads neighbouring lines: in ranges of their own, half of the L2 accesses missed.
+    const int nx = gridDim.x % 8 == 0 ? 8 : 1, xcd = chunk % nx, turn = gridDim.x / nx;
+    const int l0 = (int)((long)nlines * xcd / nx), l1 = (int)((long)nlines * (xcd + 1) / nx);
+    for (int l = l0 + chunk / nx; l < l1; l += turn) {
         const int yg = l % ny, r = l / ny, zg = r % nz, t = r / nz;
         const int y = yg * YG + iy, z = zg * ZG + iz;
         const size_t ca = (size_t)g.Lxh * (y + (size_t)g.Ly * (z + (size_t)g.Lz * t));
         const size_t cx = (size_t)g.Lxh *
                           (wrap(y + dy, g.Ly) + (size_t)g.Ly * (wrap(z + dz, g.Lz) + (size_t)g.Lz * wrap(t + dt, g.Lt)));
-        const unsigned short* pa = dYT + (ca * 32 + li) * NS + s8;
-        const unsigned short* px = XT + (cx * 32 + li) * NS + s8;
+        const unsigned short* pa = dYT + site_unit(ca, s8, li, NS) * 8;
+        const unsigned short* px = XT + site_unit(cx, s8, li, NS) * 8;
         bf16x8 fm[2], f0[2], fp[2], a[2];
         ld(px + (size_t)(g.Lxh - 1) * STEP, fm);
         ld(px, f0);
@@ -321,6 +237,7 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(const unsigned short* __rest
             const int xa = x + 1 < g.Lxh ? x + 1 : 0, xf = xa + 1 < g.Lxh ? xa + 1 : 0;
             ld(pa + (size_t)xa * STEP, an);
             ld(px + (size_t)xf * STEP, fn);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int n = 0; n < 2; n++)
 #pragma unroll
@@ -378,14 +295,15 @@ __global__ __launch_bounds__(256) void k_dy_prep(const float* __restrict__ dY, c
         double sum[256][8];
     } sh;
     const int row = threadIdx.x >> 2, q = threadIdx.x & 3, c = threadIdx.x >> 3, g8 = threadIdx.x & 7;
-    typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int r0 = blockIdx.x * 64; r0 < rows; r0 += gridDim.x * 64) {  // rows is a multiple of 64
         const size_t e = (size_t)(r0 + row) * 32 + q * 8;
+        const int cr = (r0 + row) / Ns;
+        const size_t u = row_unit(cr, r0 + row - cr * Ns, q, Ns) * 8;
         const f32x4 v0 = *(const f32x4*)(dY + e), v1 = *(const f32x4*)(dY + e + 4);
         float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
         if (act) {
-            const u16x8 a = *(const u16x8*)(act + e);
+            const u16x8 a = *(const u16x8*)(act + u);
 #pragma unroll
             for (int k = 0; k < 8; k++)
                 if (bf16_float(a[k]) <= 0.0f) v[k] = 0.0f;
@@ -397,10 +315,10 @@ __global__ __launch_bounds__(256) void k_dy_prep(const float* __restrict__ dY, c
             h[k] = bf16_bits(v[k]);
             sh.tile[q * 8 + k][row] = h[k];
         }
-        if (rows_out) *(u16x8*)(rows_out + e) = h;
+        if (rows_out) *(u16x8*)(rows_out + u) = h;
         __syncthreads();
         const int r8 = r0 + g8 * 8, cb = r8 / Ns;
-        *(u16x8*)(dYT + ((size_t)cb * 32 + c) * Ns + (r8 - cb * Ns)) = *(const u16x8*)&sh.tile[c][g8 * 8];
+        *(u16x8*)(dYT + site_unit(cb, r8 - cb * Ns, c, Ns) * 8) = *(const u16x8*)&sh.tile[c][g8 * 8];
         __syncthreads();
     }
 #pragma unroll
@@ -429,32 +347,31 @@ __global__ __launch_bounds__(1024) void k_bgrad_fin(const double* __restrict__ p
 }
 
 // -------------------------------------------------------------------- elementwise helpers
-// [rows][32] bf16 -> site-transposed [cb][32][Ns] bf16, 64 rows per workgroup through LDS (16-byte reads and writes)
+// bf16 rows -> bf16 sites, 64 rows per workgroup through LDS (16-byte reads and writes)
 __global__ __launch_bounds__(256) void k_rows_to_site(const unsigned short* __restrict__ in,
                                                       unsigned short* __restrict__ out, int Ns) {
     __shared__ unsigned short tile[32][72];
-    typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
-    const int row = threadIdx.x >> 2, q = threadIdx.x & 3, c = threadIdx.x >> 3, g8 = threadIdx.x & 7;
+    // 64 rows are 256 consecutive units: thread -> (row, k block) in the order of the units
+    const int G = Ns < 16 ? Ns : 16, blk = threadIdx.x / (4 * G), w = threadIdx.x % (4 * G), q = w / G, row = blk * G + w % G;
+    const int c = threadIdx.x >> 3, g8 = threadIdx.x & 7;
     const size_t r0 = (size_t)blockIdx.x * 64;
-    const u16x8 v = *(const u16x8*)(in + (r0 + row) * 32 + q * 8);
+    const u16x8 v = *(const u16x8*)(in + r0 * 32 + threadIdx.x * 8);
 #pragma unroll
     for (int k = 0; k < 8; k++) tile[q * 8 + k][row] = v[k];
     __syncthreads();
     const size_t r8 = r0 + g8 * 8, cb = r8 / Ns;
-    *(u16x8*)(out + (cb * 32 + c) * Ns + (r8 - cb * Ns)) = *(const u16x8*)&tile[c][g8 * 8];
+    *(u16x8*)(out + site_unit(cb, (int)(r8 - cb * Ns), c, Ns) * 8) = *(const u16x8*)&tile[c][g8 * 8];
 }
 
-// f32 -> bf16 (same layout)
-__global__ __launch_bounds__(256) void k_f32_to_bf16(const float* __restrict__ in, unsigned short* __restrict__ out, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) out[i] = bf16_bits(in[i]);
-}
-
-// Weights for the backward-data convolution: Wt[tap][k][n] = W[80 - tap][n][k]
-__global__ __launch_bounds__(256) void k_w_transpose(const float* __restrict__ w, unsigned short* __restrict__ wt) {
+// bf16 copies of one layer's weights [81][32 n][32 k] in the order of the lanes: the layer itself, and for the
+// backward-data convolution Wt[tap][k][n] = W[80 - tap][n][k]
+__global__ __launch_bounds__(256) void k_w_pack(const float* __restrict__ w, unsigned short* __restrict__ wb,
+                                                unsigned short* __restrict__ wt) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= 81 * 1024) return;
-    const int tap = i / 1024, k = (i / 32) % 32, n = i % 32;
-    wt[i] = bf16_bits(w[(size_t)(80 - tap) * 1024 + n * 32 + k]);
+    const int tap = i / 1024, e = i % 1024, kk = e & 7, n = (e >> 9) * 16 + ((e >> 3) & 15), k = ((e >> 7) & 3) * 8 + kk;
+    wb[i] = bf16_bits(w[(size_t)tap * 1024 + n * 32 + k]);
+    wt[i] = bf16_bits(w[(size_t)(80 - tap) * 1024 + k * 32 + n]);
 }
 
 // Adam on the FP32 master parameters
@@ -471,22 +388,24 @@ __global__ __launch_bounds__(256) void k_adam(float* __restrict__ p, const float
     }
 }
 
-// half field [cb][12][Ns] (complex double) -> rows [cb*Ns + s][32] bf16 scaled by sc (24 live channels)
+// half field [cb][12][Ns] (complex double) -> bf16 rows scaled by sc (24 live channels); a thread writes one unit
 __global__ __launch_bounds__(256) void k_half_to_rows(const cd* __restrict__ h, unsigned short* __restrict__ X, int Vh,
                                                       int Ns, const double* __restrict__ scale_ptr, int inv) {
     const double sc = inv ? 1.0 / sqrt(*scale_ptr) : *scale_ptr;
-    const size_t n = (size_t)Vh * Ns * 32;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-        const int c = (int)(i % 32);
-        const size_t row = i / 32;
-        const int s = (int)(row % Ns);
-        const size_t cb = row / Ns;
-        float v = 0.0f;
-        if (c < 24) {
-            const cd z = h[(cb * 12 + (c >> 1)) * Ns + s];
-            v = (float)(sc * ((c & 1) ? z.y : z.x));
-        }
-        X[i] = bf16_bits(v);
+    const int G = Ns < 16 ? Ns : 16, per = 4 * G;
+    const size_t n = (size_t)Vh * Ns * 4;
+    for (size_t u = (size_t)blockIdx.x * 256 + threadIdx.x; u < n; u += (size_t)gridDim.x * 256) {
+        const size_t grp = u / per, cb = grp / (Ns / G);
+        const int e = (int)(u - grp * per), kb = e / G, s = (int)(grp - cb * (Ns / G)) * G + e % G;
+        u16x8 o = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (kb < 3)
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const cd z = h[(cb * 12 + kb * 4 + j) * Ns + s];
+                o[2 * j] = bf16_bits((float)(sc * z.x));
+                o[2 * j + 1] = bf16_bits((float)(sc * z.y));
+            }
+        *(u16x8*)(X + u * 8) = o;
     }
 }
 
@@ -545,37 +464,66 @@ static inline int grid_for(size_t n) {
 static CbGeom cbg(const Geom& g, int Ns) { return CbGeom{g.Lxh, g.Ly, g.Lz, g.Lt, Ns, g.Vh}; }
 
 
+template <int LEN, int NL, bool WHOLE>
+static hipError_t conv_launch(const unsigned short* X, const unsigned short* W, const float* bias, void* Y, bool out_f32,
+                              const CbGeom& g, int relu, hipStream_t st) {
+    const int YT = g.Ns == 8 ? 2 : 1, ny = g.Ly / YT;
+    ConvJobs j{WHOLE ? 1 : (g.Lxh + LEN - 1) / LEN, (ny + NL - 1) / NL, g.Lz, g.Ns == 32 ? 2 : 1, 0};
+    j.total = j.nx * j.ny * j.nz * j.ns * g.Lt;
+    const int wpb = j.total < 1024 ? 1 : 4;  // waves per workgroup: a few waves are spread over the CUs
+    const dim3 grid((j.total + wpb - 1) / wpb), block(64 * wpb);
+    if (out_f32) hipLaunchKernelGGL((k_conv<LEN, NL, WHOLE, true>), grid, block, 0, st, X, W, bias, Y, g, j, relu);
+    else hipLaunchKernelGGL((k_conv<LEN, NL, WHOLE, false>), grid, block, 0, st, X, W, bias, Y, g, j, relu);
+    return hipGetLastError();
+}
+
+// Tiles per wave by rule: whole lines up to 8 sites, else segments of equal length (5 .. 8); short lines are taken
+// 2 or 4 at a time, as far as the y extent goes, so that the weights of a group serve up to 8 tiles.
 hipError_t cnn_conv_fwd(const unsigned short* X, const unsigned short* W, const float* bias, void* Y, bool out_f32,
                         const Geom& g, int Ns, int relu, hipStream_t st) {
-    const CbGeom cg = cbg(g, Ns);
-    if (conv_tiles(cg)) {
-        const int nblk = g.Vh * Ns / CT_ROWS;
-        if (out_f32) hipLaunchKernelGGL(k_conv_fwd_lds<true>, dim3(nblk), dim3(128), 0, st, X, W, bias, Y, cg, relu);
-        else hipLaunchKernelGGL(k_conv_fwd_lds<false>, dim3(nblk), dim3(128), 0, st, X, W, bias, Y, cg, relu);
-        return hipGetLastError();
+    if (Ns != 8 && Ns != 16 && Ns != 32) return hipErrorInvalidValue;
+    const CbGeom c = cbg(g, Ns);
+    // lines taken together: while that leaves two waves per SIMD
+    const int lines = c.Ly / (Ns == 8 ? 2 : 1) * c.Lz * c.Lt * (Ns == 32 ? 2 : 1);
+    const int ny = std::min(c.Ly / (Ns == 8 ? 2 : 1), std::max(1, lines / 2048));
+#define CONV(L, N, WH) return conv_launch<L, N, WH>(X, W, bias, Y, out_f32, c, relu, st)
+    switch (c.Lxh) {
+    case 1: if (ny >= 4) CONV(1, 4, true); else if (ny >= 2) CONV(1, 2, true); else CONV(1, 1, true);
+    case 2: if (ny >= 4) CONV(2, 4, true); else if (ny >= 2) CONV(2, 2, true); else CONV(2, 1, true);
+    case 3: if (ny >= 2) CONV(3, 2, true); else CONV(3, 1, true);
+    case 4: if (ny >= 2) CONV(4, 2, true); else CONV(4, 1, true);
+    case 5: CONV(5, 1, true);
+    case 6: CONV(6, 1, true);
+    case 7: CONV(7, 1, true);
+    case 8: CONV(8, 1, true);
     }
-    const int rows = g.Vh * Ns;
-    const int waves = (rows + 63) / 64;
-    const int grid = (waves + 3) / 4;
-    if (out_f32) hipLaunchKernelGGL(k_conv_fwd<true>, dim3(grid), dim3(256), 0, st, X, W, bias, Y, cbg(g, Ns), rows, relu);
-    else hipLaunchKernelGGL(k_conv_fwd<false>, dim3(grid), dim3(256), 0, st, X, W, bias, Y, cbg(g, Ns), rows, relu);
-    return hipGetLastError();
+    const int nseg = (c.Lxh + 7) / 8;
+    switch ((c.Lxh + nseg - 1) / nseg) {
+    case 5: CONV(5, 1, false);
+    case 6: CONV(6, 1, false);
+    case 7: CONV(7, 1, false);
+    default: CONV(8, 1, false);
+    }
+#undef CONV
 }
 
 // chunks of the weight gradient: all their workgroups (7 per chunk, four waves each) fit the chip at once at four
 // per CU, and a multiple of 8 keeps the seven workgroups of a chunk on one XCD (workgroup b runs on XCD b % 8)
 constexpr int WGRAD_CHUNKS = 144;
 static int wgrad_lines(const Geom& g, int Ns) { return g.Ly / wgrad_yg(Ns) * (g.Lz / wgrad_zg(Ns)) * g.Lt; }
-int cnn_wgrad_chunks(const Geom& g, int Ns) { return std::min(wgrad_lines(g, Ns), WGRAD_CHUNKS); }
+int cnn_wgrad_chunks(const Geom& g, int Ns) {
+    const int n = std::min(wgrad_lines(g, Ns), WGRAD_CHUNKS);
+    return n < 8 ? n : n / 8 * 8;
+}
 
 hipError_t cnn_wgrad(const unsigned short* dYT, const unsigned short* XT, float* part, float* gw, const Geom& g, int Ns,
                      int cin, int cout, hipStream_t st) {
-    const int nlines = wgrad_lines(g, Ns), nchunk = cnn_wgrad_chunks(g, Ns), per = (nlines + nchunk - 1) / nchunk;
+    const int nlines = wgrad_lines(g, Ns), nchunk = cnn_wgrad_chunks(g, Ns);
     const dim3 grid(nchunk, 7);
     switch (Ns) {
-    case 8: hipLaunchKernelGGL(k_conv_wgrad<8>, grid, dim3(256), 0, st, dYT, XT, part, cbg(g, Ns), nlines, per); break;
-    case 16: hipLaunchKernelGGL(k_conv_wgrad<16>, grid, dim3(256), 0, st, dYT, XT, part, cbg(g, Ns), nlines, per); break;
-    case 32: hipLaunchKernelGGL(k_conv_wgrad<32>, grid, dim3(256), 0, st, dYT, XT, part, cbg(g, Ns), nlines, per); break;
+    case 8: hipLaunchKernelGGL(k_conv_wgrad<8>, grid, dim3(256), 0, st, dYT, XT, part, cbg(g, Ns), nlines); break;
+    case 16: hipLaunchKernelGGL(k_conv_wgrad<16>, grid, dim3(256), 0, st, dYT, XT, part, cbg(g, Ns), nlines); break;
+    case 32: hipLaunchKernelGGL(k_conv_wgrad<32>, grid, dim3(256), 0, st, dYT, XT, part, cbg(g, Ns), nlines); break;
     default: return hipErrorInvalidValue;
     }
     hipLaunchKernelGGL(k_wgrad_reduce, dim3((81 * 1024 + 255) / 256), dim3(256), 0, st, part, nchunk, gw, cin, cout);
@@ -597,13 +545,8 @@ hipError_t cnn_rows_to_site(const unsigned short* in, unsigned short* out, int r
     return hipGetLastError();
 }
 
-hipError_t cnn_f32_to_bf16(const float* in, unsigned short* out, size_t n, hipStream_t st) {
-    hipLaunchKernelGGL(k_f32_to_bf16, dim3(grid_for(n)), dim3(256), 0, st, in, out, n);
-    return hipGetLastError();
-}
-
-hipError_t cnn_w_transpose(const float* w, unsigned short* wt, hipStream_t st) {
-    hipLaunchKernelGGL(k_w_transpose, dim3((81 * 1024 + 255) / 256), dim3(256), 0, st, w, wt);
+hipError_t cnn_w_pack(const float* w, unsigned short* wb, unsigned short* wt, hipStream_t st) {
+    hipLaunchKernelGGL(k_w_pack, dim3((81 * 1024 + 255) / 256), dim3(256), 0, st, w, wb, wt);
     return hipGetLastError();
 }
 
@@ -615,7 +558,7 @@ hipError_t cnn_adam(float* p, const float* g, float* m, float* v, size_t n, floa
 
 hipError_t cnn_half_to_rows(const cd* h, unsigned short* X, const Geom& g, int Ns, const double* scale, int inv,
                             hipStream_t st) {
-    hipLaunchKernelGGL(k_half_to_rows, dim3(grid_for((size_t)g.Vh * Ns * 32)), dim3(256), 0, st, h, X, g.Vh, Ns, scale, inv);
+    hipLaunchKernelGGL(k_half_to_rows, dim3(grid_for((size_t)g.Vh * Ns * 4)), dim3(256), 0, st, h, X, g.Vh, Ns, scale, inv);
     return hipGetLastError();
 }
 

@@ -688,8 +688,7 @@ void cnn_alloc(eofa_ctx* ctx) {
 void cnn_refresh(eofa_ctx* ctx) {
     auto& c = ctx->cnn;
     for (int l = 0; l < CNN_LAYERS; l++) {
-        HIPCHK(cnn_f32_to_bf16(c.P + (size_t)l * CNN_LSZ, c.Wb + (size_t)l * CNN_WSZ, CNN_WSZ, ctx->st));
-        HIPCHK(cnn_w_transpose(c.P + (size_t)l * CNN_LSZ, c.Wt + (size_t)l * CNN_WSZ, ctx->st));
+        HIPCHK(cnn_w_pack(c.P + (size_t)l * CNN_LSZ, c.Wb + (size_t)l * CNN_WSZ, c.Wt + (size_t)l * CNN_WSZ, ctx->st));
     }
 }
 
