@@ -1432,11 +1432,9 @@ eofa_status solve_ht_impl(eofa_ctx* ctx, double mp, double mm, const void* b5, v
     auto t0 = std::chrono::steady_clock::now();
     ensure_ws(ctx, needed_bytes(ctx, P));
     Work64 W = carve64(ctx);
-    for (int par = 0; par < 2; par++)
-        HIPCHK(launch_pack5<double>((const cd*)b5, W.c.h[par], ctx->g, par, ctx->Ns, 1, ctx->st));
+    HIPCHK(launch_pack5<double>((const cd*)b5, W.c.h, ctx->g, ctx->Ns, 1, ctx->st));
     SolveOut so = solve_dt(ctx, W, mp, mm, *P);
-    for (int par = 0; par < 2; par++)
-        HIPCHK(launch_unpack5<double>(W.x.h[par], (cd*)x5, ctx->g, par, ctx->Ns, 0, ctx->st));
+    HIPCHK(launch_unpack5<double>(W.x.h, (cd*)x5, ctx->g, ctx->Ns, 0, ctx->st));
     HIPCHK(hipStreamSynchronize(ctx->st));
     collect_timing(ctx);
     fill_info(info, so, std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
@@ -1733,6 +1731,16 @@ std::vector<Sched> sched_candidates(const eofa_ctx* ctx, int prec) {
     return c;
 }
 
+// the odd sites of a canonical 5D field, and back with zeros on the even sites
+void pack_odd(eofa_ctx* ctx, const void* f5, cd* half) {
+    cd* const h[2] = {nullptr, half};
+    HIPCHK(launch_pack5<double>((const cd*)f5, h, ctx->g, ctx->Ns, 0, ctx->st));
+}
+void unpack_odd(eofa_ctx* ctx, const cd* half, void* f5) {
+    const cd* const h[2] = {nullptr, half};
+    HIPCHK(launch_unpack5<double>(h, (cd*)f5, ctx->g, ctx->Ns, 0, ctx->st));
+}
+
 template <typename R> struct ApplyBufs {
     cpx<R>* in[2];
     cpx<R>* out[2];
@@ -1749,7 +1757,11 @@ void apply_op(eofa_ctx* ctx, int op, double mp, double mm, const cd* in, cd* out
     const int Ns = ctx->Ns;
     const size_t nh = ctx->nh;
     auto tab = [&](SiteKind k) { return B.tab[k] ? B.tab[k] : site_tab(ctx, k, mp, mm); };
-    for (int par = 0; par < 2; par++) HIPCHK(launch_pack5<R>(in, B.in[par], ctx->g, par, Ns, 0, ctx->st));
+    const cpx<R>* res[2] = {B.out[0], B.out[1]};  // null: zero
+    // the parity-restricted operators read one half of the input
+    const bool odd_in = op == EOFA_OP_SCHUR || op == EOFA_OP_SCHUR_DAG || op == EOFA_OP_SCHUR_NORMAL || op == EOFA_OP_HOP_EO;
+    cpx<R>* const half_in[2] = {odd_in ? nullptr : B.in[0], op == EOFA_OP_HOP_OE ? nullptr : B.in[1]};
+    HIPCHK(launch_pack5<R>(in, half_in, ctx->g, Ns, 0, ctx->st));
     switch (op) {
     case EOFA_OP_DW:
     case EOFA_OP_HOP:
@@ -1808,13 +1820,13 @@ void apply_op(eofa_ctx* ctx, int op, double mp, double mm, const cd* in, cd* out
         auto h = hop_args<R>(ctx, par);
         h.in = B.in[1 - par]; h.out = B.out[par]; h.cz = 1; h.caux = 0;
         hop<R>(ctx, false, HM_LIN, false, h);
-        HIPCHK(launch_fill0(B.out[1 - par], nh * sizeof(cpx<R>), ctx->st));
+        res[1 - par] = nullptr;
         break;
     }
     default: {  // SCHUR, SCHUR_DAG, SCHUR_NORMAL
         const SiteOp* Ai = tab(SK_AINV);
         const SiteOp* Ad = tab(SK_AINV_DAG);
-        HIPCHK(launch_fill0(B.out[0], nh * sizeof(cpx<R>), ctx->st));
+        res[0] = nullptr;
         const cpx<R>* src = B.in[1];
         if (op != EOFA_OP_SCHUR_DAG) {
             auto a = hop_args<R>(ctx, 0);
@@ -1826,7 +1838,7 @@ void apply_op(eofa_ctx* ctx, int op, double mp, double mm, const cd* in, cd* out
             if (B.partials) { b.red.partials = B.partials; b.red.scal = B.scal; }
             hop<R>(ctx, false, HM_SCHUR_W, true, b);
             if (op == EOFA_OP_SCHUR) {
-                HIPCHK(launch_copy(B.out[1], B.w, nh * sizeof(cpx<R>), ctx->st));
+                res[1] = B.w;
                 break;
             }
             src = B.w;
@@ -1842,8 +1854,7 @@ void apply_op(eofa_ctx* ctx, int op, double mp, double mm, const cd* in, cd* out
     }
     }
     // H_T = gamma_5 R5 D_T reflects in s and flips the lower spins on the way out
-    for (int par = 0; par < 2; par++)
-        HIPCHK(launch_unpack5<R>(B.out[par], out, ctx->g, par, Ns, op == EOFA_OP_HT ? 1 : 0, ctx->st));
+    HIPCHK(launch_unpack5<R>(res, out, ctx->g, Ns, op == EOFA_OP_HT ? 1 : 0, ctx->st));
 }
 
 void check_apply(eofa_ctx* ctx, int op, const void* in, const void* out, int prec) {
@@ -2342,12 +2353,10 @@ eofa_status eofa_solve_ht_batch(eofa_ctx* ctx, int n, const double* m_plus, cons
         const eofa_status st = batch_solve(
             ctx, n, m_plus, m_minus, params, info,
             [&](const Work64& W, int j) {
-                for (int par = 0; par < 2; par++)
-                    HIPCHK(launch_pack5<double>((const cd*)b5[j], W.c.h[par], ctx->g, par, ctx->Ns, 1, ctx->st));
+                HIPCHK(launch_pack5<double>((const cd*)b5[j], W.c.h, ctx->g, ctx->Ns, 1, ctx->st));
             },
             [&](const Work64& W, int j, const SolveOut&) {
-                for (int par = 0; par < 2; par++)
-                    HIPCHK(launch_unpack5<double>(W.x.h[par], (cd*)x5[j], ctx->g, par, ctx->Ns, 0, ctx->st));
+                HIPCHK(launch_unpack5<double>(W.x.h, (cd*)x5[j], ctx->g, ctx->Ns, 0, ctx->st));
             });
         HIPCHK(hipStreamSynchronize(ctx->st));
         return st;
@@ -2653,11 +2662,9 @@ eofa_status eofa_cnn_apply(eofa_ctx* ctx, const void* in5, void* out5) {
         eofa_solve_params P{1e-10, 1, EOFA_FP64, EOFA_PC_NONE, 0, 0, 0};
         ensure_ws(ctx, needed_bytes(ctx, &P));
         Work64 W = carve64(ctx);
-        HIPCHK(launch_pack5<double>((const cd*)in5, W.r, ctx->g, 1, ctx->Ns, 0, ctx->st));
+        pack_odd(ctx, in5, W.r);
         cnn_apply_half(ctx, W.r, W.p);
-        HIPCHK(hipMemsetAsync(W.u, 0, ctx->nh * sizeof(cd), ctx->st));
-        HIPCHK(launch_unpack5<double>(W.u, (cd*)out5, ctx->g, 0, ctx->Ns, 0, ctx->st));
-        HIPCHK(launch_unpack5<double>(W.p, (cd*)out5, ctx->g, 1, ctx->Ns, 0, ctx->st));
+        unpack_odd(ctx, W.p, out5);
         HIPCHK(hipStreamSynchronize(ctx->st));
         return EOFA_OK;
     });
@@ -2672,8 +2679,8 @@ eofa_status eofa_cnn_train_step(eofa_ctx* ctx, const void* rho5, const void* e5,
         eofa_solve_params P{1e-10, 1, EOFA_FP64, EOFA_PC_NONE, 0, 0, 0};
         ensure_ws(ctx, needed_bytes(ctx, &P));
         Work64 W = carve64(ctx);
-        HIPCHK(launch_pack5<double>((const cd*)rho5, W.r, ctx->g, 1, ctx->Ns, 0, ctx->st));
-        HIPCHK(launch_pack5<double>((const cd*)e5, W.p, ctx->g, 1, ctx->Ns, 0, ctx->st));
+        pack_odd(ctx, rho5, W.r);
+        pack_odd(ctx, e5, W.p);
         const double L = cnn_grad(ctx, W.r, W.p);
         if (loss) *loss = L;
         auto& c = ctx->cnn;
@@ -2735,9 +2742,7 @@ eofa_status eofa_training_pairs(eofa_ctx* ctx, double mp, double mm, unsigned lo
             if (k == next && snap < n) {
                 sync_scal(ctx);  // no snapshot of an iterate the device has stopped updating
                 if (ctx->hscal[SC_DONE] != 0.0) break;
-                HIPCHK(hipMemsetAsync(W.res.h[0], 0, nh * sizeof(cd), ctx->st));
-                HIPCHK(launch_unpack5<double>(W.res.h[0], (cd*)e5[snap], ctx->g, 0, ctx->Ns, 0, ctx->st));
-                HIPCHK(launch_unpack5<double>(W.xcg, (cd*)e5[snap], ctx->g, 1, ctx->Ns, 0, ctx->st));
+                unpack_odd(ctx, W.xcg, e5[snap]);
                 snap++;
                 next *= 2;
             }
@@ -2748,13 +2753,12 @@ eofa_status eofa_training_pairs(eofa_ctx* ctx, double mp, double mm, unsigned lo
         }
         // e_i = x* - x_i ; rho_i = Dhat^dag Dhat e_i
         for (int i = 0; i < snap; i++) {
-            HIPCHK(launch_pack5<double>((const cd*)e5[i], W.c.h[1], ctx->g, 1, ctx->Ns, 0, ctx->st));
+            pack_odd(ctx, e5[i], W.c.h[1]);
             HIPCHK(launch_axpby<double>(1.0, W.xcg, -1.0, W.c.h[1], nh, nullptr, ctx->st));
             schur64(ctx, W, Ai, Ad, W.c.h[1], W.w);
             schur_dag64(ctx, W, Ad, W.w, W.p);
-            HIPCHK(launch_unpack5<double>(W.c.h[1], (cd*)e5[i], ctx->g, 1, ctx->Ns, 0, ctx->st));
-            HIPCHK(launch_unpack5<double>(W.res.h[0], (cd*)rho5[i], ctx->g, 0, ctx->Ns, 0, ctx->st));
-            HIPCHK(launch_unpack5<double>(W.p, (cd*)rho5[i], ctx->g, 1, ctx->Ns, 0, ctx->st));
+            unpack_odd(ctx, W.c.h[1], e5[i]);
+            unpack_odd(ctx, W.p, rho5[i]);
         }
         HIPCHK(hipStreamSynchronize(ctx->st));
         *made = snap;

@@ -141,8 +141,7 @@ hipError_t launch_hb_combine(const cd* eta, cd* phi, const HbTerms& t, size_t n,
                              const Red& red, hipStream_t st);
 // dst[i] = host_vals[i] for any n, in chunks of 64 values travelling as kernel arguments
 hipError_t launch_set_block(double* dst, size_t n, const double* host_vals, hipStream_t st);
-// bytes (a multiple of 8) of dst set to zero / copied from src, by kernels
-hipError_t launch_fill0(void* dst, size_t bytes, hipStream_t st);
+// bytes (a multiple of 8) copied from src to dst by a kernel
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t st);
 // sets S[s_i] = v_i for the slots s_i >= 0 (stream-ordered, no host buffer)
 hipError_t launch_scal_set(double* S, int s0, double v0, int s1, double v1, int s2, double v2, hipStream_t st);
@@ -150,9 +149,10 @@ hipError_t launch_scal_set(double* S, int s0, double v0, int s1, double v1, int 
 hipError_t launch_scal_arm(double* S, double rr, double rr0, double tol2, hipStream_t st);
 // xhi += xlo (first: xhi = xlo), then xlo = 0
 hipError_t launch_accum_f(cd* xhi, cpx<float>* xlo, size_t n, bool first, hipStream_t st);
-template <typename R> hipError_t launch_pack5(const cd* canon, cpx<R>* half, const Geom& g, int par, int Ns, int refl,
+// canonical 5D field -> half[par] (null: that parity is left out) and back (null: zeros)
+template <typename R> hipError_t launch_pack5(const cd* canon, cpx<R>* const half[2], const Geom& g, int Ns, int refl,
                                               hipStream_t st);
-template <typename R> hipError_t launch_unpack5(const cpx<R>* half, cd* canon, const Geom& g, int par, int Ns, int refl,
+template <typename R> hipError_t launch_unpack5(const cpx<R>* const half[2], cd* canon, const Geom& g, int Ns, int refl,
                                                 hipStream_t st);
 // D[par], F[par]: the FP64 and FP32 links of parity par
 hipError_t launch_pack_links(const cd* U, cd* const D[2], cpx<float>* const F[2], const Geom& g, double tbc,
