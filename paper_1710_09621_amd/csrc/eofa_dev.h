@@ -135,19 +135,44 @@ __device__ __forceinline__ void siteop_store(SiteOpL<NS>& d, const SiteOpShare<N
     }
 }
 
+// v_j += c o_j, o_j = the component held by the lane (s + OFF) mod NS of this group, for NC complex components.
+// FP32 at Ns = 16: the rotation is an operand of the multiply-add (v_fmac_f32 with row_ror), which the compiler does
+// not form by itself: half the instructions of a move and an FMA, same bits.  The two wait states that a DPP operand
+// needs after a VALU write of its register are in the block, before the first and after the last of them, since the
+// compiler does not look into it; within the block every instruction has its own register.
+#define EOFA_ROR(I) "v_fmac_f32_dpp %" #I ", %" #I ", %[c] row_ror:%[n] row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+template <int NS, int OFF, int NC, typename R>
+__device__ __forceinline__ void add_rotated(cpx<R> v[NC], R c, int lane) {
+    if constexpr (NS == 16 && sizeof(R) == 4 && (NC == 6 || NC == 3)) {
+        constexpr int n = ((16 - OFF) % 16 + 16) % 16;
+        static_assert(n != 0, "zero rotation");
+        if constexpr (NC == 6)
+            asm("s_nop 1\n\t" EOFA_ROR(0) EOFA_ROR(1) EOFA_ROR(2) EOFA_ROR(3) EOFA_ROR(4) EOFA_ROR(5) EOFA_ROR(6)
+                EOFA_ROR(7) EOFA_ROR(8) EOFA_ROR(9) EOFA_ROR(10) EOFA_ROR(11) "s_nop 1"
+                : "+&v"(v[0].x), "+&v"(v[0].y), "+&v"(v[1].x), "+&v"(v[1].y), "+&v"(v[2].x), "+&v"(v[2].y),
+                  "+&v"(v[3].x), "+&v"(v[3].y), "+&v"(v[4].x), "+&v"(v[4].y), "+&v"(v[5].x), "+&v"(v[5].y)
+                : [c] "v"(c), [n] "n"(n));
+        else
+            asm("s_nop 1\n\t" EOFA_ROR(0) EOFA_ROR(1) EOFA_ROR(2) EOFA_ROR(3) EOFA_ROR(4) EOFA_ROR(5) "s_nop 1"
+                : "+&v"(v[0].x), "+&v"(v[0].y), "+&v"(v[1].x), "+&v"(v[1].y), "+&v"(v[2].x), "+&v"(v[2].y)
+                : [c] "v"(c), [n] "n"(n));
+    } else {
+#pragma unroll
+        for (int j = 0; j < NC; j++) {
+            const cpx<R> o = lane_from_c<NS, OFF>(v[j], lane);
+            v[j].x = fma(c, o.x, v[j].x);
+            v[j].y = fma(c, o.y, v[j].y);
+        }
+    }
+}
+#undef EOFA_ROR
+
 // NC: the number of colour-spin components of the chirality half held by this lane (6, or 3 when the two
 // spins of a half sit in two lanes); every component is transformed independently.
 template <int NS, int SIG, int K, int NC = 6, typename R, typename T>
 __device__ __forceinline__ void ring_scan_step(cpx<R> v[NC], const T& t, int s, int lane) {
     if constexpr (K < ilog2(NS)) {
-        const R qk = (R)t.q[K][s];
-        constexpr int OFF = SIG * (1 << K);
-#pragma unroll
-        for (int j = 0; j < NC; j++) {
-            cpx<R> o = lane_from_c<NS, OFF>(v[j], lane);
-            v[j].x = fma(qk, o.x, v[j].x);
-            v[j].y = fma(qk, o.y, v[j].y);
-        }
+        add_rotated<NS, SIG * (1 << K), NC>(v, (R)t.q[K][s], lane);
         ring_scan_step<NS, SIG, K + 1, NC>(v, t, s, lane);
     }
 }
@@ -160,24 +185,16 @@ __device__ __forceinline__ void chir_op(cpx<R> v[NC], const T& t, int s, int lan
     for (int j = 0; j < NC; j++) v[j] = cscale(pre, v[j]);
     if constexpr (ORDER == 0) {
         ring_scan_step<NS, SIG, 0, NC>(v, t, s, lane);
-#pragma unroll
-        for (int j = 0; j < NC; j++) {
-            cpx<R> o = lane_from_c<NS, SIG>(v[j], lane);
-            v[j].x = post * fma(shf, o.x, v[j].x);
-            v[j].y = post * fma(shf, o.y, v[j].y);
-        }
+        add_rotated<NS, SIG, NC>(v, shf, lane);
     } else {
         const R mid = (R)t.mid[s];
+        add_rotated<NS, SIG, NC>(v, shf, lane);
 #pragma unroll
-        for (int j = 0; j < NC; j++) {
-            cpx<R> o = lane_from_c<NS, SIG>(v[j], lane);
-            v[j].x = mid * fma(shf, o.x, v[j].x);
-            v[j].y = mid * fma(shf, o.y, v[j].y);
-        }
+        for (int j = 0; j < NC; j++) v[j] = cscale(mid, v[j]);
         ring_scan_step<NS, SIG, 0, NC>(v, t, s, lane);
-#pragma unroll
-        for (int j = 0; j < NC; j++) v[j] = cscale(post, v[j]);
     }
+#pragma unroll
+    for (int j = 0; j < NC; j++) v[j] = cscale(post, v[j]);
 }
 
 // Apply a site-local operator to a 12-component spinor held lane-wise over s.

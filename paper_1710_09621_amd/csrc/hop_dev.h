@@ -97,6 +97,42 @@ __device__ __forceinline__ float load_h_raw(cpx<float> p[12], const void* __rest
     return h_norms<NS>(f, Vh)[cb * NS + s];
 }
 
+// An FP16 column as loaded: component j is the pair v[j / 4][2 (j % 4)], v[j / 4][2 (j % 4) + 1], times n.
+struct HCol { h8_t v[3]; float n; };
+template <int NS> __device__ __forceinline__ void load_h_col(HCol& c, const void* __restrict__ f, size_t cb, int s, int Vh) {
+    const size_t i = cb * 3 * NS + s;  // one 64-bit offset per column, the same for every field
+#pragma unroll
+    for (int jb = 0; jb < 3; jb++) c.v[jb] = ((const h8_t*)f)[i + jb * NS];
+    const size_t k = cb * NS + s;
+    c.n = h_norms<NS>(f, Vh)[k];
+}
+
+// project() straight from the binary16 values: a + b as fma(a, 1, b), which the compiler turns into one
+// v_fma_mix_f32 on both halves' bits instead of two conversions and an add (the product with 1 is exact, so these are
+// the bits of the widened sum).  one: 1.0 in a register that the compiler cannot fold.
+// The FP16 hop is bound by vector instructions.  With this and the rotations as operands (add_rotated) at 16^3 x 32,
+// Ns = 16, two systems: HM_SITE 100 -> 88 us, HM_SCHUR_W 138 -> 120 us, HM_SCHUR_Q 133 -> 129 us (memory).
+template <int MU, int S>
+__device__ __forceinline__ void project_hcol(const HCol& c, float one, cpx<float> h[6]) {
+    // h_up[k] = up[k] + S (B dn)[k]; the real and imaginary parts of B dn are +- those of one lower component
+    auto f = [&](int j, int im) { return (float)c.v[j / 4][2 * (j % 4) + im]; };
+    auto add = [&](float a, float b, bool neg) { return __builtin_fmaf(neg ? -b : b, one, a); };
+#pragma unroll
+    for (int k = 0; k < 6; k++) {
+        const int dn = 6 + ((MU < 2) ? (k + 3) % 6 : k);  // lower component that meets upper component k
+        const bool second = k >= 3;
+        if constexpr (MU == 0 || MU == 2) {  // -i dn (both; mu = z: +i on the second spin)
+            const bool mi = MU == 0 || !second;  // factor -i, else +i
+            h[k].x = add(f(k, 0), f(dn, 1), (S > 0) != mi);
+            h[k].y = add(f(k, 1), f(dn, 0), (S > 0) == mi);
+        } else {  // mu = y: -dn on the first spin, +dn on the second; mu = t: +dn
+            const bool pl = MU == 3 || second;
+            h[k].x = add(f(k, 0), f(dn, 0), (S > 0) != pl);
+            h[k].y = add(f(k, 1), f(dn, 1), (S > 0) != pl);
+        }
+    }
+}
+
 // reconstruct() of n w: the column norm of an FP16 neighbour folded into the accumulation (one FMA per real
 // instead of a multiply on every loaded component and an add)
 template <int MU, int S, typename R>

@@ -23,6 +23,23 @@ namespace eofa {
 // to the top (which spills at 256 VGPRs in FP64).
 #define HOP_FENCE() __builtin_amdgcn_sched_barrier(0)
 
+// h = the projected column of the input site cbi; H: without the column's norm, which goes to n
+template <int NS, int MU, int S, bool H, typename R>
+__device__ __forceinline__ void hop_h(cpx<R> h[6], R& n, const cpx<R>* __restrict__ in, int cbi, int s, int Vh) {
+    if constexpr (H) {
+        HCol c;
+        load_h_col<NS>(c, in, (size_t)cbi, s, Vh);
+        float one = 1.0f;
+        asm("" : "+s"(one));
+        project_hcol<MU, S>(c, one, h);
+        n = c.n;
+    } else {
+        cpx<R> p[12];
+        load_col<NS, false>(p, in, (size_t)cbi, s, 0);
+        project<MU, S>(p, h);
+    }
+}
+
 // One direction mu of the hop: forward (1 - S gamma) U in(x+mu) and backward (1 + S gamma) U^dag in(x-mu).
 // Uf / Ub point at the 9 complex entries of U_mu(x) and U_mu(x-mu) (global memory or LDS).  FP16 columns (H)
 // are projected and multiplied unscaled; their norm enters in the accumulation.
@@ -32,12 +49,9 @@ __device__ __forceinline__ void hop_mu(cpx<R> acc[12], const cpx<R>* __restrict_
     constexpr int SF = DAG ? +1 : -1;
     constexpr int SB = -SF;
     {
-        cpx<R> p[12];
-        R n = 1;
-        if constexpr (H) n = load_h_raw<NS>(p, in, (size_t)nb[2 * MU], s, Vh);
-        else load_col<NS, H>(p, in, (size_t)nb[2 * MU], s, Vh);
         cpx<R> h[6], w[6], U[9];
-        project<MU, SF>(p, h);
+        R n = 1;
+        hop_h<NS, MU, SF, H>(h, n, in, nb[2 * MU], s, Vh);
 #pragma unroll
         for (int k = 0; k < 9; k++) U[k] = Uf[k];
         link_mul<false>(U, h, w);
@@ -45,12 +59,9 @@ __device__ __forceinline__ void hop_mu(cpx<R> acc[12], const cpx<R>* __restrict_
         else reconstruct<MU, SF>(acc, w);
     }
     {
-        cpx<R> p[12];
-        R n = 1;
-        if constexpr (H) n = load_h_raw<NS>(p, in, (size_t)nb[2 * MU + 1], s, Vh);
-        else load_col<NS, H>(p, in, (size_t)nb[2 * MU + 1], s, Vh);
         cpx<R> h[6], w[6], U[9];
-        project<MU, SB>(p, h);
+        R n = 1;
+        hop_h<NS, MU, SB, H>(h, n, in, nb[2 * MU + 1], s, Vh);
 #pragma unroll
         for (int k = 0; k < 9; k++) U[k] = Ub[k];
         link_mul<true>(U, h, w);
