@@ -402,6 +402,7 @@ void cg_iteration(eofa_ctx* ctx, cpx<R>* x, cpx<R>* r, cpx<R>* p, cpx<R>* u, cpx
                   const SiteOp* Ai, const SiteOp* Ad) {
     const int k0 = sizeof(R) == 8 ? 0 : -EOFA_NKERN;  // kernel classes are timed in FP64 only
     const double* done = ctx->scal + SC_DONE;
+    XpFin fin{};
     {
         auto a = hop_args<R>(ctx, 0);
         a.in = p; a.out = u; a.opA = Ai; a.cz = 1; a.caux = 0; a.done = done;
@@ -423,9 +424,12 @@ void cg_iteration(eofa_ctx* ctx, cpx<R>* x, cpx<R>* r, cpx<R>* p, cpx<R>* u, cpx
         auto a = hop_args<R>(ctx, 1);
         a.in = at; a.out = r; a.aux = w; a.aux2 = r; a.cz = (R)-0.25; a.caux = 1;
         a.red = red_of(ctx, 0, EPI_CG_R); a.done = done;
+        fin.partials = a.red.partials;
+        fin.n = xp_finishes(hop_partials(ctx->g, ctx->Ns, a.sc, 1), (size_t)ctx->g.Vh * ctx->Ns, sizeof(R), false);
+        a.defer = fin.n > 0;
         hop<R>(ctx, true, HM_SCHUR_Q, true, a, k0 + EOFA_K_SCHUR_Q);
     }
-    timed(ctx, k0 + EOFA_K_XP, [&] { HIPCHK(launch_cg_xp<R>(x, p, r, ctx->scal, ctx->nh, ctx->st)); });
+    timed(ctx, k0 + EOFA_K_XP, [&] { HIPCHK(launch_cg_xp<R>(x, p, r, ctx->scal, ctx->nh, fin, ctx->st)); });
 }
 
 // Most iterations between host checks when the caller leaves it to the library (check_every = 0); it also is the
@@ -434,7 +438,7 @@ constexpr int kAutoCheckEvery = 16;
 
 // Length of the blocks of iterations between host checks.  A given check_every is taken as it is.  Otherwise a block
 // ends where the residual is expected to reach its target by the rate measured so far (in CG iterations per factor e
-// of |r|^2): iterations past the target exit at once on the device, but each still costs its six launches, and a
+// of |r|^2): iterations past the target exit at once on the device, but each still costs its launches, and a
 // reliable-update cycle (a factor 10 in |r|) is shorter than 16 iterations on small lattices, where 44% of the
 // iterations launched in blocks of 16 were such idle ones (trajectory on 8^4, FP16 columns: 313 ms with blocks of 16, 251 ms).
 // Captured blocks come in multiples of 4, so that at most four graphs are kept per set of buffers.
@@ -1055,6 +1059,8 @@ template <typename R> HopArgsMR<R> mr_args(eofa_ctx* ctx, int par, int nr, bool 
 template <typename R, bool H = false> void cg_iteration_mr(eofa_ctx* ctx, std::vector<Sys>& sys) {
     const int nr = (int)sys.size();
     auto V = [](void* p) { return (cpx<R>*)p; };
+    const unsigned np = hop_mr_partials(ctx->g, ctx->Ns, nr);
+    const XpFin fin{ctx->partials_mr, ctx->pstride, xp_finishes(np, (size_t)ctx->g.Vh * ctx->Ns, sizeof(R), H)};
     {
         auto a = mr_args<R>(ctx, 0, nr, H);
         for (int r = 0; r < nr; r++) { a.in[r] = V(sys[r].p); a.out[r] = V(sys[r].u); a.opA[r] = sys[r].Ai; }
@@ -1072,7 +1078,7 @@ template <typename R, bool H = false> void cg_iteration_mr(eofa_ctx* ctx, std::v
     }
     {
         auto a = mr_args<R>(ctx, 0, nr, H);
-        a.fin_partials = a.partials; a.fin_n = hop_mr_partials(ctx->g, ctx->Ns, nr); a.fin_epi = EPI_CG_W;
+        a.fin_partials = a.partials; a.fin_n = np; a.fin_epi = EPI_CG_W;
         for (int r = 0; r < nr; r++) { a.in[r] = V(sys[r].wt); a.out[r] = V(sys[r].at); a.opA[r] = sys[r].Ad; }
         a.cz = 1; a.caux = 0;
         HIPCHK(launch_hop_mr<R>(ctx->Ns, true, HM_SITE, a, ctx->st, H));
@@ -1082,7 +1088,7 @@ template <typename R, bool H = false> void cg_iteration_mr(eofa_ctx* ctx, std::v
         for (int r = 0; r < nr; r++) {
             a.in[r] = V(sys[r].at); a.out[r] = V(sys[r].r); a.aux[r] = V(sys[r].w); a.aux2[r] = V(sys[r].r);
         }
-        a.cz = (R)-0.25; a.caux = 1; a.epi = EPI_CG_R;
+        a.cz = (R)-0.25; a.caux = 1; a.epi = EPI_CG_R; a.defer = fin.n > 0;
         HIPCHK(launch_hop_mr<R>(ctx->Ns, true, HM_SCHUR_Q, a, ctx->st, H));
     }
     cpx<R>* xs[NRMAX];
@@ -1093,9 +1099,9 @@ template <typename R, bool H = false> void cg_iteration_mr(eofa_ctx* ctx, std::v
         void* ph[NRMAX];
         for (int r = 0; r < nr; r++) ph[r] = sys[r].p;
         HIPCHK(launch_cg_xp_mr_h(ctx->Ns, nr, (cpx<float>* const*)xs, ph, (cpx<float>* const*)rs, ctx->scal + BATCH_OFF,
-                                 ctx->g.Vh, ctx->st));
+                                 ctx->g.Vh, fin, ctx->st));
     } else {
-        HIPCHK(launch_cg_xp_mr<R>(nr, xs, ps, rs, ctx->scal + BATCH_OFF, ctx->nh, ctx->st));
+        HIPCHK(launch_cg_xp_mr<R>(nr, xs, ps, rs, ctx->scal + BATCH_OFF, ctx->nh, fin, ctx->st));
     }
 }
 

@@ -333,9 +333,10 @@ enum : int {
     SC_RR0 = 4,     // |r_0|^2 (stop reference)
     SC_DONE = 5,    // 1 when converged (read by graph replays)
     SC_TOL2 = 6,    // stop threshold on |r|^2 / |r_0|^2
-    SC_DONEX = 7,   // SC_DONE as it was before the last residual reduction: the x/p update that follows is skipped
+    SC_DONEX = 7,   // SC_DONE at the start of this iteration (set with alpha): its x/p update is skipped
     SC_TMP = 8,     // 8..29 free slots for norms
     SC_ITERS = 30,  // CG iterations applied since the counter was cleared (counted on the device)
+    SC_RRK = 31,    // SC_RR at the start of this iteration (set with alpha)
     SC_N = 32
 };
 enum : int { EPI_STORE = 0, EPI_CG_W = 1, EPI_CG_R = 2, EPI_CG_INIT = 3 };
@@ -345,9 +346,8 @@ __device__ __forceinline__ void finish_sum(const Red& rd, double bsum) {
     if (threadIdx.x == 0) rd.partials[blockIdx.x] = bsum;
 }
 
-// Sum partials[0..n) in a fixed order (256 threads) and apply the epilogue.
-__device__ __forceinline__ void finish_partials(const double* partials, unsigned n, double* S, int slot, int epi) {
-    __shared__ double lds[4];
+// Sum of partials[0..n) in a fixed order (256 threads; valid in every thread).
+__device__ __forceinline__ double sum_partials(const double* partials, unsigned n, double* lds4) {
     // 8 independent loads in flight per thread; the summation order is fixed
     double a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     unsigned i = threadIdx.x;
@@ -355,22 +355,33 @@ __device__ __forceinline__ void finish_partials(const double* partials, unsigned
 #pragma unroll
         for (int k = 0; k < 8; k++) a[k] += partials[i + k * 256];
     for (; i < n; i += 256) a[0] += partials[i];
-    double s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-    s = block_sum256(s, lds);
+    const double s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+    return block_sum256(s, lds4);
+}
+
+// One thread, end of a running CG's iteration: s = |r_new|^2.
+__device__ __forceinline__ void cg_new_residual(double* S, double s) {
+    S[SC_ITERS] += 1.0;
+    S[SC_BETA] = s / S[SC_RRK];
+    S[SC_RR] = s;
+    if (s <= S[SC_TOL2] * S[SC_RR0]) S[SC_DONE] = 1.0;
+}
+
+// Sum the partials and apply the epilogue (256 threads).
+__device__ __forceinline__ void finish_partials(const double* partials, unsigned n, double* S, int slot, int epi) {
+    __shared__ double lds[4];
+    const double s = sum_partials(partials, n, lds);
     if (threadIdx.x == 0) {
         switch (epi) {
         case EPI_CG_W:          // s = |Dhat p|^2 (after convergence the hops were skipped: keep the scalars)
+            S[SC_DONEX] = S[SC_DONE];
             if (S[SC_DONE] != 0.0) break;
+            S[SC_RRK] = S[SC_RR];
             S[SC_WW] = s;
             S[SC_ALPHA] = S[SC_RR] / s;
             break;
         case EPI_CG_R:          // s = |r_new|^2; the x/p update that follows belongs to this iteration
-            S[SC_DONEX] = S[SC_DONE];
-            if (S[SC_DONE] != 0.0) break;
-            S[SC_ITERS] += 1.0;
-            S[SC_BETA] = s / S[SC_RR];
-            S[SC_RR] = s;
-            if (s <= S[SC_TOL2] * S[SC_RR0]) S[SC_DONE] = 1.0;
+            if (S[SC_DONE] == 0.0) cg_new_residual(S, s);
             break;
         case EPI_CG_INIT:       // s = |r_0|^2
             S[SC_RR] = s;

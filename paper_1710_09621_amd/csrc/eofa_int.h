@@ -87,6 +87,15 @@ template <typename R> struct HopArgsMR {
 // half: FP16-column Krylov fields (R = float; see load_h / store_h in kernels.hip)
 template <typename R> hipError_t launch_hop_mr(int Ns, bool dag, int mode, const HopArgsMR<R>& a, hipStream_t st,
                                                bool half = false);
+// The residual's partial sums (n > 0 of system r at partials + r pstride) that the x/p update finishes itself: every
+// workgroup adds them up for its beta, the first one writes the scalars.  n = 0: they are finished already.
+struct XpFin {
+    const double* partials;
+    int pstride;
+    unsigned n;
+};
+// n, the partial sums of a system, if an x/p update of Vh Ns lanes is to finish them, else 0
+unsigned xp_finishes(unsigned n, size_t lanes, size_t real_bytes, bool half);
 // Partial sums that a reducing launch of nr systems writes per system (for fin_n).
 unsigned hop_partials(const Geom& g, int Ns, const Sched& sc, int nr);
 unsigned hop_mr_partials(const Geom& g, int Ns, int nr);
@@ -100,12 +109,12 @@ template <typename R> hipError_t launch_hop_split(int Ns, bool dag, int mode, bo
 inline size_t half_field_bytes_h(const Geom& g, int Ns) { return (size_t)g.Vh * Ns * (12 * 4 + 4); }
 // x_r (FP32) += alpha_r p_r ; p_r (FP16 columns) = r_r (FP32) + beta_r p_r unless SC_DONEX is set
 hipError_t launch_cg_xp_mr_h(int Ns, int nr, cpx<float>* const* x, void* const* p, cpx<float>* const* r, double* scal,
-                             int Vh, hipStream_t st);
+                             int Vh, const XpFin& fin, hipStream_t st);
 hipError_t launch_f2h(int Ns, const cpx<float>* in, void* out, int Vh, hipStream_t st);
 hipError_t launch_h2d(int Ns, const void* in, cd* out, int Vh, hipStream_t st);
 // x_r += alpha_r p_r ; p_r = r_r + beta_r p_r for the systems whose SC_DONEX is clear
 template <typename R> hipError_t launch_cg_xp_mr(int nr, cpx<R>* const* x, cpx<R>* const* p, cpx<R>* const* r,
-                                                 double* scal, size_t n, hipStream_t st);
+                                                 double* scal, size_t n, const XpFin& fin, hipStream_t st);
 
 template <typename R> hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& a, hipStream_t st);
 int tw_grid(const Geom& g, int Ns, const Sched& sc);
@@ -115,7 +124,7 @@ template <typename R> hipError_t launch_site(int Ns, bool dag, const cpx<R>* in,
                                              hipStream_t st);
 // x += alpha p ; p = r + beta p unless scal[SC_DONEX] is set
 template <typename R> hipError_t launch_cg_xp(cpx<R>* x, cpx<R>* p, const cpx<R>* r, double* scal, size_t n,
-                                              hipStream_t st);
+                                              const XpFin& fin, hipStream_t st);
 template <typename R> hipError_t launch_axpby(R a, const cpx<R>* x, R b, cpx<R>* y, size_t n, const Red* red,
                                               hipStream_t st);
 template <typename R> hipError_t launch_norm2(const cpx<R>* x, size_t n, const Red& red, hipStream_t st);

@@ -272,8 +272,15 @@ __device__ __forceinline__ void ops_store(SiteOpL<NS>& sA, SiteOpL<NS>& sB, cons
 
 template <int NS, bool DAG, int MODE, bool RED, typename R>
 __global__ __launch_bounds__(256, HOP_WAVES) void k_hop(const HopArgs<R> a) {
+    if constexpr (MODE == HM_SITE && DAG && !RED) {
+        if (a.fin_n && blockIdx.x == gridDim.x - 1) {  // the pending reduction of an earlier launch
+            finish_partials(a.fin.partials, a.fin_n, a.fin.scal, a.fin.slot, a.fin.epi);
+            return;
+        }
+    }
     if (a.done && *a.done != 0.0) return;
-    const int tid = tile_of(blockIdx.x, gridDim.x, a.sc, a.g) * 256 + threadIdx.x;
+    const int fin = MODE == HM_SITE && DAG && a.fin_n;  // that workgroup is not part of the order
+    const int tid = tile_of(blockIdx.x, gridDim.x - fin, a.sc, a.g) * 256 + threadIdx.x;
     const int lane = threadIdx.x & 63;
     const int s = lane & (NS - 1);
     int cb = tid / NS;
@@ -790,7 +797,15 @@ __global__ __launch_bounds__(512, 1) void k_hop_tws(const HopArgs<R> a) {
 // the residual (aux2 and the output of HM_SCHUR_Q) stays FP32.
 template <int NS, bool DAG, int MODE, typename R, bool H>
 __global__ __launch_bounds__(256, HOP_WAVES) void k_hop_mr(const HopArgsMR<R> a) {
-    const int tid = tile_of(blockIdx.x, gridDim.x, a.sc, a.g) * 256 + threadIdx.x;
+    if constexpr (MODE == HM_SITE && DAG) {
+        if (a.fin_n && blockIdx.x == gridDim.x - 1) {  // the pending reductions of an earlier launch
+            for (int r = blockIdx.y * a.rpb; r < min(a.nr, (int)(blockIdx.y + 1) * a.rpb); r++)
+                finish_partials(a.fin_partials + (size_t)r * a.pstride, a.fin_n, a.scal + r * SC_N, 0, a.fin_epi);
+            return;
+        }
+    }
+    const int fin = MODE == HM_SITE && DAG && a.fin_n;  // that workgroup is not part of the order
+    const int tid = tile_of(blockIdx.x, gridDim.x - fin, a.sc, a.g) * 256 + threadIdx.x;
     const int lane = threadIdx.x & 63;
     const int s = lane & (NS - 1);
     int cb = tid / NS;
@@ -879,7 +894,7 @@ __global__ __launch_bounds__(256) void k_finish_mr(const double* __restrict__ pa
                                                    double* scal, int epi) {
     double* S = scal + blockIdx.x * SC_N;
     if (S[SC_DONE] != 0.0) {
-        if (epi == EPI_CG_R && threadIdx.x == 0) S[SC_DONEX] = 1.0;
+        if (epi == EPI_CG_W && threadIdx.x == 0) S[SC_DONEX] = 1.0;
         return;
     }
     finish_partials(partials + (size_t)blockIdx.x * pstride, n, S, 0, epi);
@@ -903,10 +918,34 @@ template <bool NT, typename R> __device__ __forceinline__ void xp_st(cpx<R>* q, 
         *q = v;
     }
 }
-template <typename R, bool NT>
+// alpha and beta of the system whose scalars are S; false: its update is skipped.  With n > 0 the workgroup finishes
+// the residual's reduction itself (in the order of k_finish): on small fields the one-workgroup launch in between cost
+// as much as half of this update.  With |w|^2 finished by one more workgroup of the following hop: trajectory on 8^4
+// 249 -> 241 ms, a solve on 12x6x10x8 at Ns = 32 in FP32 17.75 -> 16.95 ms, two on 4^4 in FP64 5.6 -> 5.2 ms.
+// Only one workgroup writes S, and only entries that none reads here.
+// The sum comes before the loads of the fields: loads in flight across it double the registers (heatbath 8^3 x 16: 47.2
+// instead of 46.7 ms) and gain 1% where the launch fits on the chip at once.
+template <bool FIN>
+__device__ __forceinline__ bool xp_scalars(double* S, const double* partials, unsigned n, double& alpha, double& beta) {
+    const bool go = S[SC_DONEX] == 0.0;
+    alpha = S[SC_ALPHA];
+    if constexpr (!FIN) {
+        beta = S[SC_BETA];
+    } else {
+        __shared__ double lds[4];
+        const double rrk = S[SC_RRK], s = sum_partials(partials, n, lds);
+        beta = s / rrk;
+        if (go && blockIdx.x == 0 && threadIdx.x == 0) cg_new_residual(S, s);
+    }
+    return go;
+}
+template <typename R, bool NT, bool FIN>
 __device__ __forceinline__ void xp_chunk(cpx<R>* __restrict__ x, cpx<R>* __restrict__ p, const cpx<R>* __restrict__ r,
-                                         R alpha, R beta, size_t n) {
+                                         double* S, const double* partials, unsigned np, size_t n) {
     constexpr int U = xp_unroll<R>();
+    double al, be;
+    if (!xp_scalars<FIN>(S, partials, np, al, be)) return;
+    const R alpha = (R)al, beta = (R)be;
     const size_t i0 = (size_t)blockIdx.x * (256 * U) + threadIdx.x;
     cpx<R> pp[U], rr[U], xx[U];
 #pragma unroll
@@ -939,23 +978,21 @@ template <typename R> struct XpArgs {
     cpx<R>* r[NRMAX];
 };
 
-template <typename R, bool NT>
-__global__ __launch_bounds__(256) void k_cg_xp_mr(const XpArgs<R> a, double* scal, size_t n) {
+template <typename R, bool NT, bool FIN>
+__global__ __launch_bounds__(256) void k_cg_xp_mr(const XpArgs<R> a, double* scal, size_t n, const XpFin f) {
     const int r = blockIdx.y;
-    const double* S = scal + r * SC_N;
-    if (S[SC_DONEX] != 0.0) return;
-    xp_chunk<R, NT>(a.x[r], a.p[r], a.r[r], (R)S[SC_ALPHA], (R)S[SC_BETA], n);
+    xp_chunk<R, NT, FIN>(a.x[r], a.p[r], a.r[r], scal + r * SC_N, f.partials + (size_t)r * f.pstride, f.n, n);
 }
 
 // FP16 form: x (FP32) += alpha p ; p (FP16 columns) = r (FP32) + beta p; one thread per (cb, s).  The stores
 // are nontemporal; NT: the loads too (fields above the Infinity Cache, as in xp_chunk).
-template <int NS, bool NT>
-__global__ __launch_bounds__(256) void k_cg_xp_mr_h(const XpArgs<float> a, double* scal, int Vh) {
+template <int NS, bool NT, bool FIN>
+__global__ __launch_bounds__(256) void k_cg_xp_mr_h(const XpArgs<float> a, double* scal, int Vh, const XpFin f) {
     const int r = blockIdx.y;
-    const double* S = scal + r * SC_N;
-    if (S[SC_DONEX] != 0.0) return;
-    const float alpha = (float)S[SC_ALPHA], beta = (float)S[SC_BETA];
     const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;  // one (cb, s) column per thread, no loop
+    double al, be;
+    if (!xp_scalars<FIN>(scal + r * SC_N, f.partials + (size_t)r * f.pstride, f.n, al, be)) return;
+    const float alpha = (float)al, beta = (float)be;
     if (t < (size_t)Vh * NS) {
         const size_t cb = t / NS;
         const int s = (int)(t % NS);
@@ -1023,12 +1060,10 @@ __global__ __launch_bounds__(256) void k_site(const cpx<R>* __restrict__ in, cpx
 // ===================================================================== BLAS-1
 // CG step after the residual update: x += alpha p ; p = r + beta p   (alpha, beta on device; skipped once
 // the update of the converging iteration has been applied)
-template <typename R, bool NT>
+template <typename R, bool NT, bool FIN>
 __global__ __launch_bounds__(256) void k_cg_xp(cpx<R>* __restrict__ x, cpx<R>* __restrict__ p,
-                                               const cpx<R>* __restrict__ r, const double* __restrict__ scal,
-                                               size_t n) {
-    if (scal[SC_DONEX] != 0.0) return;
-    xp_chunk<R, NT>(x, p, r, (R)scal[SC_ALPHA], (R)scal[SC_BETA], n);
+                                               const cpx<R>* __restrict__ r, double* scal, size_t n, const XpFin f) {
+    xp_chunk<R, NT, FIN>(x, p, r, scal, f.partials, f.n, n);
 }
 
 // y = a*x + b*y, with an optional |y|^2 reduction
@@ -1487,7 +1522,8 @@ template <typename K> static size_t lds_room(K kern) {
 }
 
 template <typename R>
-hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& a, hipStream_t st) {
+hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& args, hipStream_t st) {
+    HopArgs<R> a = args;
     const size_t nthreads = (size_t)a.g.Vh * Ns;
     const bool tw = a.sc.mode == 3 || a.sc.mode == 5 || a.sc.mode == 6;
     const bool reduces = red || mode == HM_SCHUR_W || mode == HM_SCHUR_Q;
@@ -1504,9 +1540,15 @@ hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& a,
         if (reduces && !a.defer) finish(a.red, (unsigned)hop_split_blocks(a.g, Ns), st);
         return hipGetLastError();
     }
-    if (a.fin_n) finish(a.fin, a.fin_n, st);
-    const int grid = tw ? tw_grid(a.g, Ns, a.sc) : (int)((nthreads + 255) / 256);
-    if (grid <= 0) return hipErrorInvalidValue;
+    // a pending reduction: one more workgroup of the launches that follow HM_SCHUR_W, a launch of its own otherwise
+    const bool fin_here = a.fin_n && mode == HM_SITE && dag && !red && !tw;
+    if (a.fin_n && !fin_here) {
+        finish(a.fin, a.fin_n, st);
+        a.fin_n = 0;
+    }
+    const int blocks = tw ? tw_grid(a.g, Ns, a.sc) : (int)((nthreads + 255) / 256);
+    if (blocks <= 0) return hipErrorInvalidValue;
+    const int grid = blocks + fin_here;
     const size_t pad = tw ? (size_t)a.sc.ord * 1024 : 0;  // LDS reserved to cap workgroups per CU
 #define HOP_L(D, M, RD)                                                                                  \
     if constexpr (!hop_has(M, D) || (M == HM_SCHUR_RES && sizeof(R) == 4)) return hipErrorInvalidValue;  \
@@ -1547,7 +1589,7 @@ hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& a,
     NS_SWITCH(Ns, if (dag) { HOP_MODES(true) } else { HOP_MODES(false) });
 #undef HOP_MODES
 #undef HOP_L
-    if (reduces && !a.defer) finish(a.red, (unsigned)grid, st);
+    if (reduces && !a.defer) finish(a.red, (unsigned)blocks, st);
     return hipGetLastError();
 }
 template hipError_t launch_hop<double>(int, bool, int, bool, const HopArgs<double>&, hipStream_t);
@@ -1579,10 +1621,13 @@ hipError_t launch_hop_mr(int Ns, bool dag, int mode, const HopArgsMR<R>& args, h
             hipLaunchKernelGGL(k_finish_mr, dim3(a.nr), dim3(256), 0, st, a.partials, a.pstride, npart, a.scal, a.epi);
         return hipGetLastError();
     }
-    if (a.fin_n)
+    const bool fin_here = a.fin_n && mode == HM_SITE && dag;
+    if (a.fin_n && !fin_here) {
         hipLaunchKernelGGL(k_finish_mr, dim3(a.nr), dim3(256), 0, st, a.fin_partials, a.pstride, a.fin_n, a.scal, a.fin_epi);
-    const int grid = (int)npart;
-    a.rpb = hop_mr_rpb(grid, a.nr);
+        a.fin_n = 0;
+    }
+    const int grid = (int)npart + fin_here;
+    a.rpb = hop_mr_rpb((int)npart, a.nr);
     const int gy = (a.nr + a.rpb - 1) / a.rpb;
 #define MR_L(D, M)                                                                                       \
     if constexpr (!hop_has(M, D)) return hipErrorInvalidValue;                                           \
@@ -1615,16 +1660,31 @@ hipError_t launch_hop_mr(int Ns, bool dag, int mode, const HopArgsMR<R>& args, h
 template hipError_t launch_hop_mr<double>(int, bool, int, const HopArgsMR<double>&, hipStream_t, bool);
 template hipError_t launch_hop_mr<float>(int, bool, int, const HopArgsMR<float>&, hipStream_t, bool);
 
+// Up to 2^20 partial sums read by all workgroups together (8 MB through the L2s) the x/p update finishes the residual
+// itself: of the six launches of an iteration one goes.  16^3 x 32 at Ns = 16 would read 134 MB, a third of the update's
+// own traffic, to save 5 of 560 us.
+unsigned xp_finishes(unsigned n, size_t lanes, size_t real_bytes, bool half) {
+    const size_t blocks = half ? (lanes + 255) / 256 : real_bytes == 8 ? xp_grid<double>(12 * lanes) : xp_grid<float>(12 * lanes);
+    return n * blocks <= (size_t)1 << 20 ? n : 0;
+}
+
+// A launch that finishes the residual has fields far below the Infinity Cache (no NT form of it).
+#define XP_LAUNCH(KERN, T, NT_, GRID, ...)                                                                         \
+    {                                                                                                              \
+        const dim3 grid_ = GRID;                                                                                   \
+        if (fin.n) hipLaunchKernelGGL((KERN<T, false, true>), grid_, dim3(256), 0, st, __VA_ARGS__);               \
+        else if (NT_) hipLaunchKernelGGL((KERN<T, true, false>), grid_, dim3(256), 0, st, __VA_ARGS__);            \
+        else hipLaunchKernelGGL((KERN<T, false, false>), grid_, dim3(256), 0, st, __VA_ARGS__);                    \
+    }
+
 hipError_t launch_cg_xp_mr_h(int Ns, int nr, cpx<float>* const* x, void* const* p, cpx<float>* const* r, double* scal,
-                             int Vh, hipStream_t st) {
+                             int Vh, const XpFin& fin, hipStream_t st) {
     if (nr < 1 || nr > NRMAX) return hipErrorInvalidValue;
     XpArgs<float> a{};
     for (int i = 0; i < nr; i++) { a.x[i] = x[i]; a.p[i] = (cpx<float>*)p[i]; a.r[i] = r[i]; }
     const unsigned gx = (unsigned)(((size_t)Vh * Ns + 255) / 256);
     const bool nt = (size_t)Vh * Ns * 12 * sizeof(cpx<float>) > kXpNtBytes;  // the FP32 x and r fields
-#define XPH(NS_)                                                                                                   \
-    if (nt) hipLaunchKernelGGL((k_cg_xp_mr_h<NS_, true>), dim3(gx, nr), dim3(256), 0, st, a, scal, Vh);           \
-    else hipLaunchKernelGGL((k_cg_xp_mr_h<NS_, false>), dim3(gx, nr), dim3(256), 0, st, a, scal, Vh);
+#define XPH(NS_) XP_LAUNCH(k_cg_xp_mr_h, NS_, nt, dim3(gx, nr), a, scal, Vh, fin)
     switch (Ns) {
     case 8: XPH(8) break;
     case 16: XPH(16) break;
@@ -1649,19 +1709,17 @@ hipError_t launch_h2d(int Ns, const void* in, cd* out, int Vh, hipStream_t st) {
 
 template <typename R>
 hipError_t launch_cg_xp_mr(int nr, cpx<R>* const* x, cpx<R>* const* p, cpx<R>* const* r, double* scal, size_t n,
-                           hipStream_t st) {
+                           const XpFin& fin, hipStream_t st) {
     if (nr < 1 || nr > NRMAX) return hipErrorInvalidValue;
     XpArgs<R> a{};
     for (int i = 0; i < nr; i++) { a.x[i] = x[i]; a.p[i] = p[i]; a.r[i] = r[i]; }
-    if (n * sizeof(cpx<R>) > kXpNtBytes)
-        hipLaunchKernelGGL((k_cg_xp_mr<R, true>), dim3(xp_grid<R>(n), nr), dim3(256), 0, st, a, scal, n);
-    else
-        hipLaunchKernelGGL((k_cg_xp_mr<R, false>), dim3(xp_grid<R>(n), nr), dim3(256), 0, st, a, scal, n);
+    XP_LAUNCH(k_cg_xp_mr, R, n * sizeof(cpx<R>) > kXpNtBytes, dim3(xp_grid<R>(n), nr), a, scal, n, fin)
     return hipGetLastError();
 }
-template hipError_t launch_cg_xp_mr<double>(int, cd* const*, cd* const*, cd* const*, double*, size_t, hipStream_t);
+template hipError_t launch_cg_xp_mr<double>(int, cd* const*, cd* const*, cd* const*, double*, size_t, const XpFin&,
+                                            hipStream_t);
 template hipError_t launch_cg_xp_mr<float>(int, cpx<float>* const*, cpx<float>* const*, cpx<float>* const*, double*,
-                                           size_t, hipStream_t);
+                                           size_t, const XpFin&, hipStream_t);
 
 template <typename R>
 hipError_t launch_site(int Ns, bool dag, const cpx<R>* in, cpx<R>* out, const SiteOp* op, int Vh, hipStream_t st) {
@@ -1674,15 +1732,13 @@ template hipError_t launch_site<double>(int, bool, const cd*, cd*, const SiteOp*
 template hipError_t launch_site<float>(int, bool, const cpx<float>*, cpx<float>*, const SiteOp*, int, hipStream_t);
 
 template <typename R>
-hipError_t launch_cg_xp(cpx<R>* x, cpx<R>* p, const cpx<R>* r, double* scal, size_t n, hipStream_t st) {
-    if (n * sizeof(cpx<R>) > kXpNtBytes)
-        hipLaunchKernelGGL((k_cg_xp<R, true>), dim3(xp_grid<R>(n)), dim3(256), 0, st, x, p, r, scal, n);
-    else
-        hipLaunchKernelGGL((k_cg_xp<R, false>), dim3(xp_grid<R>(n)), dim3(256), 0, st, x, p, r, scal, n);
+hipError_t launch_cg_xp(cpx<R>* x, cpx<R>* p, const cpx<R>* r, double* scal, size_t n, const XpFin& fin, hipStream_t st) {
+    XP_LAUNCH(k_cg_xp, R, n * sizeof(cpx<R>) > kXpNtBytes, dim3(xp_grid<R>(n)), x, p, r, scal, n, fin)
     return hipGetLastError();
 }
-template hipError_t launch_cg_xp<double>(cd*, cd*, const cd*, double*, size_t, hipStream_t);
-template hipError_t launch_cg_xp<float>(cpx<float>*, cpx<float>*, const cpx<float>*, double*, size_t, hipStream_t);
+template hipError_t launch_cg_xp<double>(cd*, cd*, const cd*, double*, size_t, const XpFin&, hipStream_t);
+template hipError_t launch_cg_xp<float>(cpx<float>*, cpx<float>*, const cpx<float>*, double*, size_t, const XpFin&,
+                                        hipStream_t);
 
 template <typename R>
 hipError_t launch_axpby(R a, const cpx<R>* x, R b, cpx<R>* y, size_t n, const Red* red, hipStream_t st) {
