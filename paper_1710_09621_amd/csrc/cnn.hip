@@ -185,21 +185,21 @@ __global__ __launch_bounds__(256, 2) void k_conv(const unsigned short* __restric
 // -------------------------------------------------------------------- weight gradient
 // dW[tap][n][k] = sum_rows dY[row][n] X[nbr(row, tap)][k] from the site-transposed dYT and XT (8 consecutive s of one
 // channel are one 16-byte operand: Ns % 8 == 0).  A K step of 32 rows is a column of YG x ZG sites at one xh with all
-// or 32 of their slices, and a wave walks such columns along xh: it keeps the X operands of xh - 1, xh and xh + 1 of
-// its (dt, dz, dy) group in registers, so a step reads one new X column and one dY column (4 KB, in full cache lines)
-// for the 12 MFMAs of the three taps dx.  Each wave of a workgroup takes one of the 27 groups over the workgroup's
-// columns; part[chunk][tap][32][32] are summed by k_wgrad_reduce.  Bound by what the L1 delivers (64 B per cycle and
-// CU, 12 MFMAs of 16 cycles per 4 KB).  16^3 x 32, Ns = 16: 223 us a layer (173 GFLOP), against 1199 us with
-// operands gathered per tap from channel-major copies, in segments of half a cache line.
+// or 32 of their slices, and a wave walks such columns along xh for the nine taps (dy, dx) of its (dt, dz): it keeps the
+// X operands of xh - 1, xh and xh + 1 at y - 1, y and y + 1 in registers, so a step reads three new X columns and one
+// dY column (8 KB, in full cache lines) for 36 MFMAs.  The waves of a workgroup take different lines of its chunk and
+// are added up in LDS; part[chunk][tap][32][32] are summed by k_wgrad_reduce.  What the L1 delivers in a step (64 B per
+// cycle and CU) takes about as long as its MFMAs.  16^3 x 32, Ns = 16 (173 GFLOP): 175 us a layer; with one (dt, dz, dy)
+// per wave, 4 KB for 12 MFMAs, 223 us; with operands gathered per tap from channel-major copies 1199 us.
 template <int NS>
-__global__ __launch_bounds__(256) void k_conv_wgrad(const unsigned short* __restrict__ dYT,
-                                                    const unsigned short* __restrict__ XT, float* __restrict__ part,
-                                                    CbGeom g, int nlines) {
+__global__ __launch_bounds__(256, 2) void k_conv_wgrad(const unsigned short* __restrict__ dYT,
+                                                       const unsigned short* __restrict__ XT, float* __restrict__ part,
+                                                       CbGeom g, int nlines) {
     constexpr int YG = wgrad_yg(NS), ZG = wgrad_zg(NS), STEP = 32 * NS;
-    const int lane = threadIdx.x & 63, tq = blockIdx.y * 4 + (threadIdx.x >> 6), chunk = blockIdx.x;
-    if (tq >= 27) return;
+    __shared__ float sum[36 * 256];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, chunk = blockIdx.x;
     const int li = lane & 15, kb = lane >> 4;
-    const int dy = tq % 3 - 1, dz = (tq / 3) % 3 - 1, dt = tq / 9 - 1;
+    const int dz = (int)blockIdx.y % 3 - 1, dt = (int)blockIdx.y / 3 - 1;
     // rows of this lane's k block: site (iy, iz) of the column, slices s8 .. s8 + 7
     const int iy = NS == 8 ? kb & 1 : NS == 16 ? kb >> 1 : 0, iz = NS == 8 ? kb >> 1 : 0;
     const int s8 = NS == 16 ? (kb & 1) * 8 : NS == 32 ? kb * 8 : 0;
@@ -209,61 +209,81 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(const unsigned short* __rest
         f[0] = *(const bf16x8*)q;
         f[1] = *(const bf16x8*)(q + 16 * NS);  // the other half of the channels
     };
-    f32x4 acc[3][2][2];  // [dx][n tile][k tile]
+    f32x4 acc[3][3][2][2];  // [dy][dx][n tile][k tile]
 #pragma unroll
-    for (int d = 0; d < 3; d++)
+    for (int d = 0; d < 9; d++)
 #pragma unroll
-        for (int k = 0; k < 4; k++) acc[d][k >> 1][k & 1] = {0, 0, 0, 0};
+        for (int k = 0; k < 4; k++) acc[d / 3][d % 3][k >> 1][k & 1] = {0, 0, 0, 0};
     // Chunks of one XCD (workgroup b runs on XCD b % 8) take the lines of one contiguous range in turn, so that what
     // runs at one time reads neighbouring lines: in ranges of their own, half of the L2 accesses missed.
     const int nx = gridDim.x % 8 == 0 ? 8 : 1, xcd = chunk % nx, turn = gridDim.x / nx;
     const int l0 = (int)((long)nlines * xcd / nx), l1 = (int)((long)nlines * (xcd + 1) / nx);
-    for (int l = l0 + chunk / nx; l < l1; l += turn) {
+    for (int l = l0 + chunk / nx * 4 + wave; l < l1; l += turn * 4) {
         const int yg = l % ny, r = l / ny, zg = r % nz, t = r / nz;
         const int y = yg * YG + iy, z = zg * ZG + iz;
         const size_t ca = (size_t)g.Lxh * (y + (size_t)g.Ly * (z + (size_t)g.Lz * t));
-        const size_t cx = (size_t)g.Lxh *
-                          (wrap(y + dy, g.Ly) + (size_t)g.Ly * (wrap(z + dz, g.Lz) + (size_t)g.Lz * wrap(t + dt, g.Lt)));
+        const size_t cz = (size_t)g.Lz * wrap(t + dt, g.Lt) + wrap(z + dz, g.Lz);
         const unsigned short* pa = dYT + site_unit(ca, s8, li, NS) * 8;
-        const unsigned short* px = XT + site_unit(cx, s8, li, NS) * 8;
-        bf16x8 fm[2], f0[2], fp[2], a[2];
-        ld(px + (size_t)(g.Lxh - 1) * STEP, fm);
-        ld(px, f0);
-        ld(px + (size_t)(1 == g.Lxh ? 0 : 1) * STEP, fp);
+        const unsigned short* px[3];
+#pragma unroll
+        for (int e = 0; e < 3; e++)
+            px[e] = XT + site_unit((size_t)g.Lxh * (wrap(y + e - 1, g.Ly) + (size_t)g.Ly * cz), s8, li, NS) * 8;
+        bf16x8 f0[3][2], f1[3][2], f2[3][2], a[2];
+#pragma unroll
+        for (int e = 0; e < 3; e++) {
+            ld(px[e] + (size_t)(g.Lxh - 1) * STEP, f0[e]);
+            ld(px[e], f1[e]);
+            ld(px[e] + (size_t)(1 == g.Lxh ? 0 : 1) * STEP, f2[e]);
+        }
         ld(pa, a);
-        for (int x = 0; x < g.Lxh; x++) {
-            // the next step's operands are requested before this step's MFMAs (past the end: the line's first ones)
-            bf16x8 an[2], fn[2];
+        auto mfma = [&](int d, const bf16x8 f[3][2]) {
+#pragma unroll
+            for (int e = 0; e < 3; e++)
+#pragma unroll
+                for (int n = 0; n < 2; n++)
+#pragma unroll
+                    for (int k = 0; k < 2; k++)
+                        acc[e][d][n][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[n], f[e][k], acc[e][d][n][k], 0, 0, 0);
+        };
+        // one step at x: the operands of x - 1 are used first and give way to those of x + 2 (past the end: the line's
+        // first ones), which the next step needs last
+        auto step = [&](int x, bf16x8 fm[3][2], const bf16x8 fz[3][2], const bf16x8 fp[3][2]) {
+            bf16x8 an[2];
             const int xa = x + 1 < g.Lxh ? x + 1 : 0, xf = xa + 1 < g.Lxh ? xa + 1 : 0;
             ld(pa + (size_t)xa * STEP, an);
-            ld(px + (size_t)xf * STEP, fn);
+            mfma(0, fm);
+#pragma unroll
+            for (int e = 0; e < 3; e++) ld(px[e] + (size_t)xf * STEP, fm[e]);
             __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int n = 0; n < 2; n++)
-#pragma unroll
-                for (int k = 0; k < 2; k++) {
-                    acc[0][n][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[n], fm[k], acc[0][n][k], 0, 0, 0);
-                    acc[1][n][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[n], f0[k], acc[1][n][k], 0, 0, 0);
-                    acc[2][n][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[n], fp[k], acc[2][n][k], 0, 0, 0);
-                }
-#pragma unroll
-            for (int k = 0; k < 2; k++) {
-                fm[k] = f0[k];
-                f0[k] = fp[k];
-                fp[k] = fn[k];
-                a[k] = an[k];
-            }
+            mfma(1, fz);
+            mfma(2, fp);
+            a[0] = an[0];
+            a[1] = an[1];
+        };
+        int x = 0;
+        for (; x + 2 < g.Lxh; x += 3) {
+            step(x, f0, f1, f2);
+            step(x + 1, f1, f2, f0);
+            step(x + 2, f2, f0, f1);
         }
+        if (x < g.Lxh) step(x, f0, f1, f2);
+        if (x + 1 < g.Lxh) step(x + 1, f1, f2, f0);
     }
+    // the four waves' sums in order; the last one writes them out
+    for (int w = 0; w < 4; w++) {
+        if (wave == w) {
 #pragma unroll
-    for (int d = 0; d < 3; d++) {
-        float* dst = part + ((size_t)chunk * 81 + tq * 3 + d) * 1024;
+            for (int q = 0; q < 36; q++)
 #pragma unroll
-        for (int n = 0; n < 2; n++)
-#pragma unroll
-            for (int k = 0; k < 2; k++)
-#pragma unroll
-                for (int j = 0; j < 4; j++) dst[(n * 16 + kb * 4 + j) * 32 + k * 16 + li] = acc[d][n][k][j];
+                for (int j = 0; j < 4; j++) {
+                    const int e = q / 12, d = q / 4 % 3, n = q / 2 % 2, k = q % 2;
+                    float* c = sum + q * 256 + j * 64 + lane;
+                    const float v = w > 0 ? *c + acc[e][d][n][k][j] : acc[e][d][n][k][j];
+                    if (w < 3) *c = v;
+                    else part[((size_t)chunk * 81 + blockIdx.y * 9 + e * 3 + d) * 1024 + (n * 16 + kb * 4 + j) * 32 + k * 16 + li] = v;
+                }
+        }
+        __syncthreads();
     }
 }
 
@@ -507,19 +527,19 @@ hipError_t cnn_conv_fwd(const unsigned short* X, const unsigned short* W, const 
 #undef CONV
 }
 
-// chunks of the weight gradient: all their workgroups (7 per chunk, four waves each) fit the chip at once at four
-// per CU, and a multiple of 8 keeps the seven workgroups of a chunk on one XCD (workgroup b runs on XCD b % 8)
-constexpr int WGRAD_CHUNKS = 144;
+// chunks of the weight gradient: all their workgroups (9 per chunk, four waves each) fit the chip at once at two per
+// CU, and a multiple of 8 keeps the nine workgroups of a chunk on one XCD (workgroup b runs on XCD b % 8)
+constexpr int WGRAD_CHUNKS = 56;
 static int wgrad_lines(const Geom& g, int Ns) { return g.Ly / wgrad_yg(Ns) * (g.Lz / wgrad_zg(Ns)) * g.Lt; }
 int cnn_wgrad_chunks(const Geom& g, int Ns) {
-    const int n = std::min(wgrad_lines(g, Ns), WGRAD_CHUNKS);
+    const int n = std::min((wgrad_lines(g, Ns) + 3) / 4, WGRAD_CHUNKS);
     return n < 8 ? n : n / 8 * 8;
 }
 
 hipError_t cnn_wgrad(const unsigned short* dYT, const unsigned short* XT, float* part, float* gw, const Geom& g, int Ns,
                      int cin, int cout, hipStream_t st) {
     const int nlines = wgrad_lines(g, Ns), nchunk = cnn_wgrad_chunks(g, Ns);
-    const dim3 grid(nchunk, 7);
+    const dim3 grid(nchunk, 9);
     switch (Ns) {
     case 8: hipLaunchKernelGGL(k_conv_wgrad<8>, grid, dim3(256), 0, st, dYT, XT, part, cbg(g, Ns), nlines); break;
     case 16: hipLaunchKernelGGL(k_conv_wgrad<16>, grid, dim3(256), 0, st, dYT, XT, part, cbg(g, Ns), nlines); break;
