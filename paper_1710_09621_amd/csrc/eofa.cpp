@@ -1776,12 +1776,16 @@ void apply_op(eofa_ctx* ctx, int op, double mp, double mm, const cd* in, cd* out
     case EOFA_OP_HT: {
         const bool dag = (op == EOFA_OP_DT_DAG);
         const SiteOp* M = tab(dag ? SK_M_DAG : SK_M);
+        bool canon = false;
         for (int par = 0; par < 2; par++) {
             auto a = hop_args<R>(ctx, par);
             a.in = B.in[1 - par]; a.self = B.in[par]; a.out = B.out[par]; a.opA = M; a.cz = 1; a.caux = 0;
+            canon = hop_canon(ctx->g, Ns, a.sc);  // then the hop writes out itself
+            if (canon) { a.canon = out; a.refl = op == EOFA_OP_HT; }
             int mode = (op == EOFA_OP_DW) ? HM_DW : (op == EOFA_OP_HOP ? HM_LIN : HM_DT);
             hop<R>(ctx, dag, mode, false, a);
         }
+        if (canon) return;
         break;
     }
     case EOFA_OP_AT_INV: {

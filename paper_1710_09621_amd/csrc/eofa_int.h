@@ -42,6 +42,8 @@ template <typename R> struct HopArgs {
     const cpx<R>* aux2;       // parity par
     const cpx<R>* self;       // parity par (diagonal term of D_T / D_w)
     cpx<float>* outf;         // HM_LIN: not null: out goes here in FP32 instead
+    cd* canon;                // not null: out goes to the output sites of this canonical field instead (hop_canon)
+    int refl;                 // canon: gamma_5 R5 on the way, as in launch_unpack5
     const SiteOp* opA;
     const SiteOp* opB;
     R cz, caux, diag;
@@ -74,6 +76,8 @@ template <typename R> struct HopArgsMR {
     R cz, caux, diag;
     const cpx<R>* self;     // diagonal term of D_T / D_w (one system)
     cpx<float>* outf;       // as in HopArgs (one system)
+    cd* canon;
+    int refl;
     double* scal;           // nr blocks of SC_N scalars
     const double* done;     // done[r * SC_N] != 0: skip system r (may be null)
     double* partials;       // partials[r * pstride + block]
@@ -118,6 +122,8 @@ template <typename R> hipError_t launch_cg_xp_mr(int nr, cpx<R>* const* x, cpx<R
 
 template <typename R> hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& a, hipStream_t st);
 int tw_grid(const Geom& g, int Ns, const Sched& sc);
+// whether a launch under sc has a form of HM_LIN, HM_DT and HM_DW that writes a canonical field
+bool hop_canon(const Geom& g, int Ns, const Sched& sc);
 Sched block_sched(const Geom& g, int Ns);
 Sched default_sched(const Geom& g, int Ns, size_t real_bytes, bool half);
 template <typename R> hipError_t launch_site(int Ns, bool dag, const cpx<R>* in, cpx<R>* out, const SiteOp* op, int Vh,

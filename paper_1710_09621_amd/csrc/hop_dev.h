@@ -1,4 +1,5 @@
-// Column loads and stores of the hop kernels: cache policy, FP16 columns, reconstruction of scaled columns.
+// Column loads and stores of the hop kernels: cache policy, FP16 columns, reconstruction of scaled columns, canonical
+// fields.
 #pragma once
 #include "eofa_int.h"
 
@@ -150,6 +151,21 @@ __device__ __forceinline__ void reconstruct_n(cpx<R> acc[12], const cpx<R> w[6],
         acc[6 + c].x = fma(sn, t0.x, acc[6 + c].x); acc[6 + c].y = fma(sn, t0.y, acc[6 + c].y);
         acc[9 + c].x = fma(sn, t1.x, acc[9 + c].x); acc[9 + c].y = fma(sn, t1.y, acc[9 + c].y);
     }
+}
+
+// whether the kernel of MODE can write a canonical field
+template <int MODE, bool RED> constexpr bool canon_mode() {
+    return !RED && (MODE == HM_LIN || MODE == HM_DT || MODE == HM_DW);
+}
+// canonical index of (s, lex site, j): ((s * V + lex) * 12 + j)
+__device__ __forceinline__ void cb_to_lex(const Geom& g, int cb, int par, int& lex) {
+    int xh = cb % g.Lxh;
+    int r = cb / g.Lxh;
+    int y = r % g.Ly; r /= g.Ly;
+    int z = r % g.Lz;
+    int t = r / g.Lz;
+    int x = 2 * xh + ((y + z + t + par) & 1);
+    lex = x + g.Lx * (y + g.Ly * (z + g.Lz * t));
 }
 
 }  // namespace eofa

@@ -273,7 +273,15 @@ __global__ __launch_bounds__(256) void k_hop_split(const HopArgsMR<R> a) {
             if (aux) { v[c].x = fma(a.caux, ax[c].x, v[c].x); v[c].y = fma(a.caux, ax[c].y, v[c].y); }
         }
     }
-    if (MODE == HM_LIN && a.outf) {
+    if (canon_mode<MODE, RED>() && a.canon) {
+        int lex;
+        cb_to_lex(a.g, cb, a.par, lex);
+        cd* d = a.canon + ((a.refl ? NS - 1 - s : s) * 2 * (size_t)a.g.Vh + lex) * 12 + 3 * w;
+        const double sg = a.refl && !up ? -1.0 : 1.0;
+        if (valid)
+#pragma unroll
+            for (int c = 0; c < 3; c++) d[c] = {sg * (double)v[c].x, sg * (double)v[c].y};
+    } else if (MODE == HM_LIN && a.outf) {
         cpx<float> vf[3];
 #pragma unroll
         for (int c = 0; c < 3; c++) vf[c] = {(float)v[c].x, (float)v[c].y};

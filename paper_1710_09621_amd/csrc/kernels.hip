@@ -642,7 +642,10 @@ __device__ __forceinline__ double hop_epilogue_h(const HopArgs<R>& a, cpx<R> z[6
             }
         }
     }
-    if (MODE == HM_LIN && a.outf) {
+    if (canon_mode<MODE, RED>() && a.canon) {  // the caller writes them
+#pragma unroll
+        for (int j = 0; j < 6; j++) z[j] = v[j];
+    } else if (MODE == HM_LIN && a.outf) {
 #pragma unroll
         for (int j = 0; j < 6; j++) st_out(a.outf + base + J(j), cpx<float>{(float)v[j].x, (float)v[j].y});
     } else {
@@ -676,11 +679,47 @@ __device__ __forceinline__ void tws_carry(cpx<R>* cw, const cpx<R>* __restrict__
     for (int c = 0; c < 3; c++) cw[c * 512] = w[c];
 }
 
+// One slice of xch: a slot per site-lane and one more per site, and an odd number of 16-byte slots in all, so that
+// tws_canon's reads (components fastest) spread over the banks.
+template <int NS> constexpr int XCH = 256 + 256 / NS + 1;
+
+// This step's results to the canonical field, where the 12 components of a site and slice are consecutive: through
+// xch, the upper spins first and then the lower ones, in runs of 96 bytes.
+// Dt on 32^3 x 64, Ns = 16, FP64: 9.80 -> 8.11 ms (hops 2 x 2.57 -> 2 x 3.04 ms, the unpacking pass of 2.23 ms gone).
+// Ordinary stores, which the L2 joins to whole sectors: nontemporal ones took 9.80 ms.
+template <int NS, int H, typename R>
+__device__ __forceinline__ void tws_canon(const HopArgs<R>& a, const cpx<R> v[6], int cb, int ls, int q,
+                                          cpx<R> (*xch)[3][XCH<NS>]) {
+    const size_t V = 2 * (size_t)a.g.Vh;
+    size_t at[3];
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        const int u = threadIdx.x + 512 * k, site = u / 6 % (256 / NS), s = u / 6 / (256 / NS);
+        int lex;
+        cb_to_lex(a.g, cb - ls + site, a.par, lex);
+        at[k] = ((a.refl ? NS - 1 - s : s) * V + lex) * 12 + u % 6;
+    }
+#pragma unroll
+    for (int low = 0; low < 2; low++) {
+        __syncthreads();  // xch has been read
+#pragma unroll
+        for (int c = 0; c < 3; c++) xch[H][c][q + ls] = v[3 * low + c];
+        __syncthreads();
+        const double sg = a.refl && low ? -1.0 : 1.0;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            const int u = threadIdx.x + 512 * k, c = u % 6, site = u / 6 % (256 / NS), s = u / 6 / (256 / NS);
+            const cpx<R> w = xch[c / 3][c % 3][site * (NS + 1) + s];
+            a.canon[at[k] + 6 * low] = {sg * (double)w.x, sg * (double)w.y};
+        }
+    }
+}
+
 // One t-walk step of component H at (cb, s): the operations of tw_step (XL form) on this lane's share.
 template <int NS, bool DAG, int MODE, bool RED, int H, typename R>
 __device__ __forceinline__ void tws_step(const HopArgs<R>& a, cpx<R> (*sU)[8][9], const SiteOpL<NS>& sA,
                                          const SiteOpL<NS>& sB, int cb, int s, int lane, int ls, int q, cpx<R>* cw,
-                                         double& nrm, cpx<R> (*xl)[256], cpx<R> (*xch)[3][256]) {
+                                         double& nrm, cpx<R> (*xl)[256], cpx<R> (*xch)[3][XCH<NS>]) {
     constexpr int SF = DAG ? +1 : -1, SB = -SF;
     HOP_FENCE();
     int nb[8];
@@ -711,10 +750,10 @@ __device__ __forceinline__ void tws_step(const HopArgs<R>& a, cpx<R> (*sU)[8][9]
     // hand the x, y partial of the lower spin 1 - H to the other half and take its partial of the lower spin H;
     // the barrier also ends every lane's reads of this step's x neighbours in xl
 #pragma unroll
-    for (int c = 0; c < 3; c++) xch[H][c][q] = ad[c];
+    for (int c = 0; c < 3; c++) xch[H][c][q + ls] = ad[c];
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < 3; c++) ad[c] = xch[1 - H][c][q];
+    for (int c = 0; c < 3; c++) ad[c] = xch[1 - H][c][q + ls];
     HOP_FENCE();
     hop_mu_h<NS, DAG, 2, H>(au, ad, a.in, sU[ls][2], sU[ls][6], nb, s);
     HOP_FENCE();
@@ -737,12 +776,14 @@ __device__ __forceinline__ void tws_step(const HopArgs<R>& a, cpx<R> (*sU)[8][9]
     HOP_FENCE();
     cpx<R> z[6] = {au[0], au[1], au[2], ad[0], ad[1], ad[2]};
     nrm += hop_epilogue_h<NS, DAG, MODE, RED, H>(a, z, cb, s, lane, sA, sB);
+    if constexpr (canon_mode<MODE, RED>())
+        if (a.canon) tws_canon<NS, H>(a, z, cb, ls, q, xch);
     HOP_FENCE();
 }
 
 template <int NS, bool DAG, int MODE, bool RED, int H, typename R>
 __device__ __forceinline__ double tws_walk(const HopArgs<R>& a, cpx<R> (*sU)[8][9], const SiteOpL<NS>& sA,
-                                           const SiteOpL<NS>& sB, cpx<R> (*xl)[256], cpx<R> (*xch)[3][256],
+                                           const SiteOpL<NS>& sB, cpx<R> (*xl)[256], cpx<R> (*xch)[3][XCH<NS>],
                                            cpx<R> (*carry)[3][512], int i, int st, int t0, int TC, int s, int lane,
                                            int ls, int q) {
     const int tid = threadIdx.x;
@@ -766,7 +807,7 @@ __global__ __launch_bounds__(512, 1) void k_hop_tws(const HopArgs<R> a) {
     if (a.done && *a.done != 0.0) return;
     __shared__ cpx<R> sU[256 / NS][8][9];
     __shared__ cpx<R> xl[12][256];       // the current slab's input columns of this segment
-    __shared__ cpx<R> xch[2][3][256];    // lower-spin partial sums handed between the halves
+    __shared__ cpx<R> xch[2][3][XCH<NS>];  // lower-spin partial sums handed between the halves
     __shared__ cpx<R> carry[2][3][512];  // carried backward t terms (slot t % 2 for slab t), per lane
     __shared__ SiteOpL<NS> sA, sB;
     {
@@ -1165,17 +1206,6 @@ __global__ void k_finish_many(const double* __restrict__ partials, int pstride, 
 }
 
 // ===================================================================== boundary kernels
-// canonical index of (s, lex site, j): ((s * V + lex) * 12 + j)
-__device__ __forceinline__ void cb_to_lex(const Geom& g, int cb, int par, int& lex) {
-    int xh = cb % g.Lxh;
-    int r = cb / g.Lxh;
-    int y = r % g.Ly; r /= g.Ly;
-    int z = r % g.Lz;
-    int t = r / g.Lz;
-    int x = 2 * xh + ((y + z + t + par) & 1);
-    lex = x + g.Lx * (y + g.Ly * (z + g.Lz * t));
-}
-
 // canonical 5D (complex128) <-> the internal half fields of both parities.  The canonical field has s outermost, the
 // internal ones innermost: a workgroup transposes PK_SITES consecutive sites with all their slices in LDS, so that both
 // sides are read and written in runs of 1.5 KB or more.  One (site, component, slice) per thread took 16-byte pieces of
@@ -1514,6 +1544,13 @@ unsigned hop_mr_partials(const Geom& g, int Ns, int nr) {
     return hop_split(g, Ns, nr) ? (unsigned)hop_split_blocks(g, Ns) : (unsigned)(((size_t)g.Vh * Ns + 255) / 256);
 }
 
+// The forms that apply_op takes by default below kSplitLanes and, at Ns = 16, for large fields; the others leave their
+// results in the internal order and launch_unpack5 moves them.
+bool hop_canon(const Geom& g, int Ns, const Sched& sc) {
+    const bool tw = sc.mode == 3 || sc.mode == 5 || sc.mode == 6;
+    return tw ? sc.mode == 6 && Ns == 16 : hop_split(g, Ns, 1);
+}
+
 // LDS that a launch of kern may reserve on top of its static LDS (gfx950: 160 KB per workgroup).
 template <typename K> static size_t lds_room(K kern) {
     hipFuncAttributes at{};
@@ -1531,7 +1568,7 @@ hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& ar
         HopArgsMR<R> m{};
         m.g = a.g; m.par = a.par; m.nr = 1; m.Uown = a.Uown; m.Uoth = a.Uoth;
         m.in[0] = a.in; m.out[0] = a.out; m.out2[0] = a.out2; m.aux[0] = a.aux; m.aux2[0] = a.aux2;
-        m.opA[0] = a.opA; m.opB[0] = a.opB; m.self = a.self; m.outf = a.outf;
+        m.opA[0] = a.opA; m.opB[0] = a.opB; m.self = a.self; m.outf = a.outf; m.canon = a.canon; m.refl = a.refl;
         m.cz = a.cz; m.caux = a.caux; m.diag = a.diag;
         m.scal = (double*)a.scal; m.done = a.done; m.partials = a.red.partials;
         if (a.fin_n) { m.scal = a.fin.scal; m.fin_partials = a.fin.partials; m.fin_n = a.fin_n; m.fin_epi = a.fin.epi; }
@@ -1540,6 +1577,7 @@ hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& ar
         if (reduces && !a.defer) finish(a.red, (unsigned)hop_split_blocks(a.g, Ns), st);
         return hipGetLastError();
     }
+    if (a.canon && !hop_canon(a.g, Ns, a.sc)) return hipErrorInvalidValue;
     // a pending reduction: one more workgroup of the launches that follow HM_SCHUR_W, a launch of its own otherwise
     const bool fin_here = a.fin_n && mode == HM_SITE && dag && !red && !tw;
     if (a.fin_n && !fin_here) {

@@ -27,3 +27,23 @@ def test_pack_and_unpack(dims, Ns):
         out = ctx.apply("DT", x, 0.05, 0.3, prec=prec).reshape(Ns, V, 12)[:, torch.from_numpy(sites).cuda()]
         assert relerr(out.transpose(0, 1).reshape(ref.shape), ref) < tol, prec
     assert torch.equal(ctx.apply("HOP_EO", x) + ctx.apply("HOP_OE", x), ctx.apply("HOP", x))
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("dims", [(8, 8, 8, 8), (16, 8, 4, 16)], ids=str)
+def test_hops_that_write_the_canonical_field(dims, prec):
+    """The spin-split t-walk and the direction-split form write Dt, H_T, D_w and H to the canonical field themselves:
+    the bits of the unsplit forms, whose results are moved."""
+    print(f"[gpu] canonical output dims={dims} prec={prec}", flush=True)
+    ctx, lat = ctx_and_oracle(dims, 16)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    x = torch.randn(lat.shape5, dtype=torch.complex128, device="cuda", generator=g)
+    ops = ["DT", "DT_DAG", "HT", "DW", "HOP"]
+    cands = ctx.schedule_candidates(prec)
+    by_mode = {s[0]: s for s in cands}
+    assert 6 in by_mode and 5 in by_mode
+    default = [ctx.apply(op, x, 0.05, 0.3, prec=prec) for op in ops]
+    for mode in sorted(by_mode):
+        ctx.set_schedule(by_mode[mode], prec)
+        for op, ref in zip(ops, default):
+            assert torch.equal(ctx.apply(op, x, 0.05, 0.3, prec=prec), ref), (mode, op)
