@@ -63,9 +63,11 @@ typedef struct {
     eofa_precision prec;   /* storage precision of the inner Krylov solver */
     eofa_precond pc;       /* EOFA_PC_LEARNED: flexible GCR with the learned preconditioner */
     double reliable_delta; /* mixed precision: reliable update when ||r|| drops by this factor (0: 0.1) */
-    int use_graph;         /* capture blocks of check_every CG iterations in a hipGraph (once per buffer
-                              set, cached in the context) and replay them; same arithmetic as eager */
-    int check_every;       /* iterations between host convergence checks (0: automatic) */
+    int use_graph;         /* capture blocks of CG iterations (check_every of them; automatic: multiples of 4) in
+                              hipGraphs (once per buffer set, cached in the context) and replay them; same
+                              arithmetic as eager */
+    int check_every;       /* iterations between host convergence checks (0: automatic, by the convergence rate
+                              measured so far, 16 at most) */
 } eofa_solve_params;
 
 typedef struct {
@@ -343,6 +345,9 @@ eofa_status eofa_dslash_bench(eofa_ctx *ctx, int prec, int nrep, double *ms, dou
  * (mode 0: linear, 1: 3D tiles, 3: t-walk, 5: t-walk with the x neighbours from LDS, 6: mode 5 with
  * two lanes per site and slice, Ns = 16);
  * *best_ms / *base_ms (may be NULL) the chosen and the linear-order launch times.
+ * A context that was never tuned takes an order by rule: t-walk for FP64 and for FP32 fields above 256 MB,
+ * tiles or XCD-contiguous ranges below.  Launches of at most 49,152 (site, s) lanes per parity take the
+ * direction-split form, except under t-walk schedules; the batch kernels take tiles under t-walk schedules.
  */
 eofa_status eofa_autotune(eofa_ctx *ctx, int prec, int nrep, int sched_out[7], double *best_ms,
                           double *base_ms);

@@ -3,7 +3,7 @@
     python paper_1710_09621_amd/profile_cnn.py [--dims 16 16 16 32] [--Ns 16] [--nrep 5]
 
 Sets up the seeded 16^3 x 32, Ns = 16 lattice, installs seeded network parameters, then runs the
-network forward nrep times (four k_conv_fwd launches each) and nrep training steps (forward, weight
+network forward nrep times (four k_conv launches each) and nrep training steps (forward, weight
 gradient, backward-data convolutions and Adam), timing both with HIP events on the library's stream.
 Prints the per-call times and the convolution flop rate against the dense BF16 matrix-core peak.
 """

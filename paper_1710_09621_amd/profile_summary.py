@@ -35,7 +35,8 @@ import os
 import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-KERNEL_SOURCES = ["paper_1710_09621_amd/csrc/kernels.hip", "paper_1710_09621_amd/csrc/eofa_dev.h",
+KERNEL_SOURCES = ["paper_1710_09621_amd/csrc/kernels.hip", "paper_1710_09621_amd/csrc/hop_dev.h",
+                  "paper_1710_09621_amd/csrc/eofa_dev.h",
                   "paper_1710_09621_amd/csrc/eofa_int.h"]
 
 
