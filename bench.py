@@ -277,7 +277,8 @@ def main():
 
     sched64 = tune["fp64"]["sched"]
     traffic = measured_traffic(args.traffic, dims, Ns, sched64)
-    kern = {3: "k_hop_tw<16, false, HM_SITE, false, double, false> (u = A_T^{-1} H_eo p; t-walk schedule)",
+    kern = {2: "k_hop_split<16, false, HM_SITE, false, double, false> (u = A_T^{-1} H_eo p; direction-split form)",
+            3: "k_hop_tw<16, false, HM_SITE, false, double, false> (u = A_T^{-1} H_eo p; t-walk schedule)",
             5: "k_hop_tw<16, false, HM_SITE, false, double, true> (u = A_T^{-1} H_eo p; t-walk schedule, x "
                "neighbours from LDS)",
             6: "k_hop_tws<16, false, HM_SITE, false, double> (u = A_T^{-1} H_eo p; t-walk schedule, x neighbours "

@@ -342,12 +342,12 @@ eofa_status eofa_dslash_bench(eofa_ctx *ctx, int prec, int nrep, double *ms, dou
  * nrep launches of the fused hop (0: 4) and keeps the fastest for all later solves.  Every
  * schedule gives bitwise the same operator; the CG reductions may sum in another order.
  * sched_out[7] (may be NULL) receives {mode, xcd, ty, tz, tt, nyb, ord} for a persistent cache
- * (mode 0: linear, 1: 3D tiles, 3: t-walk, 5: t-walk with the x neighbours from LDS, 6: mode 5 with
- * two lanes per site and slice, Ns = 16);
+ * (mode 0: linear, 1: 3D tiles, 2: direction-split form, for at most 49,152 (site, s) lanes per parity,
+ * 3: t-walk, 5: t-walk with the x neighbours from LDS, 6: mode 5 with two lanes per site and slice, Ns = 16);
  * *best_ms / *base_ms (may be NULL) the chosen and the linear-order launch times.
- * A context that was never tuned takes an order by rule: t-walk for FP64 and for FP32 fields above 256 MB,
- * tiles or XCD-contiguous ranges below.  Launches of at most 49,152 (site, s) lanes per parity take the
- * direction-split form, except under t-walk schedules; the batch kernels take tiles under t-walk schedules.
+ * A context that was never tuned takes one by rule: the direction-split form up to its limit; above it the t-walk
+ * for FP64 and for FP32 fields above 256 MB, tiles, linear order or XCD-contiguous ranges else.  The batch kernels,
+ * which have no t-walk, take the split form or the rule's other orders where modes 2 to 6 are installed.
  */
 eofa_status eofa_autotune(eofa_ctx *ctx, int prec, int nrep, int sched_out[7], double *best_ms,
                           double *base_ms);

@@ -417,7 +417,7 @@ void cg_iteration(eofa_ctx* ctx, cpx<R>* x, cpx<R>* r, cpx<R>* p, cpx<R>* u, cpx
     {
         auto a = hop_args<R>(ctx, 0);
         a.in = wt; a.out = at; a.opA = Ad; a.cz = 1; a.caux = 0; a.done = done;
-        a.fin = red_of(ctx, 0, EPI_CG_W); a.fin_n = hop_partials(ctx->g, ctx->Ns, a.sc, 1);
+        a.fin = red_of(ctx, 0, EPI_CG_W); a.fin_n = hop_partials(ctx->g, ctx->Ns, a.sc);
         hop<R>(ctx, true, HM_SITE, false, a, k0 + EOFA_K_HOP_DAG);
     }
     {
@@ -425,7 +425,7 @@ void cg_iteration(eofa_ctx* ctx, cpx<R>* x, cpx<R>* r, cpx<R>* p, cpx<R>* u, cpx
         a.in = at; a.out = r; a.aux = w; a.aux2 = r; a.cz = (R)-0.25; a.caux = 1;
         a.red = red_of(ctx, 0, EPI_CG_R); a.done = done;
         fin.partials = a.red.partials;
-        fin.n = xp_finishes(hop_partials(ctx->g, ctx->Ns, a.sc, 1), (size_t)ctx->g.Vh * ctx->Ns, sizeof(R), false);
+        fin.n = xp_finishes(hop_partials(ctx->g, ctx->Ns, a.sc), (size_t)ctx->g.Vh * ctx->Ns, sizeof(R), false);
         a.defer = fin.n > 0;
         hop<R>(ctx, true, HM_SCHUR_Q, true, a, k0 + EOFA_K_SCHUR_Q);
     }
@@ -534,10 +534,9 @@ CgOut cg64(eofa_ctx* ctx, const Work64& W, double mp, double mm, double tol_n, i
 }
 
 void ensure_partials_mr(eofa_ctx* ctx) {
-    // batch kernels: one partial per workgroup of a launch of one system (the split form is taken by fewer systems
-    // first); launch_mdot: up to 1024 blocks
-    const int need = std::max((int)std::max(hop_mr_partials(ctx->g, ctx->Ns, 1), hop_mr_partials(ctx->g, ctx->Ns, NRMAX)) + 1,
-                              1024);
+    // batch kernels: one partial per workgroup (four times as many in the split form); launch_mdot: up to 1024 blocks
+    const unsigned np = hop_partials(ctx->g, ctx->Ns, hop_split(ctx->g, ctx->Ns, 1) ? kSplitSched : Sched{});
+    const int need = std::max((int)np + 1, 1024);
     if (ctx->partials_mr && ctx->pstride >= need) return;
     if (ctx->partials_mr) HIPCHK(hipFree(ctx->partials_mr));
     // rows: NRMAX systems of the batch kernels, or 2 x 9 (re, im) dot products of launch_mdot
@@ -1044,8 +1043,7 @@ void sync_scal_batch(eofa_ctx* ctx, int nr) {
 template <typename R> HopArgsMR<R> mr_args(eofa_ctx* ctx, int par, int nr, bool half = false) {
     HopArgsMR<R> a{};
     HopArgs<R> b = hop_args<R>(ctx, par);
-    a.g = b.g; a.sc = half ? ctx->sched[2] : b.sc; a.par = par;
-    if (a.sc.mode >= 3) a.sc = block_sched(ctx->g, ctx->Ns);
+    a.g = b.g; a.sc = batch_sched(ctx->g, ctx->Ns, half ? ctx->sched[2] : b.sc, nr); a.par = par;
     a.nr = nr; a.Uown = b.Uown; a.Uoth = b.Uoth;
     a.scal = ctx->scal + BATCH_OFF;
     a.done = a.scal + SC_DONE;
@@ -1059,7 +1057,7 @@ template <typename R> HopArgsMR<R> mr_args(eofa_ctx* ctx, int par, int nr, bool 
 template <typename R, bool H = false> void cg_iteration_mr(eofa_ctx* ctx, std::vector<Sys>& sys) {
     const int nr = (int)sys.size();
     auto V = [](void* p) { return (cpx<R>*)p; };
-    const unsigned np = hop_mr_partials(ctx->g, ctx->Ns, nr);
+    const unsigned np = hop_partials(ctx->g, ctx->Ns, mr_args<R>(ctx, 0, nr, H).sc);
     const XpFin fin{ctx->partials_mr, ctx->pstride, xp_finishes(np, (size_t)ctx->g.Vh * ctx->Ns, sizeof(R), H)};
     {
         auto a = mr_args<R>(ctx, 0, nr, H);
@@ -1691,6 +1689,7 @@ std::vector<Sched> sched_candidates(const eofa_ctx* ctx, int prec) {
     const long lanes_line = (long)g.Lxh * g.Ly * ctx->Ns;  // lanes of one (z, t) line
     const int nyb = (lanes_line % 256 == 0) ? (int)(lanes_line / 256) : 0;
     for (int x = 0; x < 2; x++) c.push_back(Sched{0, x, 1, 1, 1, nyb > 0 ? nyb : 1, 0});
+    if (hop_split(g, ctx->Ns, 1)) c.push_back(kSplitSched);
     if (nyb == 0) return c;
     const int opts[] = {1, 2, 4, 8, 16};
     for (int x = 0; x < 2; x++) {
@@ -1780,7 +1779,7 @@ void apply_op(eofa_ctx* ctx, int op, double mp, double mm, const cd* in, cd* out
         for (int par = 0; par < 2; par++) {
             auto a = hop_args<R>(ctx, par);
             a.in = B.in[1 - par]; a.self = B.in[par]; a.out = B.out[par]; a.opA = M; a.cz = 1; a.caux = 0;
-            canon = hop_canon(ctx->g, Ns, a.sc);  // then the hop writes out itself
+            canon = hop_canon(Ns, a.sc);  // then the hop writes out itself
             if (canon) { a.canon = out; a.refl = op == EOFA_OP_HT; }
             int mode = (op == EOFA_OP_DW) ? HM_DW : (op == EOFA_OP_HOP ? HM_LIN : HM_DT);
             hop<R>(ctx, dag, mode, false, a);

@@ -23,11 +23,13 @@ constexpr bool hop_has(int mode, bool dag) {
 // sites of a t-slab and walks tt consecutive slabs; the segments form an nyb x (segments / nyb) grid
 // and the workgroups that run together on an XCD take a ty x tz patch of it; ord = KB of LDS reserved
 // per workgroup (caps the workgroups per CU).  mode 5: mode 3 with the x-direction columns read from LDS,
-// for segments that hold whole x-lines.  Mode 6: mode 5 with two lanes per site and slice.  The batch kernels
-// run block_sched's order under modes 3, 5 and 6.
+// for segments that hold whole x-lines.  Mode 6: mode 5 with two lanes per site and slice.  mode 2: the
+// direction-split form (hop_split.hip) in XCD-contiguous ranges; the other fields have no meaning.
 struct Sched {
     int mode, xcd, ty, tz, tt, nyb, ord;
 };
+constexpr Sched kSplitSched{2, 1, 1, 1, 1, 1, 0};
+inline bool is_twalk(const Sched& sc) { return sc.mode == 3 || sc.mode == 5 || sc.mode == 6; }
 
 template <typename R> struct HopArgs {
     Geom g;
@@ -100,11 +102,10 @@ struct XpFin {
 };
 // n, the partial sums of a system, if an x/p update of Vh Ns lanes is to finish them, else 0
 unsigned xp_finishes(unsigned n, size_t lanes, size_t real_bytes, bool half);
-// Partial sums that a reducing launch of nr systems writes per system (for fin_n).
-unsigned hop_partials(const Geom& g, int Ns, const Sched& sc, int nr);
-unsigned hop_mr_partials(const Geom& g, int Ns, int nr);
-// direction-split form of the hop (hop_split.hip): whether a launch of nr systems takes it, its workgroups per
-// system, and the launch itself (no finishing kernel)
+// Partial sums that a reducing launch under sc writes per system (for fin_n).
+unsigned hop_partials(const Geom& g, int Ns, const Sched& sc);
+// direction-split form of the hop (hop_split.hip): whether it is small enough for a launch of nr systems, its workgroups
+// per system, and the launch itself (no finishing kernel)
 bool hop_split(const Geom& g, int Ns, int nr);
 int hop_split_blocks(const Geom& g, int Ns);
 template <typename R> hipError_t launch_hop_split(int Ns, bool dag, int mode, bool red, const HopArgsMR<R>& a,
@@ -123,8 +124,13 @@ template <typename R> hipError_t launch_cg_xp_mr(int nr, cpx<R>* const* x, cpx<R
 template <typename R> hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& a, hipStream_t st);
 int tw_grid(const Geom& g, int Ns, const Sched& sc);
 // whether a launch under sc has a form of HM_LIN, HM_DT and HM_DW that writes a canonical field
-bool hop_canon(const Geom& g, int Ns, const Sched& sc);
+bool hop_canon(int Ns, const Sched& sc);
 Sched block_sched(const Geom& g, int Ns);
+// The order of a batch launch of nr systems where sc is installed: the batch kernels have no t-walk, and the split form
+// has a limit over all systems.
+inline Sched batch_sched(const Geom& g, int Ns, const Sched& sc, int nr) {
+    return sc.mode < 2 ? sc : hop_split(g, Ns, nr) ? kSplitSched : block_sched(g, Ns);
+}
 Sched default_sched(const Geom& g, int Ns, size_t real_bytes, bool half);
 template <typename R> hipError_t launch_site(int Ns, bool dag, const cpx<R>* in, cpx<R>* out, const SiteOp* op, int Vh,
                                              hipStream_t st);

@@ -305,8 +305,8 @@ __global__ __launch_bounds__(256) void k_hop_split(const HopArgsMR<R> a) {
 
 }  // namespace
 
-// A launch of at most kSplitLanes (site, s) lanes, all its systems together, takes the split form: up to there it has
-// at most three workgroups per CU and the four round trips of k_hop are not hidden.  us per hop, k_hop in
+// The split form is the default of a launch of at most kSplitLanes (site, s) lanes, all its systems together: up to
+// there k_hop has at most three waves per CU and its four round trips are not hidden.  us per hop, k_hop in
 // XCD-contiguous ranges -> split (FP64 / FP32 / FP16 columns):
 //   4^4, Ns = 8 (1,024 lanes)            8.8 -> 5.6    7.9 -> 5.2    8.0 -> 5.0
 //   8^4, Ns = 8 (16,384)                10.8 -> 7.6    9.1 -> 5.7    9.1 -> 5.3
@@ -320,7 +320,7 @@ int hop_split_blocks(const Geom& g, int Ns) { return (int)(((size_t)g.Vh * Ns + 
 
 template <typename R>
 hipError_t launch_hop_split(int Ns, bool dag, int mode, bool red, const HopArgsMR<R>& a, hipStream_t st, bool half) {
-    if (a.nr < 1 || a.nr > NRMAX) return hipErrorInvalidValue;
+    if (a.nr < 1 || a.nr > NRMAX || !hop_split(a.g, Ns, a.nr)) return hipErrorInvalidValue;
     const int grid = hop_split_blocks(a.g, Ns) + (a.fin_n ? 1 : 0);
 #define SPLIT_L(D, M, RD)                                                                                           \
     if constexpr (!hop_has(M, D) || (M == HM_SCHUR_RES && sizeof(R) == 4)) return hipErrorInvalidValue;             \

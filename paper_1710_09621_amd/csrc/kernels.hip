@@ -1525,8 +1525,9 @@ Sched block_sched(const Geom& g, int Ns) {
 // The schedule of a context that was never tuned.  FP64, and FP32 fields above the 256 MB Infinity Cache, take the
 // t-walk with the x neighbours from LDS where it fits and fills the chip (one FP64 solve on 16^3 x 32: 164 ms in
 // linear order, 149 ms; FP64 hop on 32^3 x 64: 2253 us in tiles, 2165 us; FP32 there 1260 -> 1182 us, but 77 -> 92
-// us on 16^3 x 32); the rest block_sched.
+// us on 16^3 x 32); launches of at most kSplitLanes (site, s) lanes the split form; the rest block_sched.
 Sched default_sched(const Geom& g, int Ns, size_t real_bytes, bool half) {
+    if (hop_split(g, Ns, 1)) return kSplitSched;
     const Sched bs = block_sched(g, Ns);
     if (!half && bs.nyb > 1 && (real_bytes == 8 || (size_t)g.Vh * Ns * 24 * real_bytes > ((size_t)256 << 20)))
         for (int tt = g.Lt; tt >= 16 && tt % 2 == 0; tt /= 2) {
@@ -1536,20 +1537,14 @@ Sched default_sched(const Geom& g, int Ns, size_t real_bytes, bool half) {
     return bs;
 }
 
-unsigned hop_partials(const Geom& g, int Ns, const Sched& sc, int nr) {
-    if (sc.mode == 3 || sc.mode == 5 || sc.mode == 6) return (unsigned)tw_grid(g, Ns, sc);
-    return hop_mr_partials(g, Ns, nr);
-}
-unsigned hop_mr_partials(const Geom& g, int Ns, int nr) {
-    return hop_split(g, Ns, nr) ? (unsigned)hop_split_blocks(g, Ns) : (unsigned)(((size_t)g.Vh * Ns + 255) / 256);
+unsigned hop_partials(const Geom& g, int Ns, const Sched& sc) {
+    if (is_twalk(sc)) return (unsigned)tw_grid(g, Ns, sc);
+    return sc.mode == 2 ? (unsigned)hop_split_blocks(g, Ns) : (unsigned)(((size_t)g.Vh * Ns + 255) / 256);
 }
 
 // The forms that apply_op takes by default below kSplitLanes and, at Ns = 16, for large fields; the others leave their
 // results in the internal order and launch_unpack5 moves them.
-bool hop_canon(const Geom& g, int Ns, const Sched& sc) {
-    const bool tw = sc.mode == 3 || sc.mode == 5 || sc.mode == 6;
-    return tw ? sc.mode == 6 && Ns == 16 : hop_split(g, Ns, 1);
-}
+bool hop_canon(int Ns, const Sched& sc) { return sc.mode == 2 || (sc.mode == 6 && Ns == 16); }
 
 // LDS that a launch of kern may reserve on top of its static LDS (gfx950: 160 KB per workgroup).
 template <typename K> static size_t lds_room(K kern) {
@@ -1562,9 +1557,9 @@ template <typename R>
 hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& args, hipStream_t st) {
     HopArgs<R> a = args;
     const size_t nthreads = (size_t)a.g.Vh * Ns;
-    const bool tw = a.sc.mode == 3 || a.sc.mode == 5 || a.sc.mode == 6;
+    const bool tw = is_twalk(a.sc);
     const bool reduces = red || mode == HM_SCHUR_W || mode == HM_SCHUR_Q;
-    if (!tw && hop_split(a.g, Ns, 1)) {
+    if (a.sc.mode == 2) {
         HopArgsMR<R> m{};
         m.g = a.g; m.par = a.par; m.nr = 1; m.Uown = a.Uown; m.Uoth = a.Uoth;
         m.in[0] = a.in; m.out[0] = a.out; m.out2[0] = a.out2; m.aux[0] = a.aux; m.aux2[0] = a.aux2;
@@ -1577,7 +1572,7 @@ hipError_t launch_hop(int Ns, bool dag, int mode, bool red, const HopArgs<R>& ar
         if (reduces && !a.defer) finish(a.red, (unsigned)hop_split_blocks(a.g, Ns), st);
         return hipGetLastError();
     }
-    if (a.canon && !hop_canon(a.g, Ns, a.sc)) return hipErrorInvalidValue;
+    if (a.canon && !hop_canon(Ns, a.sc)) return hipErrorInvalidValue;
     // a pending reduction: one more workgroup of the launches that follow HM_SCHUR_W, a launch of its own otherwise
     const bool fin_here = a.fin_n && mode == HM_SITE && dag && !red && !tw;
     if (a.fin_n && !fin_here) {
@@ -1649,10 +1644,10 @@ hipError_t launch_hop_mr(int Ns, bool dag, int mode, const HopArgsMR<R>& args, h
     HopArgsMR<R> a = args;
     if (a.nr < 1 || a.nr > NRMAX) return hipErrorInvalidValue;
     if (half && sizeof(R) != 4) return hipErrorInvalidValue;
-    const unsigned npart = hop_mr_partials(a.g, Ns, a.nr);
+    const unsigned npart = hop_partials(a.g, Ns, a.sc);
     if (npart > (unsigned)a.pstride) return hipErrorInvalidValue;
     const bool finishes = mode != HM_SITE && !a.defer;
-    if (hop_split(a.g, Ns, a.nr)) {
+    if (a.sc.mode == 2) {
         const hipError_t e = launch_hop_split<R>(Ns, dag, mode, false, a, st, half);
         if (e != hipSuccess) return e;
         if (finishes)

@@ -1,0 +1,62 @@
+"""Installed schedules are what runs: linear and tiled orders also where the direction-split form is the default, and
+the split form as a schedule of its own.  The operator has the same bits under every schedule; the reductions of CG
+blocks add in the order of the workgroups, so the last bits of a row of them tell which schedule ran."""
+import pytest
+import torch
+
+from gpu_common import ctx_and_oracle, rand5
+from paper_1710_09621_amd import inputs as IN
+
+pytestmark = pytest.mark.gpu
+
+SPLIT_LANES = 49152  # (site, s) lanes per parity up to which the split form exists
+
+
+def _lanes(dims, Ns):
+    return dims[0] * dims[1] * dims[2] * dims[3] // 2 * Ns
+
+
+def _block(ctx, phi, sched=None):
+    if sched is not None:
+        ctx.set_schedule(sched)
+    return [ctx.cg_block(+1, 0.05, 0.3, phi, n) for n in range(2, 34, 4)]
+
+
+# at the split form's limit, just above it, no whole lines (linear orders only)
+@pytest.mark.parametrize("dims,Ns", [((8, 8, 8, 8), 8), ((8, 8, 8, 12), 16), ((8, 8, 8, 14), 16), ((10, 6, 4, 6), 8)], ids=str)
+def test_small_lattices_run_the_installed_schedule(dims, Ns):
+    from paper_1710_09621_amd import eofa as E
+    print(f"[gpu] schedules dims={dims} Ns={Ns}", flush=True)
+    ctx, lat = ctx_and_oracle(dims, Ns)
+    small = _lanes(dims, Ns) <= SPLIT_LANES
+    phi = IN.gaussian_spinor(lat.shape4[:-2], 71)
+    x = torch.from_numpy(rand5(lat, 72)).cuda()
+    for prec in (E.FP64, E.MIXED_FP32, E.MIXED_FP16):
+        cands = ctx.schedule_candidates(prec)
+        assert [s for s in cands if s[0] == 2] == ([[2, 1, 1, 1, 1, 1, 0]] if small else []), prec
+        if prec == E.MIXED_FP16:
+            continue
+        base = ctx.apply("DT", x, 0.05, 0.3, prec=prec)
+        for s in (cands[0], cands[1], cands[-1]):
+            ctx.set_schedule(s, prec)
+            assert torch.equal(ctx.apply("DT", x, 0.05, 0.3, prec=prec), base), (prec, s)
+    fresh, _ = ctx_and_oracle(dims, Ns)
+    default, linear = _block(fresh, phi), _block(fresh, phi, cands[0])
+    assert all(abs(a / b - 1) < 1e-8 for a, b in zip(linear, default))  # rounding, amplified by the iteration
+    if small:  # four times as many workgroups, whose partial sums add in another order
+        assert linear != default
+        assert _block(fresh, phi, [2, 1, 1, 1, 1, 1, 0]) == default
+
+
+def test_autotuned_schedule_is_installed():
+    from paper_1710_09621_amd import eofa as E
+    dims, Ns = (8, 8, 8, 8), 8
+    print(f"[gpu] autotuned schedule dims={dims} Ns={Ns}", flush=True)
+    ctx, lat = ctx_and_oracle(dims, Ns)
+    phi = IN.gaussian_spinor(lat.shape4[:-2], 75)
+    for prec in (E.FP64, E.MIXED_FP32, E.MIXED_FP16):
+        r = ctx.autotune(prec=prec)
+        assert r["sched"] in ctx.schedule_candidates(prec) and r["best_ms"] <= r["base_ms"]
+        if prec == E.FP64:
+            got = _block(ctx, phi)
+            assert got == _block(ctx, phi, r["sched"])
