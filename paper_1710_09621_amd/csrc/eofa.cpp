@@ -1683,6 +1683,11 @@ void fill_bench_buffers(eofa_ctx* ctx) {
     HIPCHK(hipMemsetAsync(W.u, 0x3F, ctx->nh * sizeof(cd), ctx->st));
 }
 
+bool same_sched(const Sched& a, const Sched& b) {
+    return a.mode == b.mode && a.xcd == b.xcd && a.ty == b.ty && a.tz == b.tz && a.tt == b.tt && a.nyb == b.nyb &&
+           a.ord == b.ord;
+}
+
 std::vector<Sched> sched_candidates(const eofa_ctx* ctx, int prec) {
     std::vector<Sched> c;
     const Geom& g = ctx->g;
@@ -1733,6 +1738,11 @@ std::vector<Sched> sched_candidates(const eofa_ctx* ctx, int prec) {
                             if (!dup) c.push_back(s);
                         }
     }
+    // the default, whose t-walk may take a part of the t extent that is not in the list (16^3 x 64: half of it)
+    const Sched d = default_sched(g, ctx->Ns, prec == EOFA_FP64 ? sizeof(double) : sizeof(float), prec == EOFA_MIXED_FP16);
+    bool listed = false;
+    for (const Sched& o : c) listed |= same_sched(o, d);
+    if (!listed) c.push_back(d);
     return c;
 }
 
@@ -2579,9 +2589,7 @@ eofa_status eofa_set_schedule(eofa_ctx* ctx, int prec, const int sched_in[7]) {
                 "prec must be FP64, MIXED_FP32 or MIXED_FP16");
         Sched s{sched_in[0], sched_in[1], sched_in[2], sched_in[3], sched_in[4], sched_in[5], sched_in[6]};
         bool ok = false;
-        for (const Sched& c : sched_candidates(ctx, prec))
-            ok |= (c.mode == s.mode && c.xcd == s.xcd && c.ty == s.ty && c.tz == s.tz && c.tt == s.tt &&
-                   c.nyb == s.nyb && c.ord == s.ord);
+        for (const Sched& c : sched_candidates(ctx, prec)) ok |= same_sched(c, s);
         REQUIRE(ok, EOFA_EINVAL, "schedule not valid for this lattice");
         ctx->sched[prec] = s;
         return EOFA_OK;

@@ -1,10 +1,11 @@
-"""Installed schedules are what runs: linear and tiled orders also where the direction-split form is the default, and
-the split form as a schedule of its own.  The operator has the same bits under every schedule; the reductions of CG
-blocks add in the order of the workgroups, so the last bits of a row of them tell which schedule ran."""
+"""Installed schedules are what runs: linear and tiled orders also where the direction-split form is the default,
+the split form as a schedule of its own, and the default of every context among the autotuner's candidates.  The
+operator has the same bits under every schedule; the reductions of CG blocks add in the order of the workgroups, so the
+last bits of a row of them tell which schedule ran."""
 import pytest
 import torch
 
-from gpu_common import ctx_and_oracle, rand5
+from gpu_common import M0, ctx_and_oracle, rand5
 from paper_1710_09621_amd import inputs as IN
 
 pytestmark = pytest.mark.gpu
@@ -46,6 +47,20 @@ def test_small_lattices_run_the_installed_schedule(dims, Ns):
     if small:  # four times as many workgroups, whose partial sums add in another order
         assert linear != default
         assert _block(fresh, phi, [2, 1, 1, 1, 1, 1, 0]) == default
+
+
+# t-walk over half of the t extent (the whole one would leave half of the CUs idle), tiles, split form, ranges
+@pytest.mark.parametrize("dims,Ns", [((16, 16, 16, 64), 16), ((16, 16, 16, 8), 16), ((8, 8, 8, 8), 8), ((10, 6, 12, 14), 16)],
+                         ids=str)
+def test_default_schedule_is_a_candidate(dims, Ns):
+    from paper_1710_09621_amd import eofa as E
+    print(f"[gpu] default schedule dims={dims} Ns={Ns}", flush=True)
+    ctx = E.Context(dims, Ns, M0, IN.optimal_omega(Ns))
+    ctx.set_gauge(IN.gauge_links(dims, 0.5, 73))
+    phi = torch.randn(dims[::-1] + (4, 3), dtype=torch.complex128, device="cuda",
+                      generator=torch.Generator(device="cuda").manual_seed(74))
+    default = _block(ctx, phi)
+    assert any(_block(ctx, phi, s) == default for s in reversed(ctx.schedule_candidates(E.FP64)))
 
 
 def test_autotuned_schedule_is_installed():
