@@ -346,8 +346,9 @@ eofa_status eofa_dslash_bench(eofa_ctx *ctx, int prec, int nrep, double *ms, dou
  * 3: t-walk, 5: t-walk with the x neighbours from LDS, 6: mode 5 with two lanes per site and slice, Ns = 16);
  * *best_ms / *base_ms (may be NULL) the chosen and the linear-order launch times.
  * A context that was never tuned takes one by rule: the direction-split form up to its limit; above it the t-walk
- * for FP64 and for FP32 fields above 256 MB, tiles, linear order or XCD-contiguous ranges else.  The batch kernels,
- * which have no t-walk, take the split form or the rule's other orders where modes 2 to 6 are installed.
+ * for FP64 (Ns <= 16) and for FP32 fields above 256 MB; else linear order over lines of eight workgroups (FP32 and
+ * FP16 at Ns = 8: also of sixteen), tiles over other whole lines, and XCD-contiguous ranges.  The batch kernels, which
+ * have no t-walk, take the split form or the rule's orders unless mode 0 or 1 is installed.
  */
 eofa_status eofa_autotune(eofa_ctx *ctx, int prec, int nrep, int sched_out[7], double *best_ms,
                           double *base_ms);

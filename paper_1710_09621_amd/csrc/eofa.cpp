@@ -118,9 +118,10 @@ struct eofa_ctx {
     hipStream_t cap_st = nullptr;
     std::map<std::vector<uintptr_t>, hipGraphExec_t> graphs;
     long graph_replays = 0;
-    // workgroup schedules of the hop kernels per storage (0: FP64, 1: FP32, 2: FP16 columns): default_sched, or set by
-    // the autotuner
+    // workgroup schedules of the hop kernels per storage (0: FP64, 1: FP32, 2: FP16 columns): default_sched, or
+    // installed by the autotuner or the caller
     Sched sched[3] = {{0, 0, 1, 1, 1, 1, 0}, {0, 0, 1, 1, 1, 1, 0}, {0, 0, 1, 1, 1, 1, 0}};
+    bool installed[3] = {false, false, false};
     double tuned_ms[3] = {0, 0, 0};
 };
 
@@ -387,8 +388,9 @@ template <typename R> std::vector<uintptr_t> graph_key(const eofa_ctx* ctx, int 
                                                        std::initializer_list<const void*> ptrs, bool half = false) {
     std::vector<uintptr_t> k{(uintptr_t)kind, (uintptr_t)n, sizeof(R), (uintptr_t)ctx->scal,
                              (uintptr_t)ctx->partials, (uintptr_t)ctx->partials_mr, (uintptr_t)ctx->pstride};
-    const Sched& sc = ctx->sched[half ? 2 : (sizeof(R) == 8 ? 0 : 1)];
-    for (int v : {sc.mode, sc.xcd, sc.ty, sc.tz, sc.tt, sc.nyb, sc.ord}) k.push_back((uintptr_t)v);
+    const int st = half ? 2 : (sizeof(R) == 8 ? 0 : 1);
+    const Sched& sc = ctx->sched[st];
+    for (int v : {sc.mode, sc.xcd, sc.ty, sc.tz, sc.tt, sc.nyb, sc.ord, (int)ctx->installed[st]}) k.push_back((uintptr_t)v);
     for (const void* p : ptrs) k.push_back((uintptr_t)p);
     return k;
 }
@@ -1043,8 +1045,10 @@ void sync_scal_batch(eofa_ctx* ctx, int nr) {
 template <typename R> HopArgsMR<R> mr_args(eofa_ctx* ctx, int par, int nr, bool half = false) {
     HopArgsMR<R> a{};
     HopArgs<R> b = hop_args<R>(ctx, par);
-    a.g = b.g; a.sc = batch_sched(ctx->g, ctx->Ns, half ? ctx->sched[2] : b.sc, nr); a.par = par;
-    a.nr = nr; a.Uown = b.Uown; a.Uoth = b.Uoth;
+    const int st = half ? 2 : (sizeof(R) == 8 ? 0 : 1);
+    a.g = b.g; a.par = par; a.nr = nr;
+    a.sc = batch_sched(ctx->g, ctx->Ns, ctx->installed[st] ? &ctx->sched[st] : nullptr, sizeof(R), nr);
+    a.Uown = b.Uown; a.Uoth = b.Uoth;
     a.scal = ctx->scal + BATCH_OFF;
     a.done = a.scal + SC_DONE;
     a.partials = ctx->partials_mr;
@@ -2571,6 +2575,7 @@ eofa_status eofa_autotune(eofa_ctx* ctx, int prec, int nrep, int sched_out[7], d
             if (t < best) { best = t; bs = cand[i]; }
         }
         ctx->sched[k] = bs;
+        ctx->installed[k] = true;
         ctx->tuned_ms[k] = best;
         if (sched_out) {
             sched_out[0] = bs.mode; sched_out[1] = bs.xcd; sched_out[2] = bs.ty;
@@ -2592,6 +2597,7 @@ eofa_status eofa_set_schedule(eofa_ctx* ctx, int prec, const int sched_in[7]) {
         for (const Sched& c : sched_candidates(ctx, prec)) ok |= same_sched(c, s);
         REQUIRE(ok, EOFA_EINVAL, "schedule not valid for this lattice");
         ctx->sched[prec] = s;
+        ctx->installed[prec] = true;
         return EOFA_OK;
     });
 }

@@ -125,11 +125,12 @@ template <typename R> hipError_t launch_hop(int Ns, bool dag, int mode, bool red
 int tw_grid(const Geom& g, int Ns, const Sched& sc);
 // whether a launch under sc has a form of HM_LIN, HM_DT and HM_DW that writes a canonical field
 bool hop_canon(int Ns, const Sched& sc);
-Sched block_sched(const Geom& g, int Ns);
-// The order of a batch launch of nr systems where sc is installed: the batch kernels have no t-walk, and the split form
-// has a limit over all systems.
-inline Sched batch_sched(const Geom& g, int Ns, const Sched& sc, int nr) {
-    return sc.mode < 2 ? sc : hop_split(g, Ns, nr) ? kSplitSched : block_sched(g, Ns);
+Sched block_sched(const Geom& g, int Ns, size_t real_bytes);
+// The order of a batch launch of nr systems: the installed one if the batch kernels have it for any number of systems,
+// else (null, t-walk, split form) by rule.
+inline Sched batch_sched(const Geom& g, int Ns, const Sched* installed, size_t real_bytes, int nr) {
+    if (installed && installed->mode < 2) return *installed;
+    return hop_split(g, Ns, nr) ? kSplitSched : block_sched(g, Ns, real_bytes);
 }
 Sched default_sched(const Geom& g, int Ns, size_t real_bytes, bool half);
 template <typename R> hipError_t launch_site(int Ns, bool dag, const cpx<R>* in, cpx<R>* out, const SiteOp* op, int Vh,

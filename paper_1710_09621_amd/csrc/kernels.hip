@@ -1508,27 +1508,45 @@ static int pow2_divisor(int n, int cap) {  // the largest power of two <= cap th
     return p;
 }
 
-// Workgroup order by rule, for kernels that visit one tile of 256 lanes per workgroup.  Lines of eight workgroups stay
-// in linear order: workgroup b runs on XCD b % 8, so every XCD keeps one slab of y and finds its z and t neighbours
-// in its own L2 (three FP16-column systems on 16^3 x 32, Ns = 16: 193.6 ms a solve, 198.1 in tiles).  Other whole
-// lines take XCD-contiguous 3D tiles (FP64 hop, linear -> tiles: 24^3 x 48 1120 -> 742 us, 32^3 x 64 3355 -> 2253),
-// lattices without whole lines XCD-contiguous ranges (20^3 x 40: 578 -> 404).
-Sched block_sched(const Geom& g, int Ns) {
+// XCD-contiguous 3D tiles, or ranges where the extents have no tile of 16 workgroups
+static Sched tile_sched(const Geom& g, int nyb) {
+    const Sched tile{1, 1, pow2_divisor(nyb, 4), pow2_divisor(g.Lz, 4), pow2_divisor(g.Lt, 8), nyb, 0};
+    return tile.ty * tile.tz * tile.tt >= 16 ? tile : Sched{0, 1, 1, 1, 1, nyb, 0};
+}
+
+// Workgroup order by rule, for kernels that visit one tile of 256 lanes per workgroup.
+// Lattices without whole lines take XCD-contiguous ranges (FP64 hop on 20^3 x 40: linear 578 us, 404).  Whole lines take
+// XCD-contiguous 3D tiles (24^3 x 48 1120 -> 742 us, 32^3 x 64 3355 -> 2253), except where linear order finds the same
+// neighbours with less: workgroup b runs on XCD b % 8, so with nyb (workgroups per line) = 8 every XCD keeps one slab
+// of y and finds its z and t neighbours in its own L2.  us per CG iteration, linear / tiles:
+//   nyb = 8: 16^3 x 32, Ns = 16, FP16 columns, 3 systems 823 / 841, 8 systems 2240 / 2314; FP32, 3 systems 1336 / 1386;
+//     8 x 16^2 x 32, Ns = 32, FP32 451 / 471; FP64 batches of 3 (single FP64 solves take the t-walk): 16^3 x 32
+//     2555 / 2620, 8 x 16^2 x 32, Ns = 32 2633 / 2755, 32 x 16^3, Ns = 8 1347 / 1317.
+//   nyb = 16, Ns = 8, where links are half of what a hop reads: 32^2 x 16 x 32 FP32 1091 / 1134 (3 systems 2999 / 3130),
+//     FP16 673 / 706 (1856 / 1923); 16 x 64 x 16^2 FP32 522 / 545 (1501 / 1522); 32^2 x 8 x 16 FP16 182 / 188 (473 / 482).
+//   nyb = 24, 32, Ns = 8, FP32: 48 x 32 x 16^2 843 / 861 (2387 / 2312); 64 x 32 x 8 x 16 559 / 553 (1626 / 1562).
+//   nyb = 16 .. 40, Ns = 16: single solves within 5% either way (FP32: mean of 16 lattices equal; 24 x 32 x 16 x 32
+//     1403 / 1468, 32^2 x 16^2 1021 / 978), batches of 3 up to 13% faster in tiles (32^2 x 16^2 3111 / 2756).
+//   FP64, nyb = 16: 32 x 16^2 x 32, Ns = 16, 3 systems 6407 / 5356; 32^2 x 16 x 32, Ns = 8 5781 / 5381.
+Sched block_sched(const Geom& g, int Ns, size_t real_bytes) {
     const long lanes_line = (long)g.Lxh * g.Ly * Ns;
     const int nyb = lanes_line % 256 == 0 ? (int)(lanes_line / 256) : 0;
     if (nyb == 0) return Sched{0, 1, 1, 1, 1, 1, 0};
-    if (nyb == 8) return Sched{0, 0, 1, 1, 1, nyb, 0};
-    const Sched tile{1, 1, pow2_divisor(nyb, 4), pow2_divisor(g.Lz, 4), pow2_divisor(g.Lt, 8), nyb, 0};
-    return tile.ty * tile.tz * tile.tt >= 16 ? tile : Sched{0, 1, 1, 1, 1, nyb, 0};
+    if (nyb == 8 || (nyb == 16 && Ns == 8 && real_bytes == 4)) return Sched{0, 0, 1, 1, 1, nyb, 0};
+    return tile_sched(g, nyb);
 }
 
 // The schedule of a context that was never tuned.  FP64, and FP32 fields above the 256 MB Infinity Cache, take the
 // t-walk with the x neighbours from LDS where it fits and fills the chip (one FP64 solve on 16^3 x 32: 164 ms in
 // linear order, 149 ms; FP64 hop on 32^3 x 64: 2253 us in tiles, 2165 us; FP32 there 1260 -> 1182 us, but 77 -> 92
-// us on 16^3 x 32); launches of at most kSplitLanes (site, s) lanes the split form; the rest block_sched.
+// us on 16^3 x 32); launches of at most kSplitLanes (site, s) lanes the split form; the rest block_sched's order.
+// FP64 at Ns = 32 is tiled instead: its t-walk (mode 5, 112 KB of LDS) has four waves on a CU where mode 6 has eight,
+// and they wait for the lane exchanges, which are LDS round trips at Ns = 32 (hop, t-walk / linear / tiles: 16^3 x 32
+// 328 / 350 / 288 us, 16^4 164 / 184 / 140, 8 x 16^2 x 32 160 / 147 / 137, 16 x 8 x 16 x 32 160 / 177 / 141).
 Sched default_sched(const Geom& g, int Ns, size_t real_bytes, bool half) {
     if (hop_split(g, Ns, 1)) return kSplitSched;
-    const Sched bs = block_sched(g, Ns);
+    const Sched bs = block_sched(g, Ns, real_bytes);
+    if (real_bytes == 8 && Ns == 32 && bs.nyb > 1) return tile_sched(g, bs.nyb);
     if (!half && bs.nyb > 1 && (real_bytes == 8 || (size_t)g.Vh * Ns * 24 * real_bytes > ((size_t)256 << 20)))
         for (int tt = g.Lt; tt >= 16 && tt % 2 == 0; tt /= 2) {
             const Sched tw{Ns == 16 ? 6 : 5, 1, pow2_divisor(bs.nyb, 4), pow2_divisor(g.Lz, 4), tt, bs.nyb, 0};

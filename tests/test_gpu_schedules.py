@@ -5,7 +5,7 @@ last bits of a row of them tell which schedule ran."""
 import pytest
 import torch
 
-from gpu_common import M0, ctx_and_oracle, rand5
+from gpu_common import M0, ctx_and_oracle, rand5, relerr
 from paper_1710_09621_amd import inputs as IN
 
 pytestmark = pytest.mark.gpu
@@ -75,3 +75,33 @@ def test_autotuned_schedule_is_installed():
         if prec == E.FP64:
             got = _block(ctx, phi)
             assert got == _block(ctx, phi, r["sched"])
+
+
+def test_fp64_default_is_tiled_at_ns32():
+    """Its t-walk is the slower form on every lattice that has it (8 x 16 x 16 x 32: slower than linear order)."""
+    from paper_1710_09621_amd import eofa as E
+    dims, Ns = (8, 16, 16, 32), 32
+    print(f"[gpu] default schedule dims={dims} Ns={Ns}", flush=True)
+    ctx = E.Context(dims, Ns, M0, IN.optimal_omega(Ns))
+    ctx.set_gauge(IN.gauge_links(dims, 0.5, 76))
+    phi = torch.randn(dims[::-1] + (4, 3), dtype=torch.complex128, device="cuda",
+                      generator=torch.Generator(device="cuda").manual_seed(77))
+    default = _block(ctx, phi)
+    assert _block(ctx, phi, [1, 1, 4, 4, 8, 8, 0]) == default
+    assert _block(ctx, phi, [5, 1, 4, 4, 32, 8, 0]) != default
+
+
+# lines of 16 workgroups at Ns = 8: linear order in FP32 and FP16, tiles in FP64; batches at Ns = 32, where a single FP64
+# solve is tiled and a batch linear
+@pytest.mark.parametrize("dims,Ns", [((32, 32, 4, 4), 8), ((16, 8, 8, 6), 32)], ids=str)
+@pytest.mark.parametrize("prec", [0, 1, 2], ids=["fp64", "fp32", "fp16"])
+def test_batches_in_the_orders_of_the_rule(dims, Ns, prec):
+    from paper_1710_09621_amd import eofa as E
+    print(f"[gpu] batch orders dims={dims} Ns={Ns} prec={prec}", flush=True)
+    ctx, lat = ctx_and_oracle(dims, Ns)
+    masses = [(0.1 + 0.05 * j, 0.5) for j in range(3)]
+    bs = [torch.from_numpy(rand5(lat, 78 + j)).cuda() for j in range(3)]
+    for (mp, mm), b, (x, info) in zip(masses, bs, ctx.solve_ht_batch(masses, bs, E.params(tol=1e-11, prec=prec))):
+        assert info["true_rel_resid"] <= 1e-11 and info["fell_back"] == 0
+        one, _ = ctx.solve_ht(b, mp, mm, E.params(tol=1e-11))
+        assert relerr(x, one.cpu().numpy()) < 1e-8
