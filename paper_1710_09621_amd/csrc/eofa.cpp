@@ -340,6 +340,12 @@ void collect_timing(eofa_ctx* ctx) {
     ctx->ev_used = 0;
 }
 
+// Kept graphs: 64 sets of mass tables and buffers, as a program that cycles over its actions has them.  A set has up to
+// eight: blocks come in four lengths (BlockRule), and a solve and the corrections after it differ in the vector they
+// solve in (64 mass pairs on 4^4 in FP64: 111 graphs, on 8^4 in FP16 columns 224).  A graph takes some 50 KB of host and
+// 200 KB of device memory.
+constexpr size_t kMaxGraphs = 64 * 8;
+
 // Launch the work of body() (kernel launches on ctx->st only: no host synchronisation, copies or
 // memsets) as one replay of a captured graph.  The capture runs once per key on a private stream
 // (the caller's stream may be the legacy default stream, which cannot be captured) and the
@@ -348,7 +354,7 @@ void collect_timing(eofa_ctx* ctx) {
 template <typename F> void graph_run(eofa_ctx* ctx, std::vector<uintptr_t> key, F&& body) {
     auto it = ctx->graphs.find(key);
     if (it == ctx->graphs.end()) {
-        if (ctx->graphs.size() >= 64) {
+        if (ctx->graphs.size() >= kMaxGraphs) {
             for (auto& kv : ctx->graphs) (void)hipGraphExecDestroy(kv.second);
             ctx->graphs.clear();
         }
