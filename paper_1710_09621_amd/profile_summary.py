@@ -35,8 +35,8 @@ import os
 import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-KERNEL_SOURCES = ["paper_1710_09621_amd/csrc/kernels.hip", "paper_1710_09621_amd/csrc/hop_dev.h",
-                  "paper_1710_09621_amd/csrc/eofa_dev.h",
+KERNEL_SOURCES = ["paper_1710_09621_amd/csrc/kernels.hip", "paper_1710_09621_amd/csrc/hop_split.hip",
+                  "paper_1710_09621_amd/csrc/hop_dev.h", "paper_1710_09621_amd/csrc/eofa_dev.h",
                   "paper_1710_09621_amd/csrc/eofa_int.h"]
 
 
@@ -71,6 +71,8 @@ def hop_kernel_name(sched):
         return "eofa::k_hop_tw<16, false, 1, false, double, true>"
     if sched[0] == 3:
         return "eofa::k_hop_tw<16, false, 1, false, double, false>"
+    if sched[0] == 2:
+        return "eofa::(anonymous namespace)::k_hop_split<16, false, 1, false, double, false>"
     return "eofa::k_hop<16, false, 1, false, double>"
 
 
@@ -153,12 +155,13 @@ def traffic(fetch_dir, write_dir, out_json, fetch_cmd, write_cmd, fetch_stdout=N
            "calibration": {"kernel": f"k_site<16, false, double> (reads and writes one FP64 half field, {half} bytes "
                                      "each way)", "fetch_kib": cal_f, "write_kib": cal_w,
                            "fetch_factor": round(ff, 4), "write_factor": round(wf, 4)},
-           "kernels": "schedule mode 0/1: k_hop, 3: k_hop_tw, 5: k_hop_tw with the x neighbours from LDS, 6: k_hop_tws",
+           "kernels": "schedule mode 0/1: k_hop, 2: k_hop_split, 3: k_hop_tw, 5: k_hop_tw with the x neighbours from LDS, "
+                      "6: k_hop_tws",
            "algorithmic_bytes_per_launch": alg, "by_schedule": {}, "source_sha1": source_sha1(),
            "source_files": KERNEL_SOURCES}
 
     def hops(rows):
-        return [v for nm, v in rows if re.search(r"k_hop(_tws?)?<16, false, 1, false, double", nm)]
+        return [v for nm, v in rows if re.search(r"k_hop(_tws?|_split)?<16, false, 1, false, double", nm)]
     hf, hw = hops(f), hops(w)
     assert len(hf) == len(hw) == len(scheds) * (nrep + 2), (len(hf), len(hw), len(scheds))
     # profile_hop.py: per schedule, 2 untimed + nrep timed launches; keep the nrep timed ones
@@ -192,7 +195,7 @@ def _cg_class(name):
     import re
     if "k_cg_xp<double" in name:
         return "xp"
-    m = re.search(r"k_hop(?:_tws?)?<16, (false|true), (\d), (?:false|true), double", name)
+    m = re.search(r"k_hop(?:_tws?|_split)?<16, (false|true), (\d), (?:false|true), double", name)
     if not m:
         return None
     return {("false", "1"): "hop", ("false", "2"): "schur_w", ("true", "1"): "hop_dag",
