@@ -13,7 +13,7 @@ epilogue) over the timed steps.
 Once per invocation, outside the timed steps, the whole sequence is solved to a true residual of 1e-10 on one
 Gaussian source in plain FP64 CG and in the tuned solver (the three systems in one multi-RHS launch sequence,
 FP16-column Krylov storage with FP32 arithmetic and FP64 reliable updates, autotuned schedules, hipGraph blocks
-of 16 iterations); their times and iteration counts go into "tts".  Then one HMC trajectory of the same
+of up to 16 iterations); their times and iteration counts go into "tts".  Then one HMC trajectory of the same
 splitting on the 16^3 x 32 workload (heat-bath, three-scale Omelyan molecular dynamics, Metropolis) goes into
 "hmc".  Inputs are generated on the host and moved to HBM before anything is timed.  Prints one JSON line.
 """
@@ -264,7 +264,7 @@ def main():
                "tuned_s": round(tc - tb, 3), "tuned_iters": [r.info[0]["iters"] for r in tuned],
                "tuned": f"multi-RHS batch (the {len(actions)} systems in one launch sequence), "
                         f"{args.tuned_prec.upper()}-storage reliable-update CG, autotuned hop schedule, hipGraph "
-                        f"blocks of 16 iterations ({g1['replays'] - g0['replays']} replays)",
+                        f"blocks of up to 16 iterations ({g1['replays'] - g0['replays']} replays)",
                "speedup": round((tb - ta) / (tc - tb), 3), "max_true_rel_resid": max(resid), "max_rel_dS": dS,
                "sources": 1}
         log(f"time to solution: plain {tb - ta:.2f}s, tuned {tc - tb:.2f}s ({tts['speedup']:.2f}x)")

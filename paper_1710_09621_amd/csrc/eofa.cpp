@@ -2210,7 +2210,7 @@ eofa_status eofa_md_trajectory(eofa_ctx* ctx, void* U, double* P, int nact, cons
         for (int j = 1; j < md->nlevels; j++)
             REQUIRE(md->steps[j - 1] % (2 * md->steps[j]) == 0, EOFA_EINVAL,
                     "steps[j - 1] must be a multiple of 2 steps[j]");
-        // every link update is a kernel plus a repack: bound the work of one call
+        // bound the work of one call: a gauge force and a link update per innermost step
         REQUIRE((long)md->steps[0] <= 100000, EOFA_EINVAL, "too many steps");
         for (int i = 0; i < nact; i++) {
             REQUIRE(acts[i].level >= 1 && acts[i].level < md->nlevels, EOFA_EINVAL, "action level out of range");

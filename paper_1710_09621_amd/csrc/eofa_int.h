@@ -90,7 +90,7 @@ template <typename R> struct HopArgsMR {
     unsigned fin_n;
     int fin_epi;
 };
-// half: FP16-column Krylov fields (R = float; see load_h / store_h in kernels.hip)
+// half: FP16-column Krylov fields (R = float; see load_h / store_h in hop_dev.h)
 template <typename R> hipError_t launch_hop_mr(int Ns, bool dag, int mode, const HopArgsMR<R>& a, hipStream_t st,
                                                bool half = false);
 // The residual's partial sums (n > 0 of system r at partials + r pstride) that the x/p update finishes itself: every

@@ -225,7 +225,7 @@ __device__ __forceinline__ void spread_links(v2d* buf, const v2d r[9], int lane,
 // 753 us; the waves share most of them, though: U_nu(x + mu) and U_mu(x + nu) are both in the links of the forward
 // neighbours, U_mu(x - nu) and U_nu(x - nu) in those of the backward neighbours, U_nu(x) and U_mu(x) in those of x.
 // Wave w reads the four links of x + w, later of x - w, for all four waves, and only U_nu(x + mu - nu) for itself
-// (29 loads): 626 us (16^3 x 32: 194 -> 131 us).
+// (29 loads): 600 us a pass (16^3 x 32: 194 -> 131 us).
 __global__ __launch_bounds__(256) void k_gauge_force(const cd* __restrict__ U, Geom g, double beta,
                                                      double* __restrict__ F, double* __restrict__ P, double h,
                                                      int kick) {

@@ -61,7 +61,7 @@ __device__ __forceinline__ void neighbours_mu(const Geom& g, int cb, int par, in
     nk = c == 0 ? cb + (L - 1) * st : cb - st;
 }
 
-// The two link products of direction MU: wf = U (1 + SF gamma) projection of pf, wb = U^dag (1 - SF gamma) of pb.
+// The half-spinors of direction MU: hf = (1 + SF gamma) projection of pf, hb = (1 - SF gamma) projection of pb.
 template <int MU, int SF, typename R>
 __device__ __forceinline__ void project2(const cpx<R> pf[12], const cpx<R> pb[12], cpx<R> hf[6], cpx<R> hb[6]) {
     project<MU, SF>(pf, hf);

@@ -839,7 +839,10 @@ __global__ __launch_bounds__(512, 1) void k_hop_tws(const HopArgs<R> a) {
 template <int NS, bool DAG, int MODE, typename R, bool H>
 __global__ __launch_bounds__(256, HOP_WAVES) void k_hop_mr(const HopArgsMR<R> a) {
     if constexpr (MODE == HM_SITE && DAG) {
-        if (a.fin_n && blockIdx.x == gridDim.x - 1) {  // the pending reductions of an earlier launch
+        // The pending reductions of an earlier launch.  They end within the launch's own last wave on 16^3 x 32 (3 or 8
+        // systems of 4,096 sums: 138 and 324 us, the same hop without them 145 and 340); 8 systems of 65,536 on 32^3 x 64
+        // add at most 80 us to 5,400 of an iteration's 37,000, and one workgroup per system does not change that.
+        if (a.fin_n && blockIdx.x == gridDim.x - 1) {
             for (int r = blockIdx.y * a.rpb; r < min(a.nr, (int)(blockIdx.y + 1) * a.rpb); r++)
                 finish_partials(a.fin_partials + (size_t)r * a.pstride, a.fin_n, a.scal + r * SC_N, 0, a.fin_epi);
             return;
